@@ -542,8 +542,9 @@ void vopp_server_free(vopp_server* s);
 enum {
   VOPP_KERNEL_FORWARD = 0,      /* all levels of one iteration's search      */
   VOPP_KERNEL_ACCUMULATE = 1,   /* shallow and shared visits from the trace  */
-  VOPP_KERNEL_BACKUP_LEAF = 2,  /* leaf values (Alg. 3, leaves)              */
-  VOPP_KERNEL_BACKUP_LEVEL = 3, /* one depth of the backup (Alg. 3 loop)     */
+  VOPP_KERNEL_BACKUP_LEAF = 2,  /* leaves that several episodes reached      */
+  VOPP_KERNEL_BACKUP_LEVEL = 3, /* the rest of the backup but the root (all
+                                   depths of one iteration, Alg. 3 loop)     */
   VOPP_KERNEL_BACKUP_ROOT = 4,  /* root backup in double precision           */
   VOPP_KERNEL_SETUP = 5,        /* table clearing and root initialisation    */
   VOPP_KERNEL_SELECT = 6,       /* argmax of the root preferences            */

@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -61,6 +62,37 @@ static void row_thresholds(const float* p, int n, uint32_t* out) {
     out[j] = (uint32_t)v;
   }
   out[n - 1] = (uint32_t)two31;
+}
+
+// The layout of rows of n thresholds (RowIndex), and one row written so.
+static RowIndex row_index(int n) {
+  RowIndex x;
+  std::memset(&x, 0, sizeof(x));
+  x.n = n;
+  std::vector<int> size{n};                       // bottom level first
+  while (size.back() > kRowTop) size.push_back((size.back() + 7) / 8);
+  x.levels = (int)size.size();
+  const int pad = x.levels > 1 ? 8 : 4;
+  int at = 0;
+  for (int l = 0; l < x.levels; ++l) {
+    x.off[l] = at;
+    const int sz = (size[x.levels - 1 - l] + pad - 1) / pad * pad;
+    if (l == 0) x.top = sz;
+    at += sz;
+  }
+  x.stride = at;
+  return x;
+}
+static void write_row(const RowIndex& x, const uint32_t* thr, uint32_t* out) {
+  std::fill(out, out + x.stride, ~0u);
+  std::copy(thr, thr + x.n, out + x.off[x.levels - 1]);
+  int n = x.n;
+  for (int l = x.levels - 2; l >= 0; --l) {
+    const uint32_t* below = out + x.off[l + 1];
+    const int groups = (n + 7) / 8;
+    for (int g = 0; g < groups; ++g) out[x.off[l] + g] = below[std::min(8 * g + 7, n - 1)];
+    n = groups;
+  }
 }
 
 static bool valid_row(const float* p, int n) {
@@ -154,11 +186,22 @@ extern "C" vopp_status vopp_pomdp_tabular(const vopp_tabular_desc* d, vopp_pomdp
       hmax = std::max(hmax, (double)std::fabs(d->heur[i]));
     }
 
-  std::vector<uint32_t> thrT(nnz), thrZ((size_t)rows * d->nO);
+  int n_succ = d->rowptr[1];                      // 0: rows of different lengths
+  for (long long r = 0; r < rows && n_succ; ++r)
+    if (d->rowptr[r + 1] - d->rowptr[r] != n_succ) n_succ = 0;
+  const RowIndex rT = row_index(std::max(1, n_succ)), rZ = row_index(d->nO);
+  std::vector<uint32_t> thrT(n_succ ? (size_t)rows * rT.stride : (size_t)nnz),
+      thrZ((size_t)rows * rZ.stride), thr(std::max(n_succ, d->nO));
   for (long long r = 0; r < rows; ++r) {
     int lo = d->rowptr[r], n = d->rowptr[r + 1] - lo;
-    row_thresholds(d->tprob + lo, n, thrT.data() + lo);
-    row_thresholds(d->zprob + r * d->nO, d->nO, thrZ.data() + r * d->nO);
+    if (n_succ) {
+      row_thresholds(d->tprob + lo, n, thr.data());
+      write_row(rT, thr.data(), thrT.data() + r * rT.stride);
+    } else {
+      row_thresholds(d->tprob + lo, n, thrT.data() + lo);
+    }
+    row_thresholds(d->zprob + r * d->nO, d->nO, thr.data());
+    write_row(rZ, thr.data(), thrZ.data() + r * rZ.stride);
   }
 
   vopp_pomdp* p = new vopp_pomdp();
@@ -170,7 +213,8 @@ extern "C" vopp_status vopp_pomdp_tabular(const vopp_tabular_desc* d, vopp_pomdp
   p->branch = (double)d->nA * d->nO;
   (void)hipGetDevice(&p->device);
   size_t bytes = 0;
-  bytes += align_up((rows + 1) * 4, 256) + align_up((size_t)nnz * 4, 256) * 2;
+  bytes += align_up((rows + 1) * 4, 256) + align_up((size_t)nnz * 4, 256) +
+           align_up(thrT.size() * 4, 256);
   bytes += align_up(thrZ.size() * 4, 256) + align_up(rows * 4, 256) +
            align_up((size_t)d->nS * 4, 256) + align_up((size_t)prior_len(d->nA) * 8, 256) + 1024;
   hipError_t e = hipMalloc(&p->arena, bytes);
@@ -179,14 +223,14 @@ extern "C" vopp_status vopp_pomdp_tabular(const vopp_tabular_desc* d, vopp_pomdp
   Carver c(p->arena);
   int* rowptr = c.take<int>(rows + 1);
   int* col = c.take<int>(nnz);
-  uint32_t* tT = c.take<uint32_t>(nnz);
+  uint32_t* tT = c.take<uint32_t>(thrT.size());
   uint32_t* tZ = c.take<uint32_t>(thrZ.size());
   float* R = c.take<float>(rows);
   float* H = d->heur ? c.take<float>(d->nS) : nullptr;
   double* logpi0 = c.take<double>(prior_len(d->nA));
   e = hipMemcpy(rowptr, d->rowptr, (rows + 1) * 4, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(col, d->col, (size_t)nnz * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(tT, thrT.data(), (size_t)nnz * 4, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(tT, thrT.data(), thrT.size() * 4, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(tZ, thrZ.data(), thrZ.size() * 4, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(R, d->reward, rows * 4, hipMemcpyHostToDevice);
   if (e == hipSuccess && H) e = hipMemcpy(H, d->heur, (size_t)d->nS * 4, hipMemcpyHostToDevice);
@@ -196,6 +240,9 @@ extern "C" vopp_status vopp_pomdp_tabular(const vopp_tabular_desc* d, vopp_pomdp
   std::memset(&m, 0, sizeof(m));
   m.kind = kTabular;
   m.nS = d->nS; m.nA = d->nA; m.nO = d->nO;
+  m.n_succ = n_succ;
+  m.rT = rT;
+  m.rZ = rZ;
   m.Apad = (d->nA + 3) / 4 * 4;
   m.rowptr = rowptr; m.col = col; m.thrT = tT; m.thrZ = tZ; m.R = R; m.H = H;
   m.logpi0 = logpi0;
@@ -325,7 +372,7 @@ size_t bytes_for(const WsSizes& z) {
   auto add = [&](size_t n) { b += align_up(n, 256); };
   const size_t cb = (size_t)z.cap_b;                 // the belief field arrays
   add(cb * z.Apad * 4); add(cb * z.Apad * 4); add(cb * z.Apad * 8); add(cb * z.Apad * 8);
-  add(cb * sizeof(BeliefHot)); add(cb * sizeof(BeliefLeaf));
+  add(cb * sizeof(BeliefNode)); add(cb * sizeof(BeliefInfo));
   add(cb * (size_t)rec_bitmap_words(z.Apad) * 4);
   add(z.hcap * sizeof(HSlot));                       // table
   const size_t ar = (size_t)std::max(kMaxA, z.Apad);
@@ -333,13 +380,13 @@ size_t bytes_for(const WsSizes& z) {
   add(ar * 8);                                       // running sums of the initial row
   add(ar * 4);                                       // initial preference row
   add((size_t)3 * z.Apad * kStripes * 8);            // striped root action nodes
-  add((size_t)z.steps * z.n_p * 4);                  // level-step lists
+  add((size_t)z.steps * z.n_p * 4);                  // runs and full beliefs
   add(64); add(kStatRows * kStripes * 8); add(32); add((z.K + 1) * 4);
   add(2 * (kMaxDepth + 1) * 4);                      // kept-subtree steps by depth
   add((size_t)(z.depth + 1) * z.n_p * 8);            // trace words
   add((size_t)(z.depth + 1) * z.n_p * 4);            // trace values
   add(out_len(z) * 8);                               // result record
-  return b + 4096;
+  return b + 4096;                                   // and the full beliefs' counts
 }
 
 bool fits(const WsSizes& have, const WsSizes& need) {
@@ -350,8 +397,7 @@ bool fits(const WsSizes& have, const WsSizes& need) {
 
 // Lays out the buffers of one plan's tree (sizes z) in device memory at base,
 // bytes_for(z) of it, in the order bytes_for counts them.
-void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, int** step_base,
-                double** out) {
+void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, double** out) {
   Carver c(base);
   const size_t cb = (size_t)z.cap_b;
   t.ra = z.Apad;
@@ -360,8 +406,8 @@ void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, int*
   t.nv = c.take<int>(cb * z.Apad);
   t.cv = c.take<unsigned long long>(cb * z.Apad);
   t.wv = c.take<unsigned long long>(cb * z.Apad);
-  t.hot = c.take<BeliefHot>(cb);
-  t.leaf = c.take<BeliefLeaf>(cb);
+  t.node = c.take<BeliefNode>(cb);
+  t.info = c.take<BeliefInfo>(cb);
   t.bits = c.take<uint32_t>(cb * (size_t)t.bw);
   t.h_slot = c.take<HSlot>(z.hcap);
   t.h_mask = (uint32_t)(z.hcap - 1);
@@ -378,11 +424,10 @@ void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, int*
   t.gate = c.take<unsigned long long>(4);
   *carry_rng = c.take<int>(2 * (kMaxDepth + 1));
   t.carry_rng = *carry_rng;
-  *step_base = c.take<int>(z.K + 1);
-  t.step_base = *step_base;
   t.tr_key = c.take<unsigned long long>((size_t)(z.depth + 1) * z.n_p);
   t.tr_val = c.take<float>((size_t)(z.depth + 1) * z.n_p);
   *out = c.take<double>(out_len(z));
+  t.full_cnt = c.take<unsigned int>(kMaxDepth + 1);
 }
 
 vopp_status ws_alloc(const WsSizes& z, vopp_workspace** out) {
@@ -397,30 +442,14 @@ vopp_status ws_alloc(const WsSizes& z, vopp_workspace** out) {
                 hipGetErrorString(e));
   }
   TreeView& t = w->tree;
-  carve_tree(w->arena, z, t, &w->carry_rng_dev, &w->step_base_dev, &w->out_dev);
+  carve_tree(w->arena, z, t, &w->carry_rng_dev, &w->out_dev);
   e = hipHostMalloc((void**)&w->out_host, out_len(z) * sizeof(double), hipHostMallocDefault);
-  if (e == hipSuccess)
-    e = hipHostMalloc((void**)&w->step_host, (kMaxBudget + 8) * sizeof(int), hipHostMallocDefault);
-  if (e == hipSuccess) {
-    // step_host[kMaxBudget + 1 ..] holds the 64-bit constant 1 (dirty flag).
-    const unsigned long long one = 1ull;
-    std::memcpy(&w->step_host[kMaxBudget + 1], &one, sizeof(one));
-  }
   if (e == hipSuccess) e = hipEventCreate(&w->ev0);
   if (e == hipSuccess) e = hipEventCreate(&w->ev1);
   if (e != hipSuccess) {
     vopp_workspace_free(w);
     return hip_fail(e, "workspace set-up");
   }
-  // Counters: [3] = 1 marks the belief table as dirty (fully cleared by the
-  // next plan's set-up).
-  unsigned long long init[8] = {0, 0, 0, 1, 0, 0, 0, 0};
-  e = hipMemcpy(t.counters, init, sizeof(init), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    vopp_workspace_free(w);
-    return hip_fail(e, "workspace counters");
-  }
-  w->hash_dirty = false;
   *out = w;
   return VOPP_OK;
 }
@@ -466,7 +495,6 @@ extern "C" void vopp_workspace_free(vopp_workspace* w) {
   if (!w) return;
   if (w->arena) (void)hipFree(w->arena);
   if (w->out_host) (void)hipHostFree(w->out_host);
-  if (w->step_host) (void)hipHostFree(w->step_host);
   if (w->gate_host) (void)hipHostFree(w->gate_host);
   if (w->ev0) (void)hipEventDestroy(w->ev0);
   if (w->ev1) (void)hipEventDestroy(w->ev1);
@@ -487,6 +515,16 @@ int fixed_shift(const vopp_pomdp* p, double visits) {
   const double lg = std::log2(visits * vmax);
   int S = (int)std::floor(61.0 - lg);
   return std::min(std::max(S, 4), 40);
+}
+
+// Slots of the belief table a plan uses, less one: at most one belief per
+// episode and iteration (and every kept one) is in it, at a load of 1/2.  The
+// workspace's table holds the beliefs of all level steps, so it is as long or
+// longer.
+uint32_t table_mask(int n_p, long long runs) {
+  uint64_t h = 1024;
+  while (h < 2 * (1 + (uint64_t)n_p * (uint64_t)runs)) h <<= 1;
+  return (uint32_t)(h - 1);
 }
 
 PlanView make_view(const vopp_pomdp* p, vopp_workspace* w, const void* belief,
@@ -513,24 +551,46 @@ PlanView make_view(const vopp_pomdp* p, vopp_workspace* w, const void* belief,
   P.K = K;
   P.depth = depth;
   P.schedule = prm->schedule;
-  P.steps = sum_depths(K, depth, prm->schedule) + (carry ? w->carry.n_steps : 0);
+  P.carry_steps = carry ? w->carry.n_steps : 0;
   P.carry = carry ? 1 : 0;
+  P.t.h_mask = carry ? w->carry.h_mask : table_mask(prm->n_particles, K);
+  P.t.run = reinterpret_cast<unsigned short*>(P.t.list);
+  P.t.full = P.t.list + ((size_t)K * prm->n_particles + 1) / 2;
   P.out = w->out_dev;
   return P;
 }
 
-// Grid for a backup sweep over the beliefs of depth `dep` after iteration k.
-int backup_grid(const vopp_pomdp* p, int n_p, const int* D, int dep, int k,
-                int cap, int extra, bool wide) {
-  (void)p;
-  // One chunk of record positions per block over the level steps that hold
-  // depth dep: kBlock positions (a thread each), or 64 for the sweeps of long
-  // rows (a wavefront per 16 positions), which may use four times the blocks.
-  long long iters = extra;
-  for (int kk = 1; kk <= k; ++kk) iters += D[kk] >= dep ? 1 : 0;
-  const int per = wide ? 64 : kBlock;
-  const long long g = ((long long)n_p + per - 1) / per * iters;
-  return (int)std::max(1ll, std::min(g, (long long)cap * (wide ? 4 : 1)));
+// Grid for the sweep of the full beliefs of depth `dep` after iteration k: a
+// thread each (a wavefront each for long rows).  Half the visits of that depth
+// bound them, and there are far fewer as a rule, so the cap is what most
+// sweeps take and the blocks loop over the rest.
+int backup_grid(const PlanView& P, int dep, int k, int cap, long long kept) {
+  long long visits = 0;
+  for (int kk = 1; kk <= k; ++kk) visits += depth_at(P, kk) >= dep ? P.n_p : 0;
+  const int per = P.m.Apad > kMaxA ? kBlock / 64 : kBlock;
+  const long long g = (visits / 2 + kept + per - 1) / per;
+  return (int)std::max(1ll, std::min(g, (long long)cap));
+}
+
+// Grid of dev_full after iteration k: the items it may find, up to the cap
+// (each block takes as many as it finds).
+int full_grid(const PlanView& P, int k, const std::function<long long(int)>& kept) {
+  long long items = 1;
+  for (int dep = 1; dep <= depth_at(P, k); ++dep)
+    items += backup_grid(P, dep, k, kFullCap, kept ? kept(dep) : 0);
+  return (int)std::min(items, (long long)kFullCap);
+}
+
+// Grid of the walk along the runs of iterations 1 .. k: a thread per episode
+// and iteration (a wavefront per 16 for long rows).
+int fold_grid(const PlanView& P, int k, int cap) {
+  const int per = (P.n_p + kBlock - 1) / kBlock;
+  return 2 * std::max(1, std::min(cap, per * std::max(k, depth_at(P, k) + 1)));
+}
+int chain_grid(const PlanView& P, int k, int cap) {
+  const int per = P.m.Apad > kMaxA ? 64 : kBlock;
+  const long long g = ((long long)P.n_p + per - 1) / per * k;
+  return (int)std::max(1ll, std::min(g, (long long)cap));
 }
 
 // Enqueue one planning step on stream s.  Returns the level-step count.
@@ -562,21 +622,7 @@ static vopp_status timed_gate(const vopp_workspace* w, hipStream_t s, int k, boo
 vopp_status enqueue_plan(const vopp_pomdp* p, vopp_workspace* w, const PlanView& P,
                          hipStream_t s, int* n_steps_out) {
   const int K = P.K;
-  int D[kMaxBudget + 1] = {0};
-  const int c0 = P.carry ? w->carry.n_steps : 0;   // a kept subtree's steps first
-  int steps = c0;
   hipError_t e = hipSuccess;
-  if (!P.clear_all) w->step_host[0] = c0;
-  for (int k = 1; k <= K; ++k) {
-    D[k] = P.schedule == VOPP_SCHEDULE_FIXED ? P.depth : std::min(k, P.depth);
-    steps += D[k];
-    if (!P.clear_all) w->step_host[k] = steps;
-  }
-  // Without a workspace (P.clear_all) the set-up kernel writes the schedule.
-  if (!P.clear_all)
-    e = hipMemcpyAsync(w->step_base_dev, w->step_host, (K + 1) * sizeof(int),
-                       hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) return hip_fail(e, "upload schedule");
   w->prof_used = 0;
   // Each launch below is bracketed by prof_begin/prof_end (no-ops unless
   // profiling is enabled on the workspace); prof_end runs whenever prof_begin
@@ -590,38 +636,41 @@ vopp_status enqueue_plan(const vopp_pomdp* p, vopp_workspace* w, const PlanView&
       if (e == hipSuccess) e = e_end;                       \
     }                                                       \
   } while (0)
-  if (w->hash_dirty && !P.clear_all) {
-    // A plan did not finish: the table state is unknown, clear it fully.
-    e = hipMemcpyAsync(&w->tree.counters[3], &w->step_host[kMaxBudget + 1],
-                       sizeof(unsigned long long), hipMemcpyHostToDevice, s);
-  }
   VOPP_TIMED(VOPP_KERNEL_SETUP, launch_setup(P, s));
   if (e != hipSuccess) return hip_fail(e, "plan set-up launch");
-  w->hash_dirty = true;   // until the plan has finished
-  int t = c0;
+  int t = P.carry_steps;
   for (int k = 1; k <= K; ++k) {
+    const int D = depth_at(P, k);
     if (P.timed && k > 1) {
       bool go = true;
       const vopp_status gs = timed_gate(w, s, k, &go);
       if (gs != VOPP_OK) return gs;
       if (!go) break;
     }
-    VOPP_TIMED(VOPP_KERNEL_FORWARD, launch_forward(P, k, D[k], s));
-    VOPP_TIMED(VOPP_KERNEL_ACCUMULATE,
-               launch_accum(P, D[k], accum_blocks(P, D[k], kAccumCap), s));
+    VOPP_TIMED(VOPP_KERNEL_FORWARD, launch_forward(P, k, s));
+    if (P.m.Apad <= kMaxA)
+      VOPP_TIMED(VOPP_KERNEL_ACCUMULATE, launch_fold(P, k, fold_grid(P, k, kBackupCap), s));
+    else
+      VOPP_TIMED(VOPP_KERNEL_ACCUMULATE,
+                 launch_accum(P, k, accum_blocks(P, D, kAccumCap), s));
     if (e != hipSuccess) return hip_fail(e, "forward-search launch");
-    t += D[k];
-    VOPP_TIMED(VOPP_KERNEL_BACKUP_LEAF,
-               launch_backup_leaf(P, D[k], k,
-                                  backup_grid(p, P.n_p, D, D[k], k, kBackupCap,
-                                              P.carry ? w->carry.count[D[k]] : 0), s));
-    for (int dep = D[k]; dep >= 2; --dep)
-      VOPP_TIMED(VOPP_KERNEL_BACKUP_LEVEL,
-                 launch_backup_level(P, dep, k,
-                                     backup_grid(p, P.n_p, D, dep - 1, k, kBackupCap,
-                                                 P.carry ? w->carry.count[dep - 1] : 0,
-                                                 P.m.Apad > kMaxA), s));
-    VOPP_TIMED(VOPP_KERNEL_BACKUP_ROOT, launch_backup_root(P, k, s));
+    t += D;
+    const std::function<long long(int)> kept = [&](int dep) { return P.carry ? w->carry.beliefs[dep] : 0ll; };
+    if (P.m.Apad <= kMaxA) {
+      VOPP_TIMED(VOPP_KERNEL_BACKUP_LEVEL, launch_full(P, k, full_grid(P, k, kept), s));
+    } else {
+      VOPP_TIMED(VOPP_KERNEL_BACKUP_LEAF,
+                 launch_backup_leaf(P, D, k, backup_grid(P, D, k, kFullCap, kept(D)), s));
+      auto levels = [&]() {
+        hipError_t el = launch_chain(P, k, chain_grid(P, k, kBackupCap), s);
+        for (int dep = D; dep >= 2 && el == hipSuccess; --dep)
+          el = launch_backup_level(P, dep, k,
+                                   backup_grid(P, dep - 1, k, kFullCap, kept(dep - 1)), s);
+        return el;
+      };
+      VOPP_TIMED(VOPP_KERNEL_BACKUP_LEVEL, levels());
+      VOPP_TIMED(VOPP_KERNEL_BACKUP_ROOT, launch_backup_root(P, k, s));
+    }
     if (e != hipSuccess) return hip_fail(e, "backup launch");
   }
   VOPP_TIMED(VOPP_KERNEL_SELECT, launch_select(P, s));
@@ -748,7 +797,6 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
     P.t.dbg_act = draw_act;
     P.t.dbg_obs = draw_obs;
     P.t.dbg_force = force_act;
-    P.t.dbg_step0 = P.carry ? ws->carry.n_steps : 0;
   }
   hipError_t e = hipSuccess;
   if (time_ms > 0.0) {
@@ -780,7 +828,6 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   prof_collect(ws);
   const double* o = ws->out_host;
   ws->n_prev_beliefs = (int)o[A + 3];
-  ws->hash_dirty = false;
   const int flags = (int)o[A + 5];
   if (flags & 1) return fail(VOPP_E_INVALID, "a belief particle holds a state outside [0, nS)");
   if (flags & 2) return fail(VOPP_E_INTERNAL, "belief table overflow");
@@ -803,23 +850,22 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
       if (d > D_last) nb += ws->carry.beliefs[d];
       if (d >= D_last) na += ws->carry.nodes[d];
     }
-  // Level-step depths of this tree.
-  ws->step_depth.clear();
+  // The level steps of this tree.
+  ws->steps.clear();
   if (P.carry)
     for (int d = 1; d <= kMaxDepth; ++d)
-      for (int i = 0; i < ws->carry.count[d]; ++i) ws->step_depth.push_back(d);
-  for (int k = 1; k <= k_run; ++k) {
-    const int D = prm->schedule == VOPP_SCHEDULE_FIXED ? depth : std::min(k, depth);
-    for (int d = 0; d < D; ++d) ws->step_depth.push_back(d + 1);
-  }
-  ws->carried = P.carry != 0;
+      for (int i = 0; i < ws->carry.count[d]; ++i) {
+        const long long left = ws->carry.beliefs[d] - (long long)i * ws->carry.n_p;
+        ws->steps.push_back({d, -1, (int)std::min(left, (long long)ws->carry.n_p)});
+      }
+  for (int k = 1; k <= k_run; ++k)
+    for (int d = 0; d < depth_at(P, k); ++d) ws->steps.push_back({d + 1, k - 1, 0});
   ws->carry.pending = false;
   *action = (int32_t)o[0];
   if (values) for (int j = 0; j < A; ++j) values[j] = o[1 + j];
   if (v_root) *v_root = o[A + 1];
   ws->n_prev_beliefs = (int)nb;
   ws->n_prev_actions = (int)na;
-  ws->hash_dirty = false;
   ws->last_A = A;
   ws->last_apad = p->view.Apad;
   ws->last_steps = steps;
@@ -828,6 +874,8 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   ws->last_depth = depth;
   ws->last_schedule = prm->schedule;
   ws->last_fix_inv64 = P.fix_inv64;
+  ws->last_tree = P.t;
+  ws->last_obs_bits = p->view.obs_bits;
   if (stats) {
     stats->particle_steps = (int64_t)o[A + 2];
     stats->n_beliefs = (int64_t)nb;
@@ -926,10 +974,10 @@ extern "C" vopp_status vopp_plan_noalloc(const vopp_pomdp* p, const void* belief
   w.arena = base;
   w.bytes = need;
   double* unused_out = nullptr;
-  carve_tree(base, z, w.tree, &w.carry_rng_dev, &w.step_base_dev, &unused_out);
+  carve_tree(base, z, w.tree, &w.carry_rng_dev, &unused_out);
   w.out_dev = result;
   PlanView P = make_view(p, &w, belief, n_belief, budget, depth, prm);
-  P.clear_all = 1;
+  P.short_out = 1;
   int steps = 0;
   return enqueue_plan(p, &w, P, (hipStream_t)stream, &steps);
 }
@@ -947,6 +995,15 @@ extern "C" vopp_status vopp_plan_anytime(const vopp_pomdp* p, const void* belief
                      values, v_root, stats, iterations);
 }
 
+// Whether position ep of a level step of the last plan's tree holds a belief.
+static bool in_step(const vopp_workspace::Step& st, const std::vector<unsigned short>& run,
+                    int n_p, int ep) {
+  if (st.iter < 0) return ep < st.n;
+  const uint32_t r = run[(size_t)st.iter * n_p + ep];
+  const int top = (int)(r & kRunMask) - 1, len = (int)((r >> kRunLenShift) & kRunMask);
+  return st.depth - 1 >= top && st.depth - 1 < top + len;
+}
+
 extern "C" vopp_status vopp_tree_dump(vopp_workspace* w, int32_t* b_parent, int32_t* b_obs,
                                       int32_t* b_depth, float* psi, float* b_V, int32_t* b_N,
                                       int32_t* a_parent, int32_t* a_act, double* a_C,
@@ -960,18 +1017,17 @@ extern "C" vopp_status vopp_tree_dump(vopp_workspace* w, int32_t* b_parent, int3
   auto cp = [&](void* dst, const void* src, size_t bytes) {
     if (e == hipSuccess && bytes) e = hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
   };
-  // Beliefs with their depth: the root, then each level step's list (level d
-  // creates depth d + 1).
-  std::vector<int> list((size_t)steps * n_p);
-  cp(list.data(), w->tree.list, list.size() * 4);
+  // Beliefs with their depth: the root, then those of each level step.
+  if ((int)w->steps.size() != steps)
+    return fail(VOPP_E_INTERNAL, "tree dump: layout of %zu level steps for %d", w->steps.size(),
+                steps);
+  std::vector<unsigned short> run((size_t)w->last_K * n_p);
+  cp(run.data(), w->last_tree.run, run.size() * sizeof(unsigned short));
   std::vector<int> ids{0}, depth{0};
-  if ((int)w->step_depth.size() != steps)
-    return fail(VOPP_E_INTERNAL, "tree dump: %zu level-step depths for %d steps",
-                w->step_depth.size(), steps);
   for (int t = 0; t < steps; ++t) {
     for (int j = 0; j < n_p; ++j)
-      if (list[(size_t)t * n_p + j]) ids.push_back(1 + t * n_p + j);
-    depth.resize(ids.size(), w->step_depth[t]);
+      if (in_step(w->steps[t], run, n_p, j)) ids.push_back(1 + t * n_p + j);
+    depth.resize(ids.size(), w->steps[t].depth);
   }
   if (e != hipSuccess) return hip_fail(e, "tree dump");
   const size_t nb = ids.size();
@@ -985,7 +1041,9 @@ extern "C" vopp_status vopp_tree_dump(vopp_workspace* w, int32_t* b_parent, int3
   e = hipMalloc(&ids_dev, nb * 4);
   if (e == hipSuccess) e = hipMalloc(&rec_dev, nb * (size_t)rs);
   if (e == hipSuccess) e = hipMemcpy(ids_dev, ids.data(), nb * 4, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = launch_gather(w->tree, ids_dev, (int)nb, rec_dev, nullptr);
+  if (e == hipSuccess)
+    e = launch_gather(w->last_tree, n_p, w->last_obs_bits, (float)(1.0 / w->last_fix_inv64),
+                      ids_dev, (int)nb, rec_dev, nullptr);
   cp(rec.data(), rec_dev, nb * (size_t)rs);
   if (ids_dev) (void)hipFree(ids_dev);
   if (rec_dev) (void)hipFree(rec_dev);
@@ -1083,15 +1141,16 @@ extern "C" vopp_status vopp_level_counts(const vopp_workspace* w, int32_t* count
   *n_steps = w->last_steps;
   const int n = std::min(cap, w->last_steps);
   if (counts && n > 0) {
-    const size_t n_p = (size_t)w->last_n_p;
-    std::vector<int> list((size_t)n * n_p);
+    const int n_p = w->last_n_p;
+    std::vector<unsigned short> run((size_t)w->last_K * n_p);
     hipError_t e = hipDeviceSynchronize();
     if (e == hipSuccess)
-      e = hipMemcpy(list.data(), w->tree.list, list.size() * 4, hipMemcpyDeviceToHost);
+      e = hipMemcpy(run.data(), w->last_tree.run, run.size() * sizeof(unsigned short),
+                    hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "level counts");
     for (int t = 0; t < n; ++t) {
       int c = 0;
-      for (size_t j = 0; j < n_p; ++j) c += list[t * n_p + j] != 0;
+      for (int j = 0; j < n_p; ++j) c += in_step(w->steps[t], run, n_p, j) ? 1 : 0;
       counts[t] = c;
     }
   }

@@ -2,8 +2,9 @@
 // together.
 //
 // Each instance's plan is a fixed list of phases (set-up; per iteration the
-// forward search, the accumulate sweep, the leaf sweep, one sweep per depth,
-// the root; finally select), each split into tiles (one block's share).
+// forward search, the accumulate sweep, the walk along the runs, the full
+// beliefs and the root; finally select), each split into tiles (one block's
+// share).
 //   - Persistent launch: one kernel whose blocks take tiles
 //     from a device queue; every instance moves through its own phases as
 //     soon as its previous phase's tiles are done, so short and long
@@ -68,20 +69,11 @@ namespace vopp {
 std::vector<Phase> plan_phases(const vopp_pomdp* p, const PlanView& P, int accum_cap,
                                int backup_cap) {
   std::vector<Phase> ph;
-  const int K = P.K;
-  std::vector<int> D(K + 1, 0);
-  for (int k = 1; k <= K; ++k)
-    D[k] = P.schedule == VOPP_SCHEDULE_FIXED ? P.depth : std::min(k, P.depth);
   ph.push_back({kPhaseSetup, 0, 0, setup_blocks(P)});
-  int t = 0;
-  for (int k = 1; k <= K; ++k) {
-    ph.push_back({kPhaseForward, k, D[k], forward_blocks(P)});
-    ph.push_back({kPhaseAccum, D[k], 0, accum_blocks(P, D[k], accum_cap)});
-    t += D[k];
-    ph.push_back({kPhaseLeaf, D[k], k, backup_grid(p, P.n_p, D.data(), D[k], k, backup_cap)});
-    for (int dep = D[k]; dep >= 2; --dep)
-      ph.push_back({kPhaseLevel, dep, k, backup_grid(p, P.n_p, D.data(), dep - 1, k, backup_cap)});
-    ph.push_back({kPhaseRoot, k, 0, 1});
+  for (int k = 1; k <= P.K; ++k) {
+    ph.push_back({kPhaseForward, k, 0, forward_blocks(P)});
+    ph.push_back({kPhaseFold, k, 0, fold_grid(P, k, std::min(accum_cap, backup_cap))});
+    ph.push_back({kPhaseFull, k, 0, std::min(backup_cap, full_grid(P, k, nullptr))});
   }
   ph.push_back({kPhaseSelect, 0, 0, 1});
   return ph;
@@ -164,7 +156,7 @@ vopp_status build_schedule(vopp_batch* b) {
     const vopp_request& r = b->reqs[i];
     for (const Phase& f0 : plan_phases(r.pomdp, b->views[i], big, big)) {
       Phase f = f0;
-      if (f.kind == kPhaseAccum || f.kind == kPhaseLeaf || f.kind == kPhaseLevel) {
+      if (f.kind == kPhaseFold) {
         const int g = std::max(1, b->tuning.sweep_group);
         f.nblk = (f.nblk + g - 1) / g;
       }
@@ -332,19 +324,6 @@ extern "C" vopp_status vopp_batch_create(const vopp_request* reqs, int32_t n,
       vopp_batch_free(b);
       return st;
     }
-    // Upload the instance's iteration schedule once.
-    int* sb = b->ws[i]->step_host;
-    sb[0] = 0;
-    for (int k = 1; k <= reqs[i].budget; ++k)
-      sb[k] = sb[k - 1] + (reqs[i].params.schedule == VOPP_SCHEDULE_FIXED
-                               ? reqs[i].depth
-                               : std::min(k, reqs[i].depth));
-    hipError_t e = hipMemcpy(b->ws[i]->step_base_dev, sb, (reqs[i].budget + 1) * sizeof(int),
-                             hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      vopp_batch_free(b);
-      return hip_fail(e, "batch schedule");
-    }
   }
   hipError_t e = hipDeviceGetAttribute(&b->n_cu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess && b->n_cu < 1) b->n_cu = 1;
@@ -416,12 +395,7 @@ extern "C" vopp_status vopp_batch_run(vopp_batch* b, void* stream, int32_t mode,
     e = hipMemcpyAsync(b->out_host, b->out_dev, (size_t)b->n * kOutStride * sizeof(double),
                        hipMemcpyDeviceToHost, b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-  if (e != hipSuccess) {
-    // The tables of every instance are in an unknown state now.
-    const unsigned long long one = 1ull;
-    for (vopp_workspace* w : b->ws) (void)hipMemcpy(&w->tree.counters[3], &one, 8, hipMemcpyHostToDevice);
-    return hip_fail(e, "batch execution");
-  }
+  if (e != hipSuccess) return hip_fail(e, "batch execution");
   if (device_ms) {
     float ms = 0.0f;
     (void)hipEventElapsedTime(&ms, b->ev0, b->ev1);

@@ -18,53 +18,75 @@ constexpr int kActBits = 12;
 constexpr unsigned long long kActMask = (1ull << kActBits) - 1;
 constexpr int kMaxBudget = 256;             // iterations per plan
 constexpr int kMaxDepth = 64;               // maximum leaf depth of a plan
-// Level steps a sweep of one depth may visit: the plan's own (one per
-// iteration) and up to as many again holding a kept subtree.
-constexpr int kMaxRanges = 2 * kMaxBudget;
 constexpr unsigned long long kEmptyKey = ~0ull;
 
-// Belief keys of the open-addressing table (AppendBeliefs):
-//   bits  0..19  observation key      bits 20..25  action
-//   bits 26..55  parent's slot id     bits 56..63  iteration that inserted it
-// A belief's slot id is its table slot + 1 (the root is 0): every episode that
-// reaches a belief knows it as soon as its probe ends, without waiting for a
-// numbering pass, so one launch can run every level.  The iteration stamp
-// tells whether the belief was inserted by an earlier kernel (then its record
-// exists and may be read) or by this one (then its preference row is psi0).
-// Beliefs of a kept subtree carry the stamp 0xFF, which no iteration of a plan
-// from a kept tree uses (such plans have at most 255 iterations).
-// Records are stored by creation: the belief that episode ep inserts at level
-// step t owns record 1 + t*n_p + ep (an episode inserts at most one belief per
-// level step), so no episode allocates anything; the inserting episode stores
-// the record index in the slot for later kernels.
+// The tree holds two kinds of beliefs.
+//   - Single-visit beliefs.  Deep in the tree almost every belief is reached
+//     by one episode only (more than 99% of the beliefs of depth >= 3 on the
+//     navigation and sparse workloads): it has one action node with N = 1 and
+//     its subtree is the rest of that episode's path.  Such a belief is one
+//     16-byte record (BeliefNode); its preference row is the initial row with
+//     one entry replaced.  The beliefs an episode creates in one iteration
+//     form one run of consecutive levels (TreeView::run), so a backup walks
+//     the run of an episode in registers (dev_chain).
+//   - Full beliefs: two or more episodes reached them.  They own rows of the
+//     field arrays and are listed by depth (TreeView::full).
+// A belief is created as the first kind and becomes the second when another
+// episode reaches it (it is then claimed, see claim()).
+//
+// A belief that episode ep creates at level step t has id 1 + t*n_p + ep (an
+// episode creates at most one belief per level step), so no id is ever
+// allocated at run time.
+//
+// How an episode finds the child of belief b under (action, observation):
+// the belief that b's own creator went on to has id b + n_p, and b's record
+// holds its (action, observation) key, so that one needs no look-up.  Every
+// other child is in the open-addressing table (AppendBeliefs), under the key
+//   bits  0..25  action and observation      bits 26..55  parent's id
+//   bits 56..63  iteration that inserted it
+// Only the first belief of each run is in the table: at most one per episode
+// and iteration.  Beliefs of a kept subtree carry the stamp 0xFF, which no
+// iteration of a plan from a kept tree uses (such plans have at most 255
+// iterations).
 constexpr int kObsBits = 20;                // observation field for |A| <= 64
 constexpr int kKeyLowBits = 26;             // action and observation fields together
 constexpr int kMaxAWide = 1 << 12;          // largest action set (rows in memory)
 constexpr int kStampShift = 56;
 constexpr unsigned long long kStampMask = 0xFFull << kStampShift;
-constexpr unsigned long long kSidMask = (1ull << 30) - 1;
-constexpr long long kMaxBeliefs = 1ll << 28;   // twice as many slots: ids <= 2^29
+constexpr long long kMaxBeliefs = 1ll << 28;   // ids take 28 bits
 constexpr unsigned long long kCarryStamp = 0xFFull << kStampShift;
 constexpr int kMaxCarryBudget = kMaxBudget - 1;
 
 struct HSlot {
   unsigned long long key;
-  int id;                    // record index (valid in later kernels)
+  int id;                    // belief id, or -1: not published yet
   int pad;
 };
 
-// Trace words written by the forward kernel, one per (level, episode), for
+// Trace words written by the forward search, one per (level, episode), for
 // the visits it does not count itself (the two shallowest levels, which many
-// episodes share, and beliefs another episode inserted in this iteration):
+// episodes share, and beliefs that became full in this iteration):
 //   level d < D: (id << kActBits) | action;  leaf (d = D): id;
-//   kTraceRec: id is a record index, else a slot id;  kEmptyKey: nothing.
-constexpr unsigned long long kTraceRec = 1ull << 62;
+//   kTraceClaim: this visit made the belief full;  kEmptyKey: counted already.
+constexpr unsigned long long kTraceClaim = 1ull << 62;
 constexpr int kDirectLevel = 2;             // levels >= this count in place
 
-// Parent link of a record: (record << kActBits) | action, or kLinkSlot |
-// (slot id << kActBits) | action while the parent's record is not known yet;
-// ~0 for the root.
-constexpr unsigned long long kLinkSlot = 1ull << 62;
+// BeliefNode::link: the key (action, observation) of the belief's action node
+// and own child, and flags.
+constexpr uint32_t kLinkKey = (1u << kKeyLowBits) - 1;
+constexpr uint32_t kLinkAct = 1u << 26;     // the creator drew an action here
+constexpr uint32_t kLinkChild = 1u << 27;   // its child is id + n_p
+constexpr uint32_t kLinkHead = 1u << 28;    // first of its run (in the table)
+constexpr uint32_t kLinkClaim = 1u << 29;   // another episode reached it
+constexpr uint32_t kLinkFull = 1u << 30;    // its rows hold it (set after the
+                                            // iteration that claimed it)
+
+// An episode's run of one iteration (TreeView::run): levels 0 .. tl-1 were
+// visits of existing beliefs (trace rows), then len beliefs were created, at
+// levels tl-1 .. tl+len-2.
+constexpr uint32_t kRunLenShift = 7;
+constexpr uint32_t kRunMask = 127u;
+constexpr uint32_t kRunLeaf = 1u << 14;     // the episode ended at an existing leaf
 
 enum : uint32_t { kTagRoot = 1, kTagStep = 2, kTagEnv = 4, kTagPF = 5, kTagResample = 6 };
 enum : int { kTabular = 0, kNav = 1 };
@@ -78,14 +100,31 @@ struct NavParams {
   int n_disks;
 };
 
+// Rows of n sampling thresholds laid out as search trees: level 0 is the row
+// itself for up to kRowTop thresholds; of a longer row, every level above holds
+// the last threshold of each group of 8 of the level below, until one has at
+// most kRowTop.  A row is stored top level first, each level padded to a
+// multiple of 8 (of 4 for a single level) with 2^32 - 1.
+constexpr int kRowTop = 16;
+constexpr int kRowLevels = 8;
+struct RowIndex {
+  int n, stride, levels;
+  int top;                                 // entries of the top level, padded
+  int off[kRowLevels];                     // levels in stored order; off[0] = 0
+};
+
 // Device copy of a model (owned by the pomdp handle).
 struct ModelView {
   int kind;
   int nS, nA, nO, Apad;                    // Apad: row stride, multiple of 4
+  int n_succ;                              // successors of every (s, a), or 0 if
+                                           // the rows differ (rowptr then says)
   const int* rowptr;                       // [nS*nA+1]
   const int* col;                          // [nnz]
-  const uint32_t* thrT;                    // [nnz]
-  const uint32_t* thrZ;                    // [nS*nA*nO]
+  const uint32_t* thrT;                    // rows of T: [nnz], or trees (rT) if
+                                           // n_succ
+  const uint32_t* thrZ;                    // [nS*nA] trees (rZ)
+  RowIndex rT, rZ;
   const float* R;                          // [nS*nA]
   const float* H;                          // [nS] or null
   NavParams nav;
@@ -99,44 +138,45 @@ struct ModelView {
   double gamma64;
 };
 
-// Per-belief fields besides the preference row and the action-node columns:
-// the part every backup visit reads (hot) and the part only the leaf updates,
-// the observation key and the tree dump use.
-struct BeliefHot {
+// What the forward search and the walk along single-visit beliefs read.
+struct BeliefNode {
   float V;                   // L_eta Psi (internal) or mean heuristic (leaf)
-  int Nb;                    // visit count N_b
-  unsigned long long parent; // (parent id << kActBits) | action; ~0 for the root
+  uint32_t link;             // key and flags, see kLink*
+  union {
+    struct {
+      float r;               // single visit: its reward (or leaf heuristic)
+      float psi;             // and the preference of its action
+    } one;
+    unsigned long long leaf_h;   // full leaf: this iteration's heuristic sum
+  } u;
 };
-struct BeliefLeaf {
+// The rest of a full belief; of a run's first belief, `own` only.
+struct BeliefInfo {
   int leaf_cnt;              // this iteration's leaf visits (0 between iterations)
-  int obs;                   // observation key (-1 for the root)
-  unsigned long long leaf_h; // this iteration's heuristic sum (fixed point)
+  int Nb;                    // visit count N_b
+  unsigned long long own;    // (parent id << kKeyLowBits) | key under the parent;
+                             // ~0 for the root
 };
 
 // The tree store in HBM: one array per field, indexed by belief id.  With
-// ra = |A| rounded up to a multiple of 4, belief id owns
-//   psi[id*ra ..] f32, n[id*ra ..] i32, c[id*ra ..] i64, w[id*ra ..] i64,
-//   hot[id], leaf[id]
+// ra = |A| rounded up to a multiple of 4, a full belief owns
+//   psi[id*ra ..] f32, n[id*ra ..] i32, c[id*ra ..] i64, w[id*ra ..] i64
 // where N, C (cumulative reward) and W (sum of V*N_b over the child beliefs)
 // are the action nodes (b, a) of tensor A, stored with their parent belief.
 // C, W and the leaf sums are 64-bit two's-complement fixed point.  Belief 0 is
-// the root (its preference row is kept in double precision in psi_root); the
-// beliefs created by level step t are ids 1 + t*n_p + [0, n_p), where
-// list[t*n_p + ep] says which ids are used.  One depth of the tree is thus a
-// few contiguous runs of ids, and a backup sweep that gives consecutive ids to
-// consecutive lanes reads each field with full cache lines.
+// the root (its preference row is kept in double precision in psi_root).
 struct TreeView {
   float* psi;                    // [cap * ra]
   int* nv;                       // [cap * ra]
   unsigned long long* cv;        // [cap * ra]
   unsigned long long* wv;        // [cap * ra]
-  BeliefHot* hot;                // [cap]
-  BeliefLeaf* leaf;              // [cap]
+  BeliefNode* node;              // [cap]
+  BeliefInfo* info;              // [cap]
   uint32_t* bits;                // [cap * bw] long rows only (see below)
   int ra;
   int bw;                        // bitmap words per belief (0 up to kMaxA actions)
   HSlot* h_slot;                 // [h_mask + 1] open-addressing table
-  uint32_t h_mask;
+  uint32_t h_mask;               // of the present plan (the array may be longer)
   double* psi_root;              // [nA]
   float* psi0;                   // [ra] initial preference row ln pi0 / eta,
                                  // zero past |A|
@@ -149,20 +189,23 @@ struct TreeView {
                                  // action nodes, striped over blocks (every
                                  // episode passes through one of them)
   double* v_root;                // [1]
-  int* list;                     // [steps * n_p]: slot id of the belief that
-                                 // episode ep inserted at level step t, or 0
-  unsigned long long* counters;  // [1] error flags [2] beliefs of the last plan
-                                 // [3] table dirty [5] last plan's level steps
-                                 // [6] last plan's n_p
+  int* list;                     // [steps * n_p] words holding run and full:
+  unsigned short* run;           // [K * n_p] runs by (iteration, episode), 0 until
+                                 // the episode has ended
+  int* full;                     // full beliefs by depth (full_first); a full
+                                 // belief has two visits or more, so half the
+                                 // level steps' episodes bound them
+  unsigned int* full_cnt;        // [kMaxDepth + 1] how many of each depth
+  unsigned long long* counters;  // [1] error flags [2], [3] items taken and
+                                 // done of dev_full [4] insert re-probes
   unsigned long long* stats;     // [kStatRows][kStripes] particle steps, then two
                                  // banks of (action nodes, beliefs), near-tie
                                  // draws and the sweeps' work, striped over
                                  // blocks so that no address takes many atomics
   unsigned long long* gate;      // [4] plans with a time budget: [0] start on
                                  // the wall clock, [1] stop flag, [2] iterations run
-  const int* carry_rng;          // [kMaxDepth + 1][2] level steps of a kept
-                                 // subtree by depth: first step, step count
-  const int* step_base;          // [K+1] first level step of each iteration
+  const int* carry_rng;          // [kMaxDepth + 1][2] a kept subtree by depth:
+                                 // first level step, beliefs (packed from there)
   unsigned long long* tr_key;    // [(depth + 1) * n_p] trace words
   float* tr_val;                 // reward (levels) or heuristic (leaf)
   // Optional per-draw export (null unless a traced plan): for the plan's own
@@ -174,22 +217,21 @@ struct TreeView {
   // Optional forced draws, same indexing: an entry in [0, nA) replaces the
   // kernel's decision at that draw (dbg_act still receives the kernel's own).
   const short* dbg_force;
-  int dbg_step0;                 // level step of the plan's first own step
 };
 
 // Long rows (ra > kMaxA) add a bitmap of ra bits per belief, padded to
-// 16-byte quads: for a belief other than the root, N[a], C[a] and W[a] hold
-// values only where bit a is set (set, and the three cleared, by the first
-// visit of (b, a)); elsewhere they are whatever the memory held.  A new belief
-// then writes Psi, its tails and the bitmap, not three quarters of its bytes.
-// The root's columns are all valid.
+// 16-byte quads: for a full belief other than the root, N[a], C[a] and W[a]
+// hold values only where bit a is set (set, and the three cleared, by the
+// first visit of (b, a)); elsewhere they are whatever the memory held.  A
+// belief that becomes full then writes Psi and the bitmap, not three quarters
+// of its bytes.  The root's columns are all valid.
 __host__ __device__ inline int rec_bitmap_quads(int ra) { return (ra + 127) / 128; }
 __host__ __device__ inline int rec_bitmap_words(int ra) {
   return ra > kMaxA ? 4 * rec_bitmap_quads(ra) : 0;
 }
 // Bytes one belief owns across the field arrays.
 __host__ __device__ inline int rec_bytes(int ra) {
-  return 24 * ra + (int)(sizeof(BeliefHot) + sizeof(BeliefLeaf)) + 4 * rec_bitmap_words(ra);
+  return 24 * ra + (int)(sizeof(BeliefNode) + sizeof(BeliefInfo)) + 4 * rec_bitmap_words(ra);
 }
 __device__ __forceinline__ float* rec_psi(const TreeView& t, int id) {
   return t.psi + (size_t)id * (size_t)t.ra;
@@ -203,8 +245,6 @@ __device__ __forceinline__ unsigned long long* rec_c(const TreeView& t, int id) 
 __device__ __forceinline__ unsigned long long* rec_w(const TreeView& t, int id) {
   return t.wv + (size_t)id * (size_t)t.ra;
 }
-__device__ __forceinline__ BeliefHot* rec_hot(const TreeView& t, int id) { return t.hot + id; }
-__device__ __forceinline__ BeliefLeaf* rec_leaf(const TreeView& t, int id) { return t.leaf + id; }
 __device__ __forceinline__ uint32_t* rec_bits(const TreeView& t, int id) {
   return t.bits + (size_t)id * (size_t)t.bw;
 }
@@ -259,7 +299,7 @@ struct PlanView {
   float fix_inv;           // 2^-S
   double fix_inv64;
   int K, depth, schedule;
-  int steps;               // level steps of the plan (sum of D_k)
+  int carry_steps;         // level steps of a kept subtree, before the plan's own
   double* out;             // max(kOutStride, ra + 12) doubles: the plan's result
   // Time budget (anytime plan): 0 = run all K iterations.  Otherwise the
   // iterations after the first run only while fewer than budget_ticks
@@ -270,12 +310,26 @@ struct PlanView {
   // The plan starts from a kept subtree (tree re-rooting): its beliefs sit in
   // the level steps before the plan's own, listed by depth in t.carry_rng.
   int carry;
-  // Plans without a workspace (the allocation-free entry point): set-up clears
-  // the whole table (the memory holds whatever the last call left) and
-  // writes the schedule t.step_base itself (the host copies nothing).
-  int clear_all;
+  int short_out;           // the result record ends at A + 9
   FilterView f;            // served episodes only
 };
+
+// The schedule: D_k, and the level step of level 0 of iteration k.
+__host__ __device__ inline int depth_at(const PlanView& P, int k) {
+  return P.schedule == 1 || k >= P.depth ? P.depth : k;
+}
+__host__ __device__ inline int first_step(const PlanView& P, int k) {
+  const int j = k - 1;                       // iterations before it
+  const int ramp = P.schedule == 1 ? 0 : (j < P.depth ? j : P.depth);
+  return P.carry_steps + ramp * (ramp + 1) / 2 + (j - ramp) * P.depth;
+}
+// First entry of TreeView::full for depth d: half of n_p times the level
+// steps that create beliefs of lower depths.
+__host__ __device__ inline long long full_first(const PlanView& P, int d) {
+  const long long e = d - 1;
+  const long long s = e * P.K - (P.schedule == 1 ? 0 : e * (e - 1) / 2);
+  return (long long)P.n_p * s / 2;
+}
 
 // Tree statistics are counted by the backups of one iteration (the backup
 // sweeps the whole tree): the last one, K.  Under a time budget the last
@@ -300,12 +354,14 @@ __device__ __forceinline__ bool budget_spent(const PlanView& P) {
 // [A+7 .. A+9] the level sweeps' belief, internal-belief and action-node visits.
 constexpr int kOutStride = kMaxA + 12;
 
-// Phase kinds (same numbering as the ABI's VOPP_KERNEL_* kinds).
+// Phase kinds of a batch.
 enum : int {
-  kPhaseForward = 0, kPhaseAccum = 1, kPhaseLeaf = 2, kPhaseLevel = 3,
-  kPhaseRoot = 4, kPhaseSetup = 5, kPhaseSelect = 6,
+  kPhaseForward = 0, kPhaseSetup = 5, kPhaseSelect = 6,
   // Served episodes: true-environment step and SIR belief update.
-  kPhaseEnv = 7, kPhasePFWeight = 8, kPhasePFScan = 9, kPhasePFResample = 10
+  kPhaseEnv = 7, kPhasePFWeight = 8, kPhasePFScan = 9, kPhasePFResample = 10,
+  // The trace together with the walk along single-visit beliefs; the full
+  // beliefs and the root.
+  kPhaseFold = 11, kPhaseFull = 12
 };
 
 // One phase of one instance inside a batched launch: blocks
@@ -338,8 +394,10 @@ __device__ __forceinline__ U4 philox(uint32_t c0, uint32_t c1, uint32_t c2,
                                      uint32_t c3, uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int i = 0; i < 10; ++i) {
-    const uint32_t lo0 = c0 * 0xD2511F53u, hi0 = __umulhi(c0, 0xD2511F53u);
-    const uint32_t lo1 = c2 * 0xCD9E8D57u, hi1 = __umulhi(c2, 0xCD9E8D57u);
+    // (one 32 x 32 -> 64 multiply-add each, rather than a low and a high product)
+    const uint64_t p0 = (uint64_t)c0 * 0xD2511F53u, p1 = (uint64_t)c2 * 0xCD9E8D57u;
+    const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
+    const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
     c0 = hi1 ^ c1 ^ k0;
     c1 = lo1;
     c2 = hi0 ^ c3 ^ k1;
@@ -389,9 +447,46 @@ __device__ __forceinline__ int count_le(const uint32_t* __restrict__ thr, int n,
   return c;
 }
 
+// How many of 4 * NQ thresholds are <= u: all loads first, then the counts.
+template <int NQ>
+__device__ __forceinline__ int quads_le(const uint32_t* __restrict__ thr, uint32_t u) {
+  const uint4* q = reinterpret_cast<const uint4*>(thr);
+  uint4 v[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) v[i] = q[i];
+  int c = 0;
+#pragma unroll
+  for (int i = 0; i < NQ; ++i)
+    c += (v[i].x <= u) + (v[i].y <= u) + (v[i].z <= u) + (v[i].w <= u);
+  return c;
+}
+
+// The first j with u < thr_j in a row laid out as a search tree; u < 2^31 and
+// the last threshold is 2^31, so there is one.  A lane reads its own row, so a
+// 16-byte load costs the address unit 64 lines whatever it holds: 32
+// thresholds take three loads instead of eight, 120 six instead of 30.
+__device__ __forceinline__ int row_find(const uint32_t* __restrict__ row, const RowIndex& x,
+                                        uint32_t u) {
+  int c;
+  switch (x.top >> 2) {                     // uniform
+    case 1: c = quads_le<1>(row, u); break;
+    case 2: c = quads_le<2>(row, u); break;
+    case 3: c = quads_le<3>(row, u); break;
+    default: c = quads_le<4>(row, u); break;
+  }
+  for (int l = 1; l < x.levels; ++l) c = 8 * c + quads_le<2>(row + x.off[l] + 8 * c, u);
+  return min(c, x.n - 1);
+}
+// The thresholds themselves.
+__device__ __forceinline__ const uint32_t* row_leaves(const uint32_t* row, const RowIndex& x) {
+  return row + x.off[x.levels - 1];
+}
+
 // Tabular transition: successor of (s, a) from a 32-bit random word.
 __device__ __forceinline__ int tabular_next(const ModelView& m, int s, int a, uint32_t word) {
   const int row = s * m.nA + a;
+  if (m.n_succ)
+    return m.col[row * m.n_succ + row_find(m.thrT + (size_t)row * m.rT.stride, m.rT, word >> 1)];
   const int lo = m.rowptr[row];
   const int n = m.rowptr[row + 1] - lo;
   int j = count_le(m.thrT + lo, n, word >> 1);
@@ -405,9 +500,7 @@ __device__ __forceinline__ void tabular_step(const ModelView& m, int s, int a,
                                              float& r) {
   r = m.R[s * m.nA + a];
   sn = tabular_next(m, s, a, x.y);
-  const uint32_t* zr = m.thrZ + ((size_t)sn * m.nA + a) * m.nO;
-  int o = count_le(zr, m.nO, x.z >> 1);
-  obs = o < m.nO ? o : m.nO - 1;
+  obs = row_find(m.thrZ + ((size_t)sn * m.nA + a) * m.rZ.stride, m.rZ, x.z >> 1);
 }
 
 __device__ __forceinline__ int nav_axis(const NavParams& p, float v) {
@@ -438,9 +531,9 @@ __device__ __forceinline__ float nav_obs_sd(const NavParams& p, float nx) {
 }
 
 // Obstacle centres of the navigation model held in registers (uniform across
-// the wavefront) when there are at most kDiskRegs of them; more are read from
-// memory.  Reading them once per kernel keeps the obstacle test free of
-// memory waits.
+// the wavefront) when there are at most kDiskRegs of them; more are read where
+// the caller has them (LDS in the forward search).  Reading them once per
+// kernel keeps the obstacle test free of memory waits.
 constexpr int kDiskRegs = 8;
 struct DiskCache {
   float c[2 * kDiskRegs];
@@ -452,8 +545,8 @@ __device__ __forceinline__ DiskCache load_disks(const ModelView& m) {
   for (int i = 0; i < 2 * kDiskRegs; ++i) d.c[i] = i < 2 * n ? m.disks[i] : 0.0f;
   return d;
 }
-__device__ __forceinline__ bool nav_hit(const ModelView& m, const DiskCache& dc, float nx,
-                                        float ny) {
+__device__ __forceinline__ bool nav_hit(const ModelView& m, const DiskCache& dc,
+                                        const float* disks, float nx, float ny) {
   const NavParams& p = m.nav;
   bool hit = false;
   if (p.n_disks <= kDiskRegs) {
@@ -464,7 +557,7 @@ __device__ __forceinline__ bool nav_hit(const ModelView& m, const DiskCache& dc,
     }
   } else {
     for (int i = 0; i < p.n_disks; ++i) {
-      const float ex = nx - m.disks[2 * i], ey = ny - m.disks[2 * i + 1];
+      const float ex = nx - disks[2 * i], ey = ny - disks[2 * i + 1];
       hit = hit || ((ex * ex + ey * ey) <= p.disk_r2);
     }
   }
@@ -476,15 +569,15 @@ __device__ __forceinline__ bool nav_hit(const ModelView& m, const DiskCache& dc,
 struct NavNoise {
   float mx, my, ox, oy;
 };
-__device__ __forceinline__ NavNoise nav_noise(const ModelView& m, const U4& w) {
-  return NavNoise{m.gauss[w.y >> 20], m.gauss[(w.y >> 8) & 4095u], m.gauss[w.z >> 20],
-                  m.gauss[(w.z >> 8) & 4095u]};
+__device__ __forceinline__ NavNoise nav_noise(const float* __restrict__ gauss, const U4& w) {
+  return NavNoise{gauss[w.y >> 20], gauss[(w.y >> 8) & 4095u], gauss[w.z >> 20],
+                  gauss[(w.z >> 8) & 4095u]};
 }
 
 // Navigation G with its noise already read.  Built without contraction: each
 // operation rounds once.
-__device__ __forceinline__ void nav_step_z(const ModelView& m, const DiskCache& dc, float x,
-                                           float y, int a, const NavNoise& z, float& nx,
+__device__ __forceinline__ void nav_step_z(const ModelView& m, const DiskCache& dc,
+                                           const float* disks, float x, float y, int a, const NavNoise& z, float& nx,
                                            float& ny, int& key, float& r, bool& term) {
   const NavParams& p = m.nav;
   float dx = 0.0f, dy = 0.0f;
@@ -502,7 +595,7 @@ __device__ __forceinline__ void nav_step_z(const ModelView& m, const DiskCache& 
   key = nav_axis(p, ox) * p.key_n + nav_axis(p, oy);
   const float gx = nx - p.goal_x, gy = ny - p.goal_y;
   const bool goal = (gx * gx + gy * gy) <= p.goal_r2;
-  const bool hit = nav_hit(m, dc, nx, ny);
+  const bool hit = nav_hit(m, dc, disks, nx, ny);
   float rr = p.r_step;
   if (goal) rr = rr + p.r_goal;
   if (hit) rr = rr + p.r_hit;
@@ -515,7 +608,7 @@ __device__ __forceinline__ void nav_step(const ModelView& m, float x, float y,
                                          int a, const U4& w, float& nx,
                                          float& ny, int& key, float& r,
                                          bool& term) {
-  nav_step_z(m, load_disks(m), x, y, a, nav_noise(m, w), nx, ny, key, r, term);
+  nav_step_z(m, load_disks(m), m.disks, x, y, a, nav_noise(m.gauss, w), nx, ny, key, r, term);
 }
 
 __device__ __forceinline__ float nav_heuristic(const NavParams& p, float x, float y) {
@@ -593,20 +686,6 @@ __device__ __forceinline__ void root_cdf(const double* __restrict__ row, int A, 
   }
 }
 
-// draw_cdf64 by bisection: the first j with t < P_j in a non-decreasing row.
-__device__ __forceinline__ int draw_cdf64_bisect(const double* __restrict__ cdf, int A,
-                                                 uint32_t x0) {
-  const double u = (double)(x0 >> 8) * (1.0 / 16777216.0);
-  const double t = u * cdf[A - 1];
-  int lo = 0, hi = A - 1;                     // the answer lies in [lo, hi]
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (t < cdf[mid]) hi = mid;
-    else lo = mid + 1;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ int draw_cdf64(const double* __restrict__ cdf, int A, uint32_t x0) {
   const double u = (double)(x0 >> 8) * (1.0 / 16777216.0);
   const double t = u * cdf[A - 1];
@@ -655,6 +734,11 @@ __device__ __forceinline__ unsigned long long to_fix(float v, float scale) {
 }
 __device__ __forceinline__ float from_fix(unsigned long long v, float inv) {
   return (float)(long long)v * inv;
+}
+// from_fix(to_fix(v)): the scale is a power of two, so v * scale is exact and
+// its nearest integer is a float.
+__device__ __forceinline__ float fix_round(float v, float scale, float inv) {
+  return rintf(v * scale) * inv;
 }
 
 }  // namespace vopp

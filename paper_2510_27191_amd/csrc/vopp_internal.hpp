@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <functional>
 #include <vector>
 
 #include "../../include/vopp.h"
@@ -38,16 +39,19 @@ struct vopp_workspace {
   void* arena = nullptr;
   size_t bytes = 0;
   vopp::TreeView tree{};
-  int* step_base_dev = nullptr;
-  int* step_host = nullptr;       // pinned
   double* out_dev = nullptr;
   double* out_host = nullptr;     // pinned
-  // Depth of the beliefs each level step of the last plan's tree holds (the
-  // steps of a kept subtree first, then the plan's own).
-  std::vector<int> step_depth;
+  // The level steps of the last plan's tree (the steps of a kept subtree
+  // first, then the plan's own): the depth of their beliefs and the iteration
+  // (0-based) that created them; iter < 0: a kept subtree's, n beliefs.
+  struct Step {
+    int depth, iter, n;
+  };
+  std::vector<Step> steps;
+  vopp::TreeView last_tree{};     // its view (table size, run and full arrays)
+  int last_obs_bits = 0;
   // A kept subtree written by vopp_reroot: its layout by depth, and whether
-  // the next plan starts from it.  `carried` says the last plan's tree holds
-  // these steps.
+  // the next plan starts from it.
   struct Carry {
     bool pending = false;
     int n_p = 0, n_steps = 0;
@@ -56,15 +60,14 @@ struct vopp_workspace {
     long long root_visits = 0;
     int shift = 0;               // fixed-point shift the kept sums were scaled to
     int budget = 0;              // iterations that shift allows
+    uint32_t h_mask = 0;         // of the table it was inserted into
   } carry;
-  bool carried = false;
-  int* carry_rng_dev = nullptr;   // [kMaxDepth + 1][2] device copy of first, count
+  int* carry_rng_dev = nullptr;   // [kMaxDepth + 1][2] device copy of first, beliefs
   // Anytime plans: pinned coherent host word written by the device at the end
   // of each iteration (iterations run | stop << 32), and its device address.
   unsigned long long* gate_host = nullptr;
   unsigned long long* gate_dev = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
-  bool hash_dirty = true;
   int n_prev_beliefs = 0, n_prev_actions = 0;
   int last_A = 0, last_apad = 0, last_steps = 0, last_n_p = 0, last_K = 0,
       last_depth = 0, last_schedule = 0;
@@ -101,10 +104,14 @@ vopp_status ensure_ws(const vopp_pomdp* p, vopp_workspace** ws, const vopp_param
                       int K, int depth);
 PlanView make_view(const vopp_pomdp* p, vopp_workspace* w, const void* belief,
                    int n_belief, int K, int depth, const vopp_params* prm);
-// Blocks of a backup sweep over the beliefs of depth dep after iteration k;
-// extra: level steps of a kept subtree holding that depth.
-int backup_grid(const vopp_pomdp* p, int n_p, const int* D, int dep, int k,
-                int cap, int extra = 0, bool wide = false);
+// Blocks of a sweep over the full beliefs of depth dep after iteration k
+// (kept: those of a kept subtree), and of the walk along the runs.
+int backup_grid(const PlanView& P, int dep, int k, int cap, long long kept = 0);
+int fold_grid(const PlanView& P, int k, int cap);
+int chain_grid(const PlanView& P, int k, int cap);
+int full_grid(const PlanView& P, int k, const std::function<long long(int)>& kept);
+constexpr int kFullCap = 512;               // block cap of a sweep of full beliefs
+uint32_t table_mask(int n_p, long long runs);
 // Sizes of a plan; extra_steps: level steps of a kept subtree in front.
 WsSizes sizes_for(const vopp_pomdp* p, int n_p, int K, int depth, int schedule,
                   int extra_steps = 0);

@@ -7,22 +7,24 @@
 //               action from the softmax of the belief's preferences (Eq. 6),
 //               call G, count the visit and reward into the action node
 //               (AppendActions), and find or insert the child belief
-//               (belief, action, observation) in the open-addressing table
-//               (AppendBeliefs).  A belief is named by its table slot, so no
-//               episode ever waits for another and one launch covers all D_k
-//               levels; the inserting episode also takes the belief's record.
-//               Visits it cannot count in place go to a trace.
-//   accumulate  folds the trace into the records (LDS-aggregated atomics).
-//   backup      Alg. 3, one phase per depth over every belief of that depth:
-//               leaves take their mean heuristic, internal beliefs update their
-//               preference row with Q = C/N + gamma W and V = L_eta Psi, and
-//               each belief pushes V*N_b into its parent action's W
-//               accumulator.  The root runs in double precision.
+//               (belief, action, observation) (AppendBeliefs).  Once an
+//               episode creates a belief it is alone: the rest of its path is
+//               a run of single-visit records, written without any look-up
+//               (see vopp_device.hpp).
+//   accumulate  folds the trace of visits into the full beliefs (LDS-aggregated
+//               atomics) and lists the beliefs that became full.
+//   backup      Alg. 3 over every belief: the runs first, each walked bottom-up
+//               by one thread (dev_chain), then one phase per depth over the
+//               full beliefs of that depth; leaves take their mean heuristic,
+//               internal beliefs update their preference row with
+//               Q = C/N + gamma W and V = L_eta Psi, and each belief hands V*N_b
+//               to its parent action's W (in a register inside a run, else a
+//               64-bit add).  The root runs in double precision.
 //
 // All cross-episode sums (rewards, heuristics, V*N_b) are 64-bit fixed-point
-// integer atomics, so the results do not depend on thread order; which slot
-// and record a belief gets depends on the order of insertions, the tree and
-// every value in it do not.
+// integer atomics, so the results do not depend on thread order; which episode
+// creates a belief that several reach depends on the order of insertions, the
+// tree and every value in it do not.
 //
 // Every phase is a __device__ function of (plan view, block index within the
 // phase, block count of the phase).  The single-plan path launches one kernel
@@ -32,6 +34,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <climits>
 
 #include "vopp_device.hpp"
 #include "vopp_launch.hpp"
@@ -43,54 +46,71 @@ namespace vopp {
 // the inserting thread writes key | stamp.  Returns the slot, or ~0u if the
 // table has no free slot left (an internal error, reported by the plan).
 //
-// A key hashes to a bucket, one 128-byte line of 8 slots, which the probe
-// reads with one round of loads and scans in registers; a full bucket
-// continues into the next line.  Within a line the key visits the slots in a
-// rotated order that is a function of the key, so every thread that looks
-// for one key meets the same first empty slot (linear probing over a fixed
-// per-key sequence: one compare-and-swap there decides the insert), while
-// different keys spread their inserts over the line.  A wavefront waits for
-// its slowest lane, so reading whole lines and deciding in registers keeps
-// most wavefronts at one read and at most one compare-and-swap per lane (a
-// compare-and-swap is about twice as slow as a read).  Keys and record indices written by earlier kernels are
-// visible to the plain loads; a key being inserted by this kernel may read
-// as empty, and then the compare-and-swap returns it.
+// A key hashes to a bucket of 4 slots (64 bytes), which the probe reads with
+// one round of loads and scans in registers; a full bucket continues into the
+// next.  Within a bucket the key visits the slots in a rotated order that is a
+// function of the key, so every thread that looks for one key meets the same
+// first empty slot (linear probing over a fixed per-key sequence: one
+// compare-and-swap there decides the insert), while different keys spread
+// their inserts over the bucket.  A wavefront waits for its slowest lane, so
+// reading whole buckets and deciding in registers keeps most wavefronts at one
+// read and at most one compare-and-swap per lane (a compare-and-swap is about
+// twice as slow as a read).  Buckets of 8 slots cost twice the loads and scan.
+// Keys and belief ids written by earlier kernels are visible to the plain
+// loads; a key being inserted by this kernel may read as empty, and then the
+// compare-and-swap returns it.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t probe(const TreeView& t, unsigned long long key,
+constexpr uint32_t kBucket = 4;
+
+struct Bucket {
+  uint4 v[kBucket];
+  uint32_t base, rot;
+};
+__device__ __forceinline__ void bucket_load(const TreeView& t, Bucket& b) {
+  const uint4* ln = reinterpret_cast<const uint4*>(&t.h_slot[b.base]);
+#pragma unroll
+  for (int j = 0; j < (int)kBucket; ++j) b.v[j] = ln[j];
+}
+// The first bucket of a key's probe sequence and the key's slot order in it.
+__device__ __forceinline__ void bucket_read(const TreeView& t, unsigned long long key,
+                                            Bucket& b) {
+  const unsigned long long hk = mix64(key);
+  b.base = (uint32_t)hk & t.h_mask & ~(kBucket - 1);
+  b.rot = (uint32_t)(hk >> 40) & (kBucket - 1);
+  bucket_load(t, b);
+}
+// won: inserted by this call.  fresh: the stamp found is `stamp` (for a key
+// found, not inserted: another episode of this launch inserted it, and id is
+// not known yet); id: else the belief's id.  b: the key's first bucket, read.
+__device__ __forceinline__ uint32_t probe(const TreeView& t, Bucket& b, unsigned long long key,
                                           unsigned long long stamp, bool& won,
                                           bool& fresh, int& id) {
-  const unsigned long long hk = mix64(key);
-  uint32_t base = (uint32_t)hk & t.h_mask & ~7u;
-  const uint32_t rot = (uint32_t)(hk >> 40) & 7u;
-  const uint32_t lines = (t.h_mask >> 3) + 1;
+  const uint32_t lines = (t.h_mask + 1) / kBucket;
   for (uint32_t n = 0; n <= 2 * lines; ++n) {
-    const uint4* ln = reinterpret_cast<const uint4*>(&t.h_slot[base]);
-    uint4 v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = ln[j];
     // The first slot in the key's order that holds the key or is empty.
-    uint32_t best = 8;
+    uint32_t best = kBucket;
     int at = -1;
     bool empty = false;
     int rid = -1;
     unsigned long long seen = kEmptyKey;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const unsigned long long cur = ((unsigned long long)v[j].y << 32) | v[j].x;
-      const uint32_t pos = ((uint32_t)j - rot) & 7u;
+    for (int j = 0; j < (int)kBucket; ++j) {
+      const unsigned long long cur = ((unsigned long long)b.v[j].y << 32) | b.v[j].x;
+      const uint32_t pos = ((uint32_t)j - b.rot) & (kBucket - 1);
       if ((cur == kEmptyKey || (cur & ~kStampMask) == key) && pos < best) {
         best = pos;
         at = j;
         empty = cur == kEmptyKey;
         seen = cur;
-        rid = (int)v[j].z;
+        rid = (int)b.v[j].z;
       }
     }
-    if (at < 0) {                               // the bucket is full: next line
-      base = (base + 8u) & t.h_mask;
+    if (at < 0) {                               // the bucket is full: next bucket
+      b.base = (b.base + kBucket) & t.h_mask;
+      bucket_load(t, b);
       continue;
     }
-    const uint32_t slot = base + (uint32_t)at;
+    const uint32_t slot = b.base + (uint32_t)at;
     if (empty) {
       seen = atomicCAS(&t.h_slot[slot].key, kEmptyKey, key | stamp);
       if (seen == kEmptyKey) {
@@ -99,8 +119,18 @@ __device__ __forceinline__ uint32_t probe(const TreeView& t, unsigned long long 
         id = -1;
         return slot;
       }
-      if ((seen & ~kStampMask) != key) continue;  // another key took it: re-read
-      rid = -1;                                 // inserted by this kernel: fresh
+      if ((seen & ~kStampMask) != key) {        // another key took it: the next slot
+        atomicAdd(&t.counters[4], 1ull);
+#pragma unroll
+        for (int j = 0; j < (int)kBucket; ++j) {
+          if (j == at) {
+            b.v[j].x = (uint32_t)seen;
+            b.v[j].y = (uint32_t)(seen >> 32);
+          }
+        }
+        continue;
+      }
+      rid = -1;                                 // inserted by this launch
     }
     won = false;
     fresh = (seen & kStampMask) == stamp;
@@ -113,67 +143,13 @@ __device__ __forceinline__ uint32_t probe(const TreeView& t, unsigned long long 
   return ~0u;
 }
 
-// The first line of a key's probe sequence (its 8 slots, one batch of
-// loads) and the key's slot order in it.
-struct Bucket {
-  uint4 v[8];
-  uint32_t base, rot;
-};
-__device__ __forceinline__ void bucket_read(const TreeView& t, unsigned long long key,
-                                            Bucket& b) {
-  const unsigned long long hk = mix64(key);
-  b.base = (uint32_t)hk & t.h_mask & ~7u;
-  b.rot = (uint32_t)(hk >> 40) & 7u;
-  const uint4* ln = reinterpret_cast<const uint4*>(&t.h_slot[b.base]);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) b.v[j] = ln[j];
+// Table key of the child of belief id under `low`, its action and observation
+// (the observation takes the low ob bits, the action the next 26 - ob).
+__device__ __forceinline__ unsigned long long belief_key(int id, uint32_t low) {
+  return ((unsigned long long)(uint32_t)id << kKeyLowBits) | low;
 }
-
-// probe() split for the forward search, on the first line already read:
-//   1: the key is there (won false; fresh and id as probe() sets them);
-//   2: an empty slot comes first in the key's order; the insert's
-//      compare-and-swap is issued and its old value returned in `seen`,
-//      not waited for (the caller settles it later with settle_insert);
-//   0: the line is full (the caller falls back to probe()).
-__device__ __forceinline__ int probe_line(const TreeView& t, const Bucket& b,
-                                          unsigned long long key, unsigned long long stamp,
-                                          uint32_t& slot, bool& fresh, int& id,
-                                          unsigned long long& seen) {
-  uint32_t best = 8;
-  int at = -1;
-  bool empty = false;
-  unsigned long long cur_at = kEmptyKey;
-  int rid = -1;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const unsigned long long cur = ((unsigned long long)b.v[j].y << 32) | b.v[j].x;
-    const uint32_t pos = ((uint32_t)j - b.rot) & 7u;
-    if ((cur == kEmptyKey || (cur & ~kStampMask) == key) && pos < best) {
-      best = pos;
-      at = j;
-      empty = cur == kEmptyKey;
-      cur_at = cur;
-      rid = (int)b.v[j].z;
-    }
-  }
-  if (at < 0) return 0;
-  slot = b.base + (uint32_t)at;
-  if (empty) {
-    seen = atomicCAS(&t.h_slot[slot].key, kEmptyKey, key | stamp);
-    fresh = true;
-    id = -1;
-    return 2;
-  }
-  fresh = (cur_at & kStampMask) == stamp;
-  id = fresh ? -1 : rid;
-  return 1;
-}
-
-// Key of belief (parent slot id b, action a, observation obs); the
-// observation takes the low ob bits, the action the next 26 - ob.
-__device__ __forceinline__ unsigned long long belief_key(int b, int a, int obs, int ob) {
-  return ((unsigned long long)(uint32_t)b << kKeyLowBits) |
-         ((unsigned long long)(uint32_t)a << ob) | (uint32_t)obs;
+__device__ __forceinline__ uint32_t key_low(int a, int obs, int ob) {
+  return ((uint32_t)a << ob) | (uint32_t)obs;
 }
 
 // ---------------------------------------------------------------------------
@@ -194,18 +170,24 @@ struct AggTable {
   unsigned long long b[kAggSlots];
 };
 
-// Level steps holding the beliefs of one depth: level dep-1 of every
-// iteration that reached that depth created one run of n_p records.
-struct Ranges {
-  int n;
-  int step[kMaxRanges];
-};
-
 struct Smem {
   AggTable agg;
-  Ranges ranges;
   unsigned long long wave[kBlock / 64];
-  float psi0[kMaxA];        // the forward search's copy of the initial row
+  alignas(16) float psi0[kMaxA];   // the initial row
+  unsigned int n[2];
+};
+
+// Obstacle centres the forward search stages in LDS.
+constexpr int kDiskLds = 64;
+
+// What the forward search reads at every level, staged once per block.
+struct SearchSmem {
+  alignas(16) float psi0[kMaxA];   // the initial row
+  alignas(16) float gauss[4096];   // the navigation model's noise table
+  double psi0_cdf[kMaxA];          // running sums of the draws at new beliefs
+  double root_cdf[kMaxA];          // and at the root
+  float disks[2 * kDiskLds];       // obstacle centres, if there are no more than this
+  unsigned long long wave[kBlock / 64];
 };
 
 __device__ __forceinline__ void agg_clear(AggTable& T) {
@@ -231,6 +213,16 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
   return v;
 }
 
+__device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    unsigned long long n = __shfl_up(v, off, 64);
+    if (lane >= off) v += n;
+  }
+  return v;
+}
+
 // Sum over the block; red holds kBlock / 64 words of LDS.  Called by every
 // thread of the block (it contains barriers); thread 0 gets the total.
 __device__ __forceinline__ unsigned long long block_sum(unsigned long long v,
@@ -246,10 +238,9 @@ __device__ __forceinline__ unsigned long long block_sum(unsigned long long v,
 }
 
 // ---------------------------------------------------------------------------
-// Phase: set-up of a plan.  Clears the belief table (a full fill, or only the
-// slots the previous plan used when that is cheaper), the list lengths and
-// the root record.  The previous plan's sizes are read on the device, so the
-// phase is identical on every replay of a captured launch sequence.
+// Phase: set-up of a plan.  Clears the belief table (sized for one belief per
+// episode and iteration, so it is small beside the tree), the counts and the
+// root.
 // ---------------------------------------------------------------------------
 // LDS of the set-up of a plan with more than kMaxA actions (the root's draw
 // table is built by the block).
@@ -265,25 +256,18 @@ __device__ double block_ordered_sum(const double* x, int A, double m, double eta
 
 __device__ void dev_setup(const PlanView& P, int blk, int nblk, SetupSmem* ss) {
   const TreeView& T = P.t;
-  const unsigned long long n_prev = T.counters[2];
   const size_t hcap = (size_t)T.h_mask + 1;
-  const bool full = P.clear_all || T.counters[3] != 0ull ||
-                    n_prev * 10ull >= (unsigned long long)hcap;
   const size_t tid = (size_t)blk * kBlock + threadIdx.x;
   const size_t stride = (size_t)nblk * kBlock;
-  if (P.carry) {
-    // The table and the kept records were written by the re-rooting.
-  } else if (full) {
+  if (!P.carry) {                               // else the re-rooting wrote it
     uint4* hs = reinterpret_cast<uint4*>(T.h_slot);
     const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
     for (size_t i = tid; i < hcap; i += stride) hs[i] = ones;
-  } else {
-    const size_t used = (size_t)T.counters[5] * (size_t)T.counters[6];
-    for (size_t i = tid; i < used; i += stride) {
-      const int sid = T.list[i];
-      if (sid) T.h_slot[sid - 1].key = kEmptyKey;
-    }
   }
+  // No episode of this plan has ended: zero run words, two at a time (the list
+  // of full beliefs starts past an odd one).
+  const size_t run_words = ((size_t)P.K * (size_t)P.n_p + 1) / 2;
+  for (size_t i = tid; i < run_words; i += stride) reinterpret_cast<uint32_t*>(T.run)[i] = 0u;
   // Root action-node sums; with a kept root, stripe 0 of N and C starts from
   // its record (written below by block 0).
   for (size_t i = tid; i < (size_t)3 * T.ra * kStripes; i += stride)
@@ -297,25 +281,12 @@ __device__ void dev_setup(const PlanView& P, int blk, int nblk, SetupSmem* ss) {
         rec_w(T, 0)[i] = 0ull;
       }
       for (int i = threadIdx.x; i < T.bw; i += kBlock) rec_bits(T, 0)[i] = 0u;
-      if (threadIdx.x == 0) {
-        *rec_hot(T, 0) = BeliefHot{0.0f, 0, kEmptyKey};
-        *rec_leaf(T, 0) = BeliefLeaf{0, -1, 0ull};
-      }
+      if (threadIdx.x == 0) T.node[0].V = 0.0f;
     }
+    for (int i = threadIdx.x; i <= kMaxDepth; i += kBlock) T.full_cnt[i] = 0u;
     __syncthreads();
     const int j = threadIdx.x;
     for (int i = j; i < kStatRows * kStripes; i += kBlock) T.stats[i] = 0ull;
-    if (j == 0 && P.clear_all) {
-      // The schedule D_k (no kept subtree on this path): first level step of
-      // each iteration.
-      int* sb = const_cast<int*>(T.step_base);
-      int run = 0;
-      for (int k = 1; k <= P.K; ++k) {
-        sb[k - 1] = run;
-        run += P.schedule == 1 ? P.depth : min(k, P.depth);
-      }
-      sb[P.K] = run;
-    }
     if (j == 0) {
       T.gate[0] = (unsigned long long)wall_clock64();   // start of the plan
       T.gate[1] = 0ull;
@@ -368,9 +339,9 @@ __device__ void dev_setup(const PlanView& P, int blk, int nblk, SetupSmem* ss) {
           T.psi0_cdf64[a] = run;
         }
       }
-      rec_leaf(T, 0)->obs = -1;
-      rec_hot(T, 0)->parent = kEmptyKey;
-      T.v_root[0] = P.carry ? (double)rec_hot(T, 0)->V : 0.0;
+      T.info[0] = BeliefInfo{0, P.carry ? T.info[0].Nb : 0, kEmptyKey};
+      T.node[0].link = kLinkFull;
+      T.v_root[0] = P.carry ? (double)T.node[0].V : 0.0;
       T.counters[1] = 0ull;
       T.counters[4] = 0ull;
     }
@@ -381,483 +352,481 @@ __device__ void dev_setup(const PlanView& P, int blk, int nblk, SetupSmem* ss) {
 // Phase: the forward search of iteration k over D levels (Alg. 2).
 // ---------------------------------------------------------------------------
 
-// A new belief's record: Psi = ln pi0 / eta (the first term of Eq. 4; uniform
-// unless a reference policy is set), N = C = W = 0, its observation key and its
-// parent link.
-// psi0s: the initial row staged in LDS (a copy from global memory would wait
-// for every store issued before it).
-__device__ __forceinline__ void init_record(const PlanView& P, const float* psi0s, int id,
-                                            int obs, unsigned long long link) {
+// An episode's state.
+struct Episode {
+  int s;                      // tabular, or navigation (x, y)
+  float x, y;
+};
+
+// The rows of a belief that becomes full: what its single visit left there
+// (link, r, psi: its record).  own: its parent and key, for a belief inside a
+// run (a run's first belief has them already).  fresh: created in this
+// iteration.  Only the episode that set kLinkClaim calls, and no other reads
+// these rows before the next launch.
+__device__ __forceinline__ void make_full(const PlanView& P, const float* psi0s, int id,
+                                          uint32_t link, float r, float psi,
+                                          unsigned long long own, bool fresh) {
   const TreeView& T = P.t;
   const int ra = T.ra;
-  float4* pq = reinterpret_cast<float4*>(rec_psi(T, id));
-  int4* nq = reinterpret_cast<int4*>(rec_n(T, id));
+  const int a = (link & kLinkAct) ? (int)((link & kLinkKey) >> P.m.obs_bits) : -1;
+  float* prow = rec_psi(T, id);
+  int* nrow = rec_n(T, id);
   ulonglong2* cq = reinterpret_cast<ulonglong2*>(rec_c(T, id));
   ulonglong2* wq = reinterpret_cast<ulonglong2*>(rec_w(T, id));
-  const float4* p0 = reinterpret_cast<const float4*>(psi0s);
   const ulonglong2 z2 = make_ulonglong2(0ull, 0ull);
-  for (int j = 0; j < ra / 4; ++j) {
-    pq[j] = p0[j];
-    nq[j] = make_int4(0, 0, 0, 0);
-    cq[2 * j] = z2;
-    cq[2 * j + 1] = z2;
-    wq[2 * j] = z2;
-    wq[2 * j + 1] = z2;
+  const unsigned long long fx = to_fix(r, P.fix_scale);
+  for (int j = 0; j < ra; j += 4) {
+    float4 q = *reinterpret_cast<const float4*>(psi0s + j);
+    if (a == j) q.x = psi;
+    if (a == j + 1) q.y = psi;
+    if (a == j + 2) q.z = psi;
+    if (a == j + 3) q.w = psi;
+    *reinterpret_cast<float4*>(prow + j) = q;
+    *reinterpret_cast<int4*>(nrow + j) =
+        make_int4(a == j, a == j + 1, a == j + 2, a == j + 3);
+    cq[j / 2] = make_ulonglong2(a == j ? fx : 0ull, a == j + 1 ? fx : 0ull);
+    cq[j / 2 + 1] = make_ulonglong2(a == j + 2 ? fx : 0ull, a == j + 3 ? fx : 0ull);
+    wq[j / 2] = z2;
+    wq[j / 2 + 1] = z2;
   }
-  *rec_hot(T, id) = BeliefHot{0.0f, 0, link};
-  *rec_leaf(T, id) = BeliefLeaf{0, obs, 0ull};
+  // A leaf that this iteration created: its creator's arrival counts.
+  const bool leaf = fresh && a < 0;
+  if (!(link & kLinkHead)) T.info[id] = BeliefInfo{leaf ? 1 : 0, 1, own};
+  else if (leaf) atomicAdd(&T.info[id].leaf_cnt, 1);
+  if (a < 0) T.node[id].u.leaf_h = leaf ? fx : 0ull;
 }
 
-template <int AM>
-__device__ void dev_forward(const PlanView& P, int k, int D, int blk,
-                            unsigned long long* red, float* psi0s) {
+// Whether the caller is the first to reach the single-visit belief id besides
+// its creator (link: its record's flags as read; a full or claimed one: no).
+__device__ __forceinline__ bool claim(const TreeView& T, int id, uint32_t link) {
+  if (id == 0 || (link & (kLinkFull | kLinkClaim))) return false;
+  return !(atomicOr(&T.node[id].link, kLinkClaim) & kLinkClaim);
+}
+
+// Stores and loads that pass the caches of this XCD: what an episode's run
+// leaves for the episodes of the same launch that reach its first belief.
+__device__ __forceinline__ void store_seen(BeliefNode* p, uint32_t v, uint32_t link, uint32_t r,
+                                           uint32_t psi) {
+  unsigned long long* q = reinterpret_cast<unsigned long long*>(p);
+  __hip_atomic_store(q, ((unsigned long long)link << 32) | v, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(q + 1, ((unsigned long long)psi << 32) | r, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_seen(BeliefInfo* p, unsigned long long own) {
+  unsigned long long* q = reinterpret_cast<unsigned long long*>(p);
+  __hip_atomic_store(q, 1ull << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // {0, 1}
+  __hip_atomic_store(q + 1, own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint4 load_seen(const BeliefNode* p) {
+  const unsigned long long* q = reinterpret_cast<const unsigned long long*>(p);
+  const unsigned long long a =
+      __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long b =
+      __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
+}
+// Every store of this wavefront so far has reached the point all XCDs see.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Runs episode ep from e to its end.
+//
+// Two episodes of one launch may reach the same new belief.  The one that
+// inserted its key owns it and never waits: it goes on along its run, and
+// once the belief's record is written it publishes the belief's id in the table
+// slot (one level later, when the record's store has long arrived).  The other
+// looks at the slot once per turn of its loop until the id is there, then goes on
+// from the belief like any visitor.  If it draws the owner's own action and
+// observation it follows the owner's run, after the owner's run word
+// (TreeView::run, zero until the owner has ended) says that the run is
+// complete.  Owners run already and wait for nothing, and a turn of the loop
+// moves every other lane of the wavefront on as well, so every wait ends.
+//
+// Bound by dependent accesses while the episode visits beliefs of the
+// tree (node and row, table line, compare-and-swap: 2 to 3 levels of them),
+// then by the arithmetic of its run (Philox, draw, G; one 16-byte store per
+// level, no atomics).  Before beliefs of a single visit had records of their
+// own, every level probed the table, wrote 128 bytes or more per belief and
+// counted its visit with two atomics: 57 us a launch instead of 36 for 65,536
+// episodes of nav2d to depth 10, 202 instead of 142 for sparse4096.
+constexpr int kPolls = 4;
+template <int AM, bool NAV, bool TRACE>
+__device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e0,
+                       const SearchSmem& L, const DiskCache& dc, unsigned long long& g,
+                       unsigned long long& nt) {
+  const float* psi0s = L.psi0;
   const TreeView& T = P.t;
-  // The initial row in LDS, copied into new records (every thread of the
-  // block calls).
-  for (int i = threadIdx.x; i < T.ra; i += kBlock) psi0s[i] = T.psi0[i];
-  __syncthreads();
-  const int t0 = T.step_base[k - 1];          // level step of level 0
-  const int ep = blk * kBlock + threadIdx.x;
-  const bool ep_ok = ep < P.n_p;
-  const int A = P.m.nA;
-  const bool nav = P.m.kind != kTabular;
+  const int t0 = first_step(P, k);            // level step of level 0
+  const int first_new = 1 + t0 * P.n_p;       // ids created in this iteration
+  const int A = NAV ? 4 : P.m.nA, ob = P.m.obs_bits;
   const size_t n_p = (size_t)P.n_p;
   const unsigned long long stamp = (unsigned long long)(k - 1) << kStampShift;
-  int s = 0;
-  float x = 0.0f, y = 0.0f;
-  int sid = 0;                // current belief's slot id (0: root)
-  int rid = 0;                // its record, -1 if another episode inserted it
-                              // during this iteration
-  bool fresh = false;         // inserted during this iteration (Psi initial)
-  bool alive = false;
-  if (ep_ok) {
-    // Alg. 1: the episode starts at the root with a state drawn from the
-    // belief particles.
-    const U4 w = draw(P, (uint32_t)ep, kTagRoot, 0, (uint32_t)k);
-    const uint32_t idx = __umulhi(w.x, (uint32_t)P.e.n_belief);
-    if (!nav) {
-      s = ((const int*)P.e.belief)[idx];
-      if ((unsigned)s >= (unsigned)P.m.nS) {   // caller's particle out of range
-        atomicOr((unsigned int*)&T.counters[1], 1u);
-        s = 0;
-      }
-    } else {
-      const float* bf = (const float*)P.e.belief;
-      x = bf[idx];
-      y = bf[P.e.n_belief + idx];
-    }
-    alive = true;
-  }
-  // Inputs of the next level, read ahead of the previous level's writes: a
-  // wait for a load also waits for every memory operation issued before it.
-  U4 w = draw(P, (uint32_t)ep, kTagStep, 0u, (uint32_t)k);
-  float row[AM];
-#pragma unroll
-  for (int j = 0; j < AM; ++j) row[j] = 0.0f;
-  NavNoise z{0.0f, 0.0f, 0.0f, 0.0f};
-  if (alive && nav) z = nav_noise(P.m, w);
-  DiskCache dc;
-#pragma unroll
-  for (int i = 0; i < 2 * kDiskRegs; ++i) dc.c[i] = 0.0f;
-  if (nav) dc = load_disks(P.m);
+  int s = e0.s, id = 0, d = 0;
+  float x = e0.x, y = e0.y;
   // The running sums of the initial row in registers for short rows, so that
   // a draw at a belief created in this iteration issues no memory access.
   constexpr int kCdfRegs = AM <= 8 ? AM : 1;
   double cdf0[kCdfRegs];
 #pragma unroll
-  for (int j = 0; j < kCdfRegs; ++j) cdf0[j] = (AM <= 8 && j < A) ? T.psi0_cdf64[j] : 0.0;
-  unsigned long long g = 0;   // generative-model calls of this episode
-  unsigned long long nt = 0;  // its near-tie draws
-  // An insert whose compare-and-swap is still in flight: the episode goes on
-  // as if it had won the slot (a belief created in this iteration, Psi
-  // initial, whichever episode inserted it) and settles it at the next level
-  // or after the last one.  Only if another key took the slot does the next
-  // level's key change; it is then formed again.  The insert's writes (list
-  // entry, slot's record index, the new record) wait for the settlement.
-  bool pend = false;
-  uint32_t pend_slot = 0;
-  unsigned long long pend_key = 0, pend_seen = 0, pend_link = 0;
-  int pend_t = 0, pend_obs = 0;
-  // Settles the pending insert: sets sid and rid of the belief the episode
-  // stands on; returns false if the table is full.
-  auto settle = [&]() -> bool {
-    pend = false;
-    bool won = pend_seen == kEmptyKey;
-    int rid_new = -1;
-    uint32_t slot = pend_slot;
-    if (!won && (pend_seen & ~kStampMask) != pend_key) {
-      // Another key took the slot: find or insert the key again (a belief of
-      // this iteration either way, so the draws made on it stand).
-      atomicAdd(&T.counters[4], 1ull);
-      bool fr;
-      int id;
-      slot = probe(T, pend_key, stamp, won, fr, id);
-      if (slot == ~0u) {
-        atomicOr((unsigned int*)&T.counters[1], 2u);
-        if (ep_ok) T.list[(size_t)pend_t * n_p + ep] = 0;
-        return false;
-      }
-    }
-    if (won) rid_new = 1 + pend_t * P.n_p + ep;   // the inserter's own record
-    sid = (int)slot + 1;
-    rid = rid_new;
-    fresh = true;
-    T.list[(size_t)pend_t * n_p + ep] = won ? sid : 0;
-    if (won) {
-      T.h_slot[slot].id = rid_new;
-      init_record(P, psi0s, rid_new, pend_obs, pend_link);
-    }
-    return true;
-  };
-  for (int d = 0; d < D; ++d) {
-    unsigned long long tk = kEmptyKey;
-    float r = 0.0f;
-    bool direct = false, insert_now = false, won_now = false;
-    int obs = 0, a = 0;
-    uint32_t h = 0;
-    unsigned long long link = kEmptyKey;
-    const bool drew = alive;
-    int own = 0;                // the kernel's own decision (before a forced draw)
-    if (alive) {
-      // Eq. (6): the root's running sums (double precision), those of the
-      // initial row for a belief created in this iteration, else the row.
-      bool tie = false;
-      if (sid == 0) {
-        a = draw_cdf64(T.root_cdf, A, w.x);
-        tie = (k > 1 || P.carry) && near_tie64(T.root_cdf, A, w.x, a);
-      } else if (fresh) {
-        if constexpr (AM <= 8) a = draw_cdf64_regs<AM>(cdf0, A, w.x);
-        else a = draw_cdf64(T.psi0_cdf64, A, w.x);
-      } else {
-        a = draw_row32<AM>(row, A, P.eta, w.x, tie);
-      }
-      nt += tie ? 1u : 0u;
-      own = a;
-      if (T.dbg_force) {
-        const short f = T.dbg_force[(size_t)(t0 + d - T.dbg_step0) * n_p + ep];
-        if (f >= 0 && f < A) a = f;
-      }
-      bool term = false;
-      if (!nav) {
-        int sn;
-        tabular_step(P.m, s, a, w, sn, obs, r);
-        s = sn;
-      } else {
-        float nx, ny;
-        nav_step_z(P.m, dc, x, y, a, z, nx, ny, obs, r, term);
-        x = nx;
-        y = ny;
-      }
-      ++g;
-      // The next level's noise, issued before this level's insert.
-      const U4 wn = draw(P, (uint32_t)ep, kTagStep, (uint32_t)(d + 1), (uint32_t)k);
-      if (nav && !term && d + 1 < D) z = nav_noise(P.m, wn);
-      // AppendBeliefs, first line: read with the previous insert in flight.
-      Bucket bk;
-      unsigned long long key = 0;
-      if (!term) {
-        key = belief_key(sid, a, obs, P.m.obs_bits);
-        bucket_read(T, key, bk);
-      }
-      bool full = false;
-      if (pend) {
-        const uint32_t sid_guess = (uint32_t)sid;
-        if (!settle()) {
-          full = true;                          // the table is full: stop
-        } else if (!term && (uint32_t)sid != sid_guess) {
-          key = belief_key(sid, a, obs, P.m.obs_bits);
-          bucket_read(T, key, bk);
-        }
-      }
-      // AppendActions: visit count and reward sum of (b, a), counted below
-      // when b's record is known, else left to the accumulate pass.
-      direct = !full && d >= kDirectLevel && rid >= 0;
-      if (!direct && !full)
-        tk = rid >= 0 ? (((unsigned long long)(uint32_t)rid << kActBits) | (uint32_t)a | kTraceRec)
-                      : (((unsigned long long)(uint32_t)sid << kActBits) | (uint32_t)a);
-      link = rid >= 0 ? (((unsigned long long)(uint32_t)rid << kActBits) | (uint32_t)a)
-                      : (kLinkSlot | ((unsigned long long)(uint32_t)sid << kActBits) | (uint32_t)a);
-      const int rid_b = rid;
-      if (term || full) {
-        alive = false;                          // FilterTerminals
-      } else {
-        // AppendBeliefs: find or insert (b, a, o).
-        bool fr = false;
-        int id = -1;
-        unsigned long long seen = 0;
-        const int got = probe_line(T, bk, key, stamp, h, fr, id, seen);
-        if (got == 2) {
-          pend = true;
-          pend_slot = h;
-          pend_key = key;
-          pend_seen = seen;
-          pend_link = link;
-          pend_t = t0 + d;
-          pend_obs = obs;
-          sid = (int)h + 1;
-          fresh = true;
-          rid = -1;
-        } else {
-          bool won = false;
-          if (got == 0) h = probe(T, key, stamp, won, fr, id);   // the line is full
-          if (h == ~0u) {                       // table full: stop and report
-            atomicOr((unsigned int*)&T.counters[1], 2u);
-            alive = false;
-          } else {
-            sid = (int)h + 1;
-            fresh = fr;
-            rid = won ? 1 + (t0 + d) * P.n_p + ep : id;   // the inserter's own record
-            won_now = won;
-          }
-        }
-        insert_now = pend;
-      }
-      // The next level's row (an existing belief's; a new one's is Psi0).
-      w = wn;
-      if (alive && d + 1 < D && !fresh) load_row<AM>(rec_psi(T, rid), A, row);
-      // Writes of level d.
-      if (direct) {
-        atomicAdd(&rec_n(T, rid_b)[a], 1);
-        const unsigned long long fx = to_fix(r, P.fix_scale);
-        if (fx) atomicAdd(&rec_c(T, rid_b)[a], fx);
-      }
-    }
-    if (ep_ok) {
-      const int t = t0 + d;
-      T.tr_key[(size_t)d * n_p + ep] = tk;
-      T.tr_val[(size_t)d * n_p + ep] = r;
-      if (!insert_now) T.list[(size_t)t * n_p + ep] = won_now ? sid : 0;
-      if (won_now) {
-        T.h_slot[h].id = rid;
-        init_record(P, psi0s, rid, obs, link);
-      }
-      if (T.dbg_act) {
-        const size_t i = (size_t)(t - T.dbg_step0) * n_p + ep;
-        T.dbg_act[i] = drew ? (short)own : (short)-1;
-        T.dbg_obs[i] = drew ? obs : -1;
-      }
-    }
-  }
-  if (pend && !settle()) alive = false;
-  if (ep_ok) {
-    unsigned long long tk = kEmptyKey;
-    float hv = 0.0f;                            // ValueHeuristic of the leaf state
-    if (alive) {
-      if (!nav) {
-        if (P.m.H) hv = P.m.H[s];
-      } else {
-        hv = nav_heuristic(P.m.nav, x, y);
-      }
-      if (D >= kDirectLevel && rid >= 0) {
-        BeliefLeaf* lf = rec_leaf(T, rid);
-        atomicAdd(&lf->leaf_cnt, 1);
-        const unsigned long long fx = to_fix(hv, P.fix_scale);
-        if (fx) atomicAdd(&lf->leaf_h, fx);
-      } else {
-        tk = rid >= 0 ? ((unsigned long long)(uint32_t)rid | kTraceRec)
-                      : (unsigned long long)(uint32_t)sid;
-      }
-    }
-    T.tr_key[(size_t)D * n_p + ep] = tk;
-    T.tr_val[(size_t)D * n_p + ep] = hv;
-  }
-  // Both counts in one word: a block makes fewer than 2^32 of each.
-  g = block_sum(g | (nt << 32), red);
-  if (threadIdx.x == 0 && (g & 0xffffffffull))
-    atomicAdd(&T.stats[blk % kStripes], g & 0xffffffffull);
-  if (threadIdx.x == 0 && (g >> 32)) atomicAdd(&T.stats[kStatNear * kStripes + blk % kStripes], g >> 32);
-}
-
-// The forward search of the batched kernels: the same decisions, draws and
-// writes as dev_forward, with each insert settled before the next level.  A
-// batched kernel holds the registers of its largest phase, and carrying an
-// unsettled insert across levels (dev_forward) would cost it half its
-// wavefronts per SIMD.
-template <int AM>
-__device__ void dev_forward_inorder(const PlanView& P, int k, int D, int blk,
-                                    unsigned long long* red, float* psi0s) {
-  const TreeView& T = P.t;
-  // The initial row in LDS, copied into new records (every thread of the
-  // block calls).
-  for (int i = threadIdx.x; i < T.ra; i += kBlock) psi0s[i] = T.psi0[i];
-  __syncthreads();
-  const int t0 = T.step_base[k - 1];          // level step of level 0
-  const int ep = blk * kBlock + threadIdx.x;
-  const bool ep_ok = ep < P.n_p;
-  const int A = P.m.nA;
-  const bool nav = P.m.kind != kTabular;
-  const size_t n_p = (size_t)P.n_p;
-  const unsigned long long stamp = (unsigned long long)(k - 1) << kStampShift;
-  int s = 0;
-  float x = 0.0f, y = 0.0f;
-  int sid = 0;                // current belief's slot id (0: root)
-  int rid = 0;                // its record, -1 if another episode inserted it
-                              // during this iteration
-  bool fresh = false;         // inserted during this iteration (Psi initial)
-  bool alive = false;
-  if (ep_ok) {
-    // Alg. 1: the episode starts at the root with a state drawn from the
-    // belief particles.
-    const U4 w = draw(P, (uint32_t)ep, kTagRoot, 0, (uint32_t)k);
-    const uint32_t idx = __umulhi(w.x, (uint32_t)P.e.n_belief);
-    if (!nav) {
-      s = ((const int*)P.e.belief)[idx];
-      if ((unsigned)s >= (unsigned)P.m.nS) {   // caller's particle out of range
-        atomicOr((unsigned int*)&T.counters[1], 1u);
-        s = 0;
-      }
-    } else {
-      const float* bf = (const float*)P.e.belief;
-      x = bf[idx];
-      y = bf[P.e.n_belief + idx];
-    }
-    alive = true;
-  }
+  for (int j = 0; j < kCdfRegs; ++j) cdf0[j] = (AM <= 8 && j < A) ? L.psi0_cdf[j] : 0.0;
   // Inputs of the next level, read ahead of the previous level's writes: a
   // wait for a load also waits for every memory operation issued before it.
   U4 w = draw(P, (uint32_t)ep, kTagStep, 0u, (uint32_t)k);
+  NavNoise z{0.0f, 0.0f, 0.0f, 0.0f};
+  if (NAV) z = nav_noise(L.gauss, w);
   float row[AM];
+  uint32_t link = 0;          // the record of the belief it visits (root: 0)
+  float nr = 0.0f, npsi = 0.0f;
+  unsigned long long own = 0; // its parent and key, if it was reached by a run
+  // Reads the record of belief id, and its row if it has one of its own (a
+  // single-visit belief's row is the initial one but for one entry).
+  auto arrive = [&](bool want_row) {
+    const bool is_new = id >= first_new;
+    want_row = want_row && !is_new;
+    uint4 q;
+    if (is_new) q = load_seen(&T.node[id]);
+    else q = *reinterpret_cast<const uint4*>(&T.node[id]);
+    if (want_row) load_row<AM>(rec_psi(T, id), A, row);
+    link = q.y;
+    nr = __uint_as_float(q.z);
+    npsi = __uint_as_float(q.w);
+    if (want_row && !(link & kLinkFull)) {
+      const int a1 = (link & kLinkAct) ? (int)((link & kLinkKey) >> ob) : -1;
+#pragma unroll
+      for (int j = 0; j < AM; ++j)
+        if (j < A) row[j] = j == a1 ? npsi : psi0s[j];
+    }
+  };
 #pragma unroll
   for (int j = 0; j < AM; ++j) row[j] = 0.0f;
-  NavNoise z{0.0f, 0.0f, 0.0f, 0.0f};
-  if (alive && nav) z = nav_noise(P.m, w);
-  DiskCache dc;
-#pragma unroll
-  for (int i = 0; i < 2 * kDiskRegs; ++i) dc.c[i] = 0.0f;
-  if (nav) dc = load_disks(P.m);
-  unsigned long long g = 0;   // generative-model calls of this episode
-  unsigned long long nt = 0;  // its near-tie draws
-  for (int d = 0; d < D; ++d) {
-    unsigned long long tk = kEmptyKey;
-    float r = 0.0f;
-    bool won = false, direct = false;
-    int obs = 0, a = 0;
-    uint32_t h = 0;
-    unsigned long long link = kEmptyKey;
-    const int rid_b = rid;
-    const bool drew = alive;
-    int own = 0;                // the kernel's own decision (before a forced draw)
-    if (alive) {
-      // Eq. (6): the root's running sums (double precision), those of the
-      // initial row for a belief created in this iteration, else the row.
-      bool tie = false;
-      if (sid == 0) {
-        a = draw_cdf64(T.root_cdf, A, w.x);
-        tie = (k > 1 || P.carry) && near_tie64(T.root_cdf, A, w.x, a);
-      } else if (fresh) {
-        a = draw_cdf64(T.psi0_cdf64, A, w.x);
-      } else {
-        a = draw_row32<AM>(row, A, P.eta, w.x, tie);
-      }
-      nt += tie ? 1u : 0u;
-      own = a;
+  bool tail = false;          // it stands on a belief of its own
+  uint32_t head = 0;          // kLinkHead at the first of its run
+  int tl = 0;                 // levels that visited existing beliefs
+  uint32_t slot = 0;          // of its first belief, or of the one it waits for
+  int id_head = 0;
+  int to_publish = 0;         // 1: the first belief's record is to be written, 2: is
+                              // written, the slot's id is not
+  int waits = 0;              // 1: for the id in the slot, 2: for the end of the
+                              // run whose belief id it stands on
+  bool alive = true;
+  // The draw at a belief created in this iteration.
+  auto draw_new = [&](uint32_t x0) {
+    if constexpr (AM <= 8) return draw_cdf64_regs<AM>(cdf0, A, x0);
+    else return draw_cdf64(L.psi0_cdf, A, x0);
+  };
+  // G under the drawn action a (or the forced one, then a is that).
+  auto step = [&](int& a, float& r, int& obs, bool& term) {
+    if (TRACE) {
+      const size_t di = (size_t)(t0 + d - P.carry_steps) * n_p + ep;
+      T.dbg_act[di] = (short)a;               // the kernel's own decision
       if (T.dbg_force) {
-        const short f = T.dbg_force[(size_t)(t0 + d - T.dbg_step0) * n_p + ep];
+        const short f = T.dbg_force[di];
         if (f >= 0 && f < A) a = f;
       }
-      bool term = false;
-      if (!nav) {
-        int sn;
-        tabular_step(P.m, s, a, w, sn, obs, r);
-        s = sn;
-      } else {
-        float nx, ny;
-        nav_step_z(P.m, dc, x, y, a, z, nx, ny, obs, r, term);
-        x = nx;
-        y = ny;
-      }
-      ++g;
-      // AppendActions: visit count and reward sum of (b, a), counted below
-      // when b's record is known, else left to the accumulate pass.
-      direct = d >= kDirectLevel && rid >= 0;
-      if (!direct)
-        tk = rid >= 0 ? (((unsigned long long)(uint32_t)rid << kActBits) | (uint32_t)a | kTraceRec)
-                      : (((unsigned long long)(uint32_t)sid << kActBits) | (uint32_t)a);
-      link = rid >= 0 ? (((unsigned long long)(uint32_t)rid << kActBits) | (uint32_t)a)
-                      : (kLinkSlot | ((unsigned long long)(uint32_t)sid << kActBits) | (uint32_t)a);
-      if (term) {
-        alive = false;                          // FilterTerminals
-      } else {
-        // AppendBeliefs: find or insert (b, a, o).
-        const unsigned long long key = belief_key(sid, a, obs, P.m.obs_bits);
-        bool fr;
-        int id;
-        h = probe(T, key, stamp, won, fr, id);
-        if (h == ~0u) {                         // table full: stop and report
-          atomicOr((unsigned int*)&T.counters[1], 2u);
-          alive = false;
-        } else {
-          sid = (int)h + 1;
-          fresh = fr;
-          rid = won ? 1 + (t0 + d) * P.n_p + ep : id;   // the inserter's own record
-        }
-      }
     }
-    if (alive && d + 1 < D) {
-      w = draw(P, (uint32_t)ep, kTagStep, (uint32_t)(d + 1), (uint32_t)k);
-      if (!fresh) load_row<AM>(rec_psi(T, rid), A, row);
-      if (nav) z = nav_noise(P.m, w);
+    if constexpr (!NAV) {
+      int sn;
+      tabular_step(P.m, s, a, w, sn, obs, r);
+      s = sn;
+    } else {
+      float nx, ny;
+      nav_step_z(P.m, dc, P.m.nav.n_disks <= kDiskLds ? L.disks : P.m.disks, x, y, a, z, nx, ny,
+                 obs, r, term);
+      x = nx;
+      y = ny;
     }
-    // Writes of level d.
-    if (direct) {
-      atomicAdd(&rec_n(T, rid_b)[a], 1);
-      const unsigned long long fx = to_fix(r, P.fix_scale);
-      if (fx) atomicAdd(&rec_c(T, rid_b)[a], fx);
-    }
-    if (ep_ok) {
-      const int t = t0 + d;
-      T.tr_key[(size_t)d * n_p + ep] = tk;
-      T.tr_val[(size_t)d * n_p + ep] = r;
-      T.list[(size_t)t * n_p + ep] = won ? sid : 0;
-      if (won) {
-        T.h_slot[h].id = rid;
-        init_record(P, psi0s, rid, obs, link);
-      }
-      if (T.dbg_act) {
-        const size_t i = (size_t)(t - T.dbg_step0) * n_p + ep;
-        T.dbg_act[i] = drew ? (short)own : (short)-1;
-        T.dbg_obs[i] = drew ? obs : -1;
-      }
-    }
-  }
-  if (ep_ok) {
-    unsigned long long tk = kEmptyKey;
-    float hv = 0.0f;                            // ValueHeuristic of the leaf state
+    ++g;
+    if (TRACE) T.dbg_obs[(size_t)(t0 + d - P.carry_steps) * n_p + ep] = obs;
+  };
+  // The next level's random block and noise.
+  auto next_block = [&]() {
+    w = draw(P, (uint32_t)ep, kTagStep, (uint32_t)(d + 1), (uint32_t)k);
+    if (NAV) z = nav_noise(L.gauss, w);
+  };
+  // A level on its own run: the whole action node and the link to the next
+  // belief.
+  auto run_level = [&](int a) {
+    float r;
+    int obs;
+    bool term = false;
+    step(a, r, obs, term);
+    const uint32_t ln = key_low(a, obs, ob) | kLinkAct | (term ? 0u : kLinkChild) | head;
+    store_seen(&T.node[id], 0u, ln, __float_as_uint(r), __float_as_uint(psi0s[a]));
+    next_block();
+    alive = !term;
     if (alive) {
-      if (!nav) {
+      id += P.n_p;
+      head = 0;
+      ++d;
+    }
+  };
+  // One level at a belief of the tree.
+  auto level = [&]() {
+    // Eq. (6): the root's running sums (double precision), those of the
+    // initial row for a belief created in this iteration, else the row.
+    int a;
+    bool tie = false;
+    if (id == 0) {
+      a = draw_cdf64(L.root_cdf, A, w.x);
+      tie = (k > 1 || P.carry) && near_tie64(L.root_cdf, A, w.x, a);
+    } else if (id >= first_new) {
+      a = draw_new(w.x);
+    } else {
+      a = draw_row32<AM>(row, A, P.eta, w.x, tie);
+    }
+    nt += tie ? 1u : 0u;
+    float r;
+    int obs;
+    bool term = false;
+    step(a, r, obs, term);
+    const uint32_t low = key_low(a, obs, ob);
+    // A belief of the tree.
+    const int b = id;
+    const uint32_t blink = link;
+    const bool by_run = (blink & kLinkChild) && (blink & kLinkKey) == low;
+    const bool look = !term && !by_run;
+    const unsigned long long bk = belief_key(b, low);
+    Bucket line;
+    if (look) bucket_read(T, bk, line);
+    const bool first = claim(T, b, blink);
+    next_block();
+    const float b_r = nr, b_psi = npsi;
+    const unsigned long long b_own = own;
+    bool won = false;
+    uint32_t h = 0;
+    if (term) {
+      alive = false;                          // FilterTerminals
+      tl = d + 1;
+    } else if (by_run) {                      // where its creator went
+      id = b + P.n_p;
+      own = bk;
+      if (b >= first_new) waits = 2;
+    } else {
+      // AppendBeliefs: find or insert (b, a, o).
+      bool fresh = false;
+      int old = -1;
+      h = probe(T, line, bk, stamp, won, fresh, old);
+      if (h == ~0u) {                         // table full: stop and report
+        atomicOr((unsigned int*)&T.counters[1], 2u);
+        alive = false;
+        tl = d + 1;
+      } else if (won) {
+        tail = true;
+        head = kLinkHead;
+        tl = d + 1;
+        id = 1 + (t0 + d) * P.n_p + ep;
+        id_head = id;
+        slot = h;
+        to_publish = 1;
+      } else if (fresh) {
+        slot = h;
+        waits = 1;
+      } else {
+        id = old;
+      }
+    }
+    if (alive && !tail && !waits) arrive(d + 1 < D);
+    // Writes of level d: the visit and reward of (b, a) (AppendActions) go
+    // to the row if it may be written in this launch, else to the trace.
+    unsigned long long tk = kEmptyKey;
+    if (d >= kDirectLevel && (blink & kLinkFull)) {
+      atomicAdd(&rec_n(T, b)[a], 1);
+      const unsigned long long fx = to_fix(r, P.fix_scale);
+      if (fx) atomicAdd(&rec_c(T, b)[a], fx);
+    } else {
+      tk = ((unsigned long long)(uint32_t)b << kActBits) | (uint32_t)a |
+           (first ? kTraceClaim : 0ull);
+    }
+    T.tr_key[(size_t)d * n_p + ep] = tk;
+    T.tr_val[(size_t)d * n_p + ep] = r;
+    if (first) make_full(P, psi0s, b, blink, b_r, b_psi, b_own, b >= first_new);
+    if (won) store_seen(&T.info[id], bk);
+    if (alive) ++d;
+  };
+  // The end of the episode: its leaf, its run word.
+  auto finish = [&]() {
+    if (TRACE && !alive) {
+      for (int q = d + 1; q < D; ++q) {
+        const size_t di = (size_t)(t0 + q - P.carry_steps) * n_p + ep;
+        T.dbg_act[di] = (short)-1;
+        T.dbg_obs[di] = -1;
+      }
+    }
+    uint32_t run;
+    if (!alive) {                               // d: the level it ended at
+      run = (uint32_t)tl | (tail ? (uint32_t)(d - tl + 1) << kRunLenShift : 0u);
+    } else {
+      float hv = 0.0f;                          // ValueHeuristic of the leaf state
+      if constexpr (!NAV) {
         if (P.m.H) hv = P.m.H[s];
       } else {
         hv = nav_heuristic(P.m.nav, x, y);
       }
-      if (D >= kDirectLevel && rid >= 0) {
-        BeliefLeaf* lf = rec_leaf(T, rid);
-        atomicAdd(&lf->leaf_cnt, 1);
-        const unsigned long long fx = to_fix(hv, P.fix_scale);
-        if (fx) atomicAdd(&lf->leaf_h, fx);
+      const unsigned long long fx = to_fix(hv, P.fix_scale);
+      if (tail) {
+        store_seen(&T.node[id], __float_as_uint(from_fix(fx, P.fix_inv)), head,
+                   __float_as_uint(hv), 0u);
+        run = (uint32_t)tl | (uint32_t)(D - tl + 1) << kRunLenShift;
       } else {
-        tk = rid >= 0 ? ((unsigned long long)(uint32_t)rid | kTraceRec)
-                      : (unsigned long long)(uint32_t)sid;
+        run = (uint32_t)D;
+        const bool first = claim(T, id, link);
+        if (D >= kDirectLevel && (link & kLinkFull)) {
+          atomicAdd(&T.info[id].leaf_cnt, 1);
+          if (fx) atomicAdd(&T.node[id].u.leaf_h, fx);
+        } else {
+          run |= kRunLeaf;
+          T.tr_key[(size_t)D * n_p + ep] =
+              (unsigned long long)(uint32_t)id | (first ? kTraceClaim : 0ull);
+          T.tr_val[(size_t)D * n_p + ep] = hv;
+        }
+        if (first) make_full(P, psi0s, id, link, nr, npsi, own, id >= first_new);
       }
     }
-    T.tr_key[(size_t)D * n_p + ep] = tk;
-    T.tr_val[(size_t)D * n_p + ep] = hv;
-  }
-  // Both counts in one word: a block makes fewer than 2^32 of each.
+    stores_done();
+    if (to_publish)
+      __hip_atomic_store(&T.h_slot[slot].id, id_head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    to_publish = 0;
+    __hip_atomic_store(&T.run[(size_t)(k - 1) * n_p + ep], (unsigned short)run, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  };
+  // The loop ends for the whole wavefront at once, so that a lane that has ended
+  // has published its run before any lane of the wavefront waits again.
+  bool done = false;
+  do {
+    if (to_publish == 2) {
+      stores_done();
+      __hip_atomic_store(&T.h_slot[slot].id, id_head, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      to_publish = 0;
+    }
+    // Once every lane left is on its own run, a loop of just that (about 1,300
+    // cycles a level against 4,700 through the branches above).
+    if (__all(done || (tail && !to_publish))) {
+      if (!done) {
+        while (alive && d < D) {
+          const int a = draw_new(w.x);
+          run_level(a);
+        }
+      }
+    }
+    if (!done) {
+      // A turn costs the wavefront its slowest lane (4 us with a visited
+      // belief in it), so a lane that waits looks up to kPolls times (0.3 us
+      // each) before it lets the turn go by, and goes on in the same turn.  With
+      // one look, and the own runs' levels in level()'s branches, a launch
+      // took 31 us instead of 22 (1,024 episodes of nav2d) and 44 instead of
+      // 36 (65,536).
+      for (int tries = 0; tries < kPolls && __any(waits); ++tries) {
+        if (waits == 1) {
+          const int got = __hip_atomic_load(&T.h_slot[slot].id, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+          if (got >= 0) {
+            id = got;
+            waits = -1;
+          }
+        } else if (waits == 2) {
+          const int owner = (id - 1) % P.n_p;
+          if (__hip_atomic_load(&T.run[(size_t)(k - 1) * n_p + owner], __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT))
+            waits = -1;
+        }
+        if (__all(waits <= 0)) break;
+      }
+      if (waits < 0) {
+        waits = 0;
+        arrive(d < D);
+      }
+      if (!waits) {
+        if (!tail && alive && d < D) level();
+        if (tail && alive && d < D) {
+          run_level(draw_new(w.x));
+          if (to_publish) to_publish = 2;
+        } else if (!waits && !(alive && d < D)) {
+          finish();
+          done = true;
+        }
+      }
+    }
+  } while (__ballot(!done));
+}
+
+// The block's particle steps and near ties (both in one word: a block makes
+// fewer than 2^32 of each).
+__device__ __forceinline__ void tally(const TreeView& T, int blk, unsigned long long g,
+                                      unsigned long long nt, unsigned long long* red) {
   g = block_sum(g | (nt << 32), red);
   if (threadIdx.x == 0 && (g & 0xffffffffull))
     atomicAdd(&T.stats[blk % kStripes], g & 0xffffffffull);
-  if (threadIdx.x == 0 && (g >> 32)) atomicAdd(&T.stats[kStatNear * kStripes + blk % kStripes], g >> 32);
+  if (threadIdx.x == 0 && (g >> 32))
+    atomicAdd(&T.stats[kStatNear * kStripes + blk % kStripes], g >> 32);
+}
+
+// The initial row in LDS (every thread of the block calls).
+__device__ __forceinline__ void stage_psi0(const TreeView& T, float* psi0s) {
+  for (int i = threadIdx.x; i < T.ra; i += kBlock) psi0s[i] = T.psi0[i];
+  __syncthreads();
+}
+// The search's tables: a level of a run then reads no global memory in the
+// navigation model, and the root's draw (a serial scan of the running sums)
+// none in any.
+template <bool NAV>
+__device__ __forceinline__ void stage_search(const PlanView& P, SearchSmem& L) {
+  const int j = threadIdx.x;
+  if constexpr (NAV) {
+    const float4* src = reinterpret_cast<const float4*>(P.m.gauss);
+    float4* dst = reinterpret_cast<float4*>(L.gauss);
+#pragma unroll
+    for (int i = 0; i < 1024 / kBlock; ++i) dst[i * kBlock + j] = src[i * kBlock + j];
+    if (j < 2 * min(P.m.nav.n_disks, kDiskLds)) L.disks[j] = P.m.disks[j];
+  }
+  if (j < P.m.nA) {
+    L.psi0_cdf[j] = P.t.psi0_cdf64[j];
+    L.root_cdf[j] = P.t.root_cdf[j];
+  }
+  stage_psi0(P.t, L.psi0);
+}
+
+// Alg. 1: the episode starts at the root with a state drawn from the belief
+// particles.
+__device__ __forceinline__ Episode at_root(const PlanView& P, int k, int ep, bool report) {
+  Episode e{0, 0.0f, 0.0f};
+  const U4 w = draw(P, (uint32_t)ep, kTagRoot, 0, (uint32_t)k);
+  const uint32_t idx = __umulhi(w.x, (uint32_t)P.e.n_belief);
+  if (P.m.kind == kTabular) {
+    e.s = ((const int*)P.e.belief)[idx];
+    if ((unsigned)e.s >= (unsigned)P.m.nS) {   // caller's particle out of range
+      if (report) atomicOr((unsigned int*)&P.t.counters[1], 1u);
+      e.s = 0;
+    }
+  } else {
+    const float* bf = (const float*)P.e.belief;
+    e.x = bf[idx];
+    e.y = bf[P.e.n_belief + idx];
+  }
+  return e;
+}
+
+// All episodes from the root, one thread each.
+template <int AM, bool NAV, bool TRACE>
+__device__ void dev_forward(const PlanView& P, int k, int D, int blk, SearchSmem& L) {
+  stage_search<NAV>(P, L);
+  // dev_full of this iteration starts from nothing.
+  if (blk == 0 && threadIdx.x == 0) P.t.counters[2] = P.t.counters[3] = 0ull;
+  const int ep = blk * kBlock + threadIdx.x;
+  unsigned long long g = 0, nt = 0;
+  const DiskCache dc = NAV ? load_disks(P.m) : DiskCache{};
+  if (ep < P.n_p) {
+    const Episode e = at_root(P, k, ep, true);
+    search<AM, NAV, TRACE>(P, k, D, ep, e, L, dc, g, nt);
+  }
+  tally(P.t, blk, g, nt, L.wave);
 }
 
 // ---------------------------------------------------------------------------
-// Phase: fold the trace of an iteration with D levels into the records.
-// Aggregation keys: (record << (kActBits + 1)) | (a << 1) for action nodes,
-// (record << (kActBits + 1)) | 1
-// for leaves.
+// Phase: fold the trace of iteration k (D levels) into the rows.
+// Aggregation keys: (id << (kActBits + 1)) | (a << 1) for action nodes,
+// (id << (kActBits + 1)) | 1 for leaves.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int record_of(const TreeView& T, int sid) {
-  return sid == 0 ? 0 : T.h_slot[sid - 1].id;
-}
 
 // Stripe q (0: N, 1: C, 2: W) of root action a for the calling block.
 __device__ __forceinline__ unsigned long long* root_stripe(const TreeView& T, int q, int a) {
@@ -866,336 +835,565 @@ __device__ __forceinline__ unsigned long long* root_stripe(const TreeView& T, in
   return T.root_acc + ((size_t)q * T.ra + a) * kStripes + stripe;
 }
 
+// The trace word of episode ep at `lvl` (D: its leaf), or kEmptyKey.
+__device__ __forceinline__ unsigned long long trace_word(const PlanView& P, int k, int D,
+                                                         int lvl, int ep) {
+  const uint32_t run = P.t.run[(size_t)(k - 1) * (size_t)P.n_p + ep];
+  const bool has = lvl < D ? lvl < (int)(run & kRunMask) : (run & kRunLeaf) != 0;
+  return has ? P.t.tr_key[(size_t)lvl * (size_t)P.n_p + ep] : kEmptyKey;
+}
+
 // Long rows: the first visit of each (b, a) in the trace of an iteration
 // sets bit a of b's bitmap and clears N[a], C[a] and W[a] (the root keeps its
 // sums elsewhere).  It runs before the accumulate pass adds the visits.
-__global__ __launch_bounds__(kBlock) void k_claim_wide(PlanView P, int D) {
+__global__ __launch_bounds__(kBlock) void k_claim_wide(PlanView P, int k, int D) {
   if (budget_spent(P)) return;
   const TreeView& T = P.t;
   const long long n = (long long)D * P.n_p;
   for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n;
        i += (long long)gridDim.x * kBlock) {
-    const unsigned long long tk = T.tr_key[i];
+    const int lvl = (int)(i / P.n_p);
+    const unsigned long long tk = trace_word(P, k, D, lvl, (int)(i - (long long)lvl * P.n_p));
     if (tk == kEmptyKey) continue;
-    const unsigned long long body = tk & ~kTraceRec;
+    const unsigned long long body = tk & ~kTraceClaim;
     const int id = (int)(body >> kActBits);
-    const int rid = (tk & kTraceRec) ? id : record_of(T, id);
-    if (rid == 0) continue;
+    if (id == 0) continue;
     const int a = (int)(body & kActMask);
     const uint32_t bit = 1u << (a & 31);
-    if (!(atomicOr(&rec_bits(T, rid)[a >> 5], bit) & bit)) {
-      rec_n(T, rid)[a] = 0;
-      rec_c(T, rid)[a] = 0ull;
-      rec_w(T, rid)[a] = 0ull;
+    if (!(atomicOr(&rec_bits(T, id)[a >> 5], bit) & bit)) {
+      rec_n(T, id)[a] = 0;
+      rec_c(T, id)[a] = 0ull;
+      rec_w(T, id)[a] = 0ull;
     }
   }
 }
 
-__device__ void dev_accum(const PlanView& P, int D, int blk, int nblk, Smem& sm) {
+__device__ void dev_accum(const PlanView& P, int k, int D, int blk, int nblk, Smem& sm) {
   const TreeView& T = P.t;
   AggTable& G = sm.agg;
-  const size_t n_p = (size_t)P.n_p;
   const int per = (P.n_p + kBlock - 1) / kBlock;   // chunks of kBlock items per level
   for (int c = blk; c < (D + 1) * per; c += nblk) {
     const int lvl = c / per;
     const int ep = (c - lvl * per) * kBlock + threadIdx.x;
-    const size_t i = (size_t)lvl * n_p + (size_t)ep;
     unsigned long long tk = kEmptyKey;
-    float v = 0.0f;
-    if (ep < P.n_p) tk = T.tr_key[i];
+    if (ep < P.n_p) tk = trace_word(P, k, D, lvl, ep);
     const bool has = tk != kEmptyKey;
     const bool leaf = lvl == D;
-    unsigned long long key = kEmptyKey;
+    if (!__syncthreads_or(has)) continue;          // uniform
+    // Beliefs that became full join the list of their depth, lvl.
+    const bool claimed = has && (tk & kTraceClaim);
+    const unsigned long long cm = __ballot(claimed);
+    const int wv = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) sm.wave[wv] = (unsigned long long)__popcll(cm);
+    const unsigned long long body = tk & ~kTraceClaim;
+    const int id = (int)(leaf ? body : body >> kActBits);
+    float v = 0.0f;
+    if (has) v = T.tr_val[(size_t)lvl * (size_t)P.n_p + ep];
+    agg_clear(G);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      unsigned int n = 0;
+      for (int i = 0; i < kBlock / 64; ++i) n += (unsigned int)sm.wave[i];
+      sm.n[0] = n ? atomicAdd(&T.full_cnt[lvl], n) : 0u;
+      sm.n[1] = n;
+    }
     if (has) {
-      v = T.tr_val[i];
-      const unsigned long long body = tk & ~kTraceRec;
-      const int id = (int)(leaf ? body : body >> kActBits);
-      const int rid = (tk & kTraceRec) ? id : record_of(T, id);
-      key = ((unsigned long long)(uint32_t)rid << (kActBits + 1)) |
-            (leaf ? 1ull : ((body & kActMask) << 1));
+      const unsigned long long key = ((unsigned long long)(uint32_t)id << (kActBits + 1)) |
+                                     (leaf ? 1ull : ((body & kActMask) << 1));
+      const int sl = agg_slot(G, key);
+      atomicAdd(&G.a[sl], 1ull);
+      const unsigned long long fx = to_fix(v, P.fix_scale);
+      if (fx) atomicAdd(&G.b[sl], fx);
     }
-    if (__syncthreads_or(has)) {
-      agg_clear(G);
-      __syncthreads();
-      if (has) {
-        const int sl = agg_slot(G, key);
-        atomicAdd(&G.a[sl], 1ull);
-        const unsigned long long fx = to_fix(v, P.fix_scale);
-        if (fx) atomicAdd(&G.b[sl], fx);
+    __syncthreads();
+    if (sm.n[1]) {
+      if (claimed) {
+        unsigned int at = sm.n[0] + (unsigned int)__popcll(cm & ((1ull << (threadIdx.x & 63)) - 1));
+        for (int i = 0; i < wv; ++i) at += (unsigned int)sm.wave[i];
+        T.full[full_first(P, lvl) + at] = id;
+        T.node[id].link |= kLinkFull;
       }
-      __syncthreads();
-      for (int j = threadIdx.x; j < kAggSlots; j += kBlock) {
-        const unsigned long long k2 = G.key[j];
-        if (k2 == kEmptyKey) continue;
-        const int rid = (int)(k2 >> (kActBits + 1));
-        if (k2 & 1ull) {
-          BeliefLeaf* lf = rec_leaf(T, rid);
-          atomicAdd(&lf->leaf_cnt, (int)G.a[j]);
-          if (G.b[j]) atomicAdd(&lf->leaf_h, G.b[j]);
-        } else if (rid == 0) {
-          const int a = (int)((k2 >> 1) & kActMask);
-          atomicAdd(root_stripe(T, 0, a), G.a[j]);
-          if (G.b[j]) atomicAdd(root_stripe(T, 1, a), G.b[j]);
-        } else {
-          const int a = (int)((k2 >> 1) & kActMask);
-          atomicAdd(&rec_n(T, rid)[a], (int)G.a[j]);
-          if (G.b[j]) atomicAdd(&rec_c(T, rid)[a], G.b[j]);
-        }
-      }
-      __syncthreads();
     }
+    for (int j = threadIdx.x; j < kAggSlots; j += kBlock) {
+      const unsigned long long k2 = G.key[j];
+      if (k2 == kEmptyKey) continue;
+      const int rid = (int)(k2 >> (kActBits + 1));
+      if (k2 & 1ull) {
+        atomicAdd(&T.info[rid].leaf_cnt, (int)G.a[j]);
+        if (G.b[j]) atomicAdd(&T.node[rid].u.leaf_h, G.b[j]);
+      } else if (rid == 0) {
+        const int a = (int)((k2 >> 1) & kActMask);
+        atomicAdd(root_stripe(T, 0, a), G.a[j]);
+        if (G.b[j]) atomicAdd(root_stripe(T, 1, a), G.b[j]);
+      } else {
+        const int a = (int)((k2 >> 1) & kActMask);
+        atomicAdd(&rec_n(T, rid)[a], (int)G.a[j]);
+        if (G.b[j]) atomicAdd(&rec_c(T, rid)[a], G.b[j]);
+      }
+    }
+    __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------------------
-// Backup (Alg. 3).  Beliefs of depth `dep` were created by level dep-1 of
-// every iteration k' <= k whose depth D_k' >= dep.
+// Backup (Alg. 3).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void load_ranges(const PlanView& P, int dep, int k, Ranges& R) {
-  if (threadIdx.x == 0) {
-    int n = 0;
-    if (P.carry) {                              // a kept subtree's steps first
-      const int f = P.t.carry_rng[2 * dep], c = P.t.carry_rng[2 * dep + 1];
-      for (int i = 0; i < c; ++i) R.step[n++] = f + i;
-    }
-    for (int kk = 1; kk <= k; ++kk) {
-      const int s0 = P.t.step_base[kk - 1];
-      const int Dk = P.t.step_base[kk] - s0;
-      if (Dk >= dep) R.step[n++] = s0 + dep - 1;
-    }
-    R.n = n;
-  }
-  __syncthreads();
+
+// Adds f to the W accumulator of action `target & kActMask` of belief
+// target >> kActBits.
+__device__ __forceinline__ void push_one(const TreeView& T, unsigned long long target,
+                                         unsigned long long f) {
+  const int b = (int)(target >> kActBits), a = (int)(target & kActMask);
+  if (b == 0) atomicAdd(root_stripe(T, 2, a), f);
+  else atomicAdd(&rec_w(T, b)[a], f);
 }
 
-// The parent link of a record, resolved to (record << kActBits) | a (written
-// back); par is the stored link, read by the caller.
-__device__ __forceinline__ unsigned long long resolve_link(const TreeView& T, BeliefHot* mt,
-                                                          unsigned long long par) {
-  if (par != kEmptyKey && (par & kLinkSlot)) {
-    const int psid = (int)((par & ~kLinkSlot) >> kActBits);
-    par = ((unsigned long long)(uint32_t)record_of(T, psid) << kActBits) | (par & kActMask);
-    mt->parent = par;
-  }
-  return par;
-}
-
-// Record of position ep of level step t, or -1 if no belief was inserted there.
-__device__ __forceinline__ int record_at(const PlanView& P, int t, int ep) {
-  const size_t pos = (size_t)t * (size_t)P.n_p + (size_t)ep;
-  return P.t.list[pos] ? (int)(1 + pos) : -1;
-}
-
-// Push V*N_b of a belief into its parent action's W accumulator (parent =
-// (record << kActBits) | a, or kEmptyKey for none).  Beliefs of depth >= 3 mostly
-// have distinct parents, so they add directly; shallower ones share a few
-// parents and are combined per block first (then every thread of the block
-// must call, as it contains barriers; `shared` is uniform).
-constexpr int kPushDirectDepth = 3;
-
-__device__ __forceinline__ void push_values(const PlanView& P, AggTable& G, bool shared,
-                                            unsigned long long parent, float V, int N) {
-  unsigned long long f = 0ull;
-  if (parent != kEmptyKey && N > 0) f = to_fix(V * (float)N, P.fix_scale);
-  if (!shared) {
-    if (f) {
-      const int pr = (int)(parent >> kActBits), a = (int)(parent & kActMask);
-      if (pr == 0) atomicAdd(root_stripe(P.t, 2, a), f);
-      else atomicAdd(&rec_w(P.t, pr)[a], f);
-    }
-    return;
-  }
+// Pushes of a block into action nodes that it shares: combined in LDS first
+// (every thread of the block calls; f = 0: nothing to push).
+__device__ __forceinline__ void push_shared(const TreeView& T, AggTable& G,
+                                            unsigned long long target, unsigned long long f) {
   if (!__syncthreads_or(f != 0ull)) return;   // uniform: nothing to push
   agg_clear(G);
   __syncthreads();
-  if (f) atomicAdd(&G.a[agg_slot(G, parent)], f);
+  if (f) atomicAdd(&G.a[agg_slot(G, target)], f);
   __syncthreads();
-  for (int j = threadIdx.x; j < kAggSlots; j += kBlock) {
-    const unsigned long long key = G.key[j];
-    if (key != kEmptyKey && G.a[j]) {
-      const int pr = (int)(key >> kActBits), a = (int)(key & kActMask);
-      if (pr == 0) atomicAdd(root_stripe(P.t, 2, a), G.a[j]);
-      else atomicAdd(&rec_w(P.t, pr)[a], G.a[j]);
-    }
-  }
+  for (int j = threadIdx.x; j < kAggSlots; j += kBlock)
+    if (G.key[j] != kEmptyKey && G.a[j]) push_one(T, G.key[j], G.a[j]);
   __syncthreads();
 }
 
-// Leaves of this iteration take count and mean heuristic; every belief of
-// depth D pushes V*N_b to its parent action.
-__device__ void dev_backup_leaf(const PlanView& P, int dep, int k, int blk, int nblk,
-                                Smem& sm) {
-  Ranges& R = sm.ranges;
-  load_ranges(P, dep, k, R);
-  unsigned long long beliefs = 0;             // tree statistics (last iteration)
-  // Chunks of kBlock positions: chunk c is block c % per of range c / per
-  // (a division per chunk, on the scalar unit).
-  const int per = (P.n_p + kBlock - 1) / kBlock;
-  for (int c = blk; c < R.n * per; c += nblk) {
-    const int r = c / per;
-    const int ep = (c - r * per) * kBlock + threadIdx.x;
-    int N = 0;
-    float V = 0.0f;
-    unsigned long long parent = kEmptyKey;
-    const int b = ep < P.n_p ? record_at(P, R.step[r], ep) : -1;
-    if (b > 0) {
-      // Every field is read before the first store: on CDNA a wait for a
-      // load also waits for the stores issued before it.
-      BeliefHot* mt = rec_hot(P.t, b);
-      BeliefLeaf* lf = rec_leaf(P.t, b);
-      const int c = lf->leaf_cnt;
-      const unsigned long long hs = lf->leaf_h;
-      const float V0 = mt->V;
-      const int N0 = mt->Nb;
-      const unsigned long long par = mt->parent;
-      if (c > 0) {
-        V = from_fix(hs, P.fix_inv) / (float)c;
-        N = c;
-        mt->V = V;
-        mt->Nb = N;
-        lf->leaf_cnt = 0;
-        if (hs) lf->leaf_h = 0ull;
-      } else {
-        V = V0;
-        N = N0;
-      }
-      parent = resolve_link(P.t, mt, par);
-      ++beliefs;
-    }
-    push_values(P, sm.agg, dep < kPushDirectDepth, parent, V, N);
-  }
-  if (counts_tree(P, k)) {
-    beliefs = block_sum(beliefs, sm.wave);
-    if (threadIdx.x == 0 && beliefs) atomicAdd(&stat_bank(P, k)[kStripes + blk % kStripes], beliefs);
-  }
+// Beliefs of this depth or deeper mostly have distinct parents and push
+// directly; shallower ones share a few parents.
+constexpr int kPushDirectDepth = 3;
+
+__device__ __forceinline__ unsigned long long push_value(const PlanView& P, float V, int N) {
+  return N > 0 ? to_fix(V * (float)N, P.fix_scale) : 0ull;
+}
+// The action node a belief hangs under, from BeliefInfo::own.
+__device__ __forceinline__ unsigned long long parent_of(unsigned long long own, int ob) {
+  return ((own >> kKeyLowBits) << kActBits) | ((own & kLinkKey) >> ob);
 }
 
-// Internal beliefs of depth dep-1 >= 1.  AM >= |A| keeps the row in registers.
+// The full beliefs of one depth: those of a kept subtree (packed at the front
+// of the ids), then the list.
+struct FullSet {
+  int n_kept, n, kept0;
+  const int* ids;
+};
+__device__ __forceinline__ FullSet full_set(const PlanView& P, int dep) {
+  FullSet s;
+  s.n_kept = P.carry ? P.t.carry_rng[2 * dep + 1] : 0;
+  s.kept0 = P.carry ? 1 + P.t.carry_rng[2 * dep] * P.n_p : 0;
+  s.n = s.n_kept + (int)P.t.full_cnt[dep];
+  s.ids = P.t.full + full_first(P, dep);
+  return s;
+}
+__device__ __forceinline__ int full_id(const FullSet& s, int i) {
+  return i < s.n_kept ? s.kept0 + i : s.ids[i - s.n_kept];
+}
+
+// Full leaves of this iteration take count and mean heuristic; every full
+// belief of depth D pushes V*N_b to its parent action.  Beliefs base ..
+// base + kBlock - 1 of the set; every thread of the block calls.
+__device__ __forceinline__ void full_leaves(const PlanView& P, const FullSet& S, int dep, int base,
+                                            Smem& sm) {
+  const TreeView& T = P.t;
+  const int i = base + threadIdx.x;
+  unsigned long long target = 0, f = 0;
+  if (i < S.n) {
+    // Every field is read before the first store: on CDNA a wait for a
+    // load also waits for the stores issued before it.
+    const int b = full_id(S, i);
+    const uint4 nq = *reinterpret_cast<const uint4*>(&T.node[b]);
+    const BeliefInfo in = T.info[b];
+    float V = __uint_as_float(nq.x);
+    int N = in.Nb;
+    if (in.leaf_cnt > 0) {
+      const unsigned long long hs = ((unsigned long long)nq.w << 32) | nq.z;
+      V = from_fix(hs, P.fix_inv) / (float)in.leaf_cnt;
+      N = in.leaf_cnt;
+      T.node[b].V = V;
+      T.info[b].Nb = N;
+      T.info[b].leaf_cnt = 0;
+      if (hs) T.node[b].u.leaf_h = 0ull;
+    }
+    target = parent_of(in.own, P.m.obs_bits);
+    f = push_value(P, V, N);
+  }
+  if (dep >= kPushDirectDepth) {
+    if (f) push_one(T, target, f);
+  } else {
+    push_shared(T, sm.agg, target, f);
+  }
+}
+__device__ void dev_backup_leaf(const PlanView& P, int dep, int k, int blk, int nblk, Smem& sm) {
+  const FullSet S = full_set(P, dep);
+  unsigned long long n = 0;
+  for (int base = blk * kBlock; base < S.n; base += nblk * kBlock) {
+    full_leaves(P, S, dep, base, sm);
+    n += min(kBlock, S.n - base);
+  }
+  if (n && counts_tree(P, k) && threadIdx.x == 0)
+    atomicAdd(&stat_bank(P, k)[kStripes + blk % kStripes], n);
+}
+
+// L_eta Psi of a row whose entry is psi0s[j] but for entry a (a < 0: none),
+// in the order of the level sweep's sums.  flat: psi0s is one value (the
+// uniform reference policy): one exponential serves the whole row, since the
+// weight of the largest entry is exp(0) = 1.
 template <int AM>
-__device__ void dev_backup_level(const PlanView& P, int dep, int k, int blk, int nblk,
-                                 Smem& sm) {
-  Ranges& R = sm.ranges;
-  load_ranges(P, dep - 1, k, R);
+__device__ __forceinline__ float one_row_value(const float (&p0)[AM <= 8 ? AM : 1],
+                                               const float* psi0s, int A, int a, float pa,
+                                               float eta, bool flat) {
+  auto at = [&](int j) { return j == a ? pa : (AM <= 8 ? p0[AM <= 8 ? j : 0] : psi0s[j]); };
+  float m, se = 0.0f;
+  if (flat) {
+    const float p = p0[0];
+    if (a < 0) pa = p;
+    m = A == 1 ? pa : fmaxf(pa, p);
+    const float e = expf(eta * (fminf(pa, p) - m));
+    const float ep = p == m ? 1.0f : e, ea = pa == m ? 1.0f : e;
+#pragma unroll
+    for (int j = 0; j < AM; ++j)
+      if (j < A) se = se + (j == a ? ea : ep);
+  } else {
+    m = at(0);
+#pragma unroll
+    for (int j = 1; j < AM; ++j)
+      if (j < A) m = fmaxf(m, at(j));
+#pragma unroll
+    for (int j = 0; j < AM; ++j)
+      if (j < A) se = se + expf(eta * (at(j) - m));
+  }
+  return m + logf(se) / eta;
+}
+
+// The single-visit beliefs: one thread walks the run of one (iteration,
+// episode) from its last belief up to the first one or to a full one, holding
+// the value that goes up in a register (N = 1 all along), and pushes it into
+// the full belief (or the root) above.  Its records are 16 bytes each, read
+// and written by consecutive lanes at consecutive addresses, one level at a
+// time and kChainAhead levels ahead; the parent of a single-visit belief is
+// visited by nothing else in this phase, so there is nothing to wait for.
+constexpr int kChainAhead = 4;
+
+template <int AM>
+__device__ void dev_chain(const PlanView& P, int k, int blk, int nblk, Smem& sm) {
+  const TreeView& T = P.t;
+  const int A = P.m.nA, ob = P.m.obs_bits, D = depth_at(P, k);
+  const float gamma = P.m.gamma, eta = P.eta;
+  stage_psi0(T, sm.psi0);
+  constexpr int kRegs = AM <= 8 ? AM : 1;
+  float p0[kRegs];
+#pragma unroll
+  for (int j = 0; j < kRegs; ++j) p0[j] = sm.psi0[j < A ? j : 0];
+  bool flat = true;
+  for (int j = 1; j < A; ++j) flat = flat && sm.psi0[j] == sm.psi0[0];
+  const float v0 = one_row_value<AM>(p0, sm.psi0, A, -1, 0.0f, eta, flat);
+  const int per = (P.n_p + kBlock - 1) / kBlock;
+  unsigned long long visits = 0, inner = 0, leaves = 0;
+  for (int c = blk; c < k * per; c += nblk) {
+    const int kk = c / per + 1;
+    const int ep = (c - (kk - 1) * per) * kBlock + threadIdx.x;
+    uint32_t run = 0;
+    if (ep < P.n_p) run = T.run[(size_t)(kk - 1) * (size_t)P.n_p + ep];
+    const int len = (int)((run >> kRunLenShift) & kRunMask);
+    const int top = (int)(run & kRunMask) - 1;          // level of its first belief
+    unsigned long long target = 0, f = 0;
+    int above = D;                                      // depth of what it pushes into
+    if (len > 0) {
+      const int last = top + len - 1;
+      const int id_top = 1 + (first_step(P, kk) + top) * P.n_p + ep;
+      bool open = true, first = true;
+      float V = 0.0f;
+      for (int l0 = last; l0 >= top && open; l0 -= kChainAhead) {
+        uint4 q[kChainAhead];
+#pragma unroll
+        for (int j = 0; j < kChainAhead; ++j) {
+          const int l = max(l0 - j, top);
+          q[j] = *reinterpret_cast<const uint4*>(&T.node[id_top + (l - top) * P.n_p]);
+        }
+#pragma unroll
+        for (int j = 0; j < kChainAhead; ++j) {
+          const int l = l0 - j;
+          if (l < top || !open) continue;
+          const uint32_t link = q[j].y;
+          const int id = id_top + (l - top) * P.n_p;
+          const int a = (int)((link & kLinkKey) >> ob);
+          if (link & (kLinkFull | kLinkClaim)) {
+            // (a run whose last belief is full pushes from the depth sweep)
+            if (!first) {
+              target = ((unsigned long long)(uint32_t)id << kActBits) | (uint32_t)a;
+              f = push_value(P, V, 1);
+            }
+            above = l + 1;
+            open = false;
+            continue;
+          }
+          if (l + 1 == D) ++leaves;
+          else ++visits;
+          if (link & kLinkAct) {
+            // V_curr = L_eta Psi before the update: the stored value, or the
+            // initial row's at the first backup.
+            const float vc = kk == k ? v0 : __uint_as_float(q[j].x);
+            const float r = fix_round(__uint_as_float(q[j].z), P.fix_scale, P.fix_inv);
+            const float w = first ? 0.0f : fix_round(V, P.fix_scale, P.fix_inv);
+            const float pa = (__uint_as_float(q[j].w) - vc) + (r + gamma * w);
+            V = one_row_value<AM>(p0, sm.psi0, A, a, pa, eta, flat);
+            *reinterpret_cast<uint4*>(&T.node[id]) =
+                make_uint4(__float_as_uint(V), link, q[j].z, __float_as_uint(pa));
+            ++inner;
+          } else {
+            V = __uint_as_float(q[j].x);
+          }
+          first = false;
+        }
+      }
+      if (open) {
+        target = parent_of(T.info[id_top].own, ob);
+        f = push_value(P, V, 1);
+        above = top;
+      }
+    }
+    if (f && above + 1 >= kPushDirectDepth) push_one(T, target, f);
+    push_shared(T, sm.agg, target, above + 1 < kPushDirectDepth ? f : 0ull);
+  }
+  // The sweeps' work over the plan, then the tree statistics.
+  const unsigned long long vi = block_sum(visits | (inner << 32), sm.wave);
+  const unsigned long long lf = block_sum(leaves, sm.wave);
+  if (threadIdx.x == 0) {
+    const unsigned long long v = vi & 0xffffffffull, in = vi >> 32;
+    unsigned long long* sw = T.stats + (size_t)kStatSweep * kStripes + blk % kStripes;
+    if (v) atomicAdd(sw, v);
+    if (in) atomicAdd(sw + kStripes, in);
+    if (in) atomicAdd(sw + 2 * kStripes, in);
+    if (counts_tree(P, k)) {
+      unsigned long long* bank = stat_bank(P, k);
+      if (in) atomicAdd(&bank[blk % kStripes], in);
+      if (v + lf) atomicAdd(&bank[kStripes + blk % kStripes], v + lf);
+    }
+  }
+}
+
+// The trace and the runs in one launch: the two touch nothing in common (the
+// walk goes by kLinkClaim, which the search has set), so half of the blocks
+// take one and half the other.
+__host__ __device__ inline int fold_split(int nblk) { return nblk < 2 ? 0 : (nblk + 1) / 2; }
+template <int AM>
+__device__ void dev_fold(const PlanView& P, int k, int blk, int nblk, Smem& sm) {
+  const int half = fold_split(nblk);
+  if (half == 0) {
+    dev_accum(P, k, depth_at(P, k), 0, 1, sm);
+    dev_chain<AM>(P, k, 0, 1, sm);
+  } else if (blk < half) {
+    dev_chain<AM>(P, k, blk, half, sm);
+  } else {
+    dev_accum(P, k, depth_at(P, k), blk - half, nblk - half, sm);
+  }
+}
+
+// An accumulator that other blocks of the same launch add to, once their adds
+// are known to be done (the line may be stale in this XCD's cache).
+__device__ __forceinline__ unsigned long long read_shared(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+struct SweepCount {
+  unsigned long long beliefs, internal, nodes;
+};
+
+// Full beliefs of depth dep >= 1, base .. base + kBlock - 1 of the set.
+// AM >= |A| keeps the row in registers.  wait() returns once the deeper
+// depths' adds to W are done; every thread of the block calls it, after its other
+// loads are on their way.
+template <int AM, typename Wait>
+__device__ __forceinline__ void full_level(const PlanView& P, const FullSet& S, int dep, int base,
+                                           Smem& sm, SweepCount& cnt, Wait wait) {
+  const TreeView& T = P.t;
   const int A = P.m.nA;
   const float gamma = P.m.gamma, eta = P.eta, inv = P.fix_inv;
-  unsigned long long nodes = 0, beliefs = 0;  // tree statistics (last iteration)
-  unsigned long long internal = 0;            // beliefs with an action node
-  const int per = (P.n_p + kBlock - 1) / kBlock;
-  for (int c = blk; c < R.n * per; c += nblk) {
-    const int r = c / per;
-    const int ep = (c - r * per) * kBlock + threadIdx.x;
-    int N = 0;
-    float V = 0.0f;
-    unsigned long long parent = kEmptyKey;
-    const int b = ep < P.n_p ? record_at(P, R.step[r], ep) : -1;
-    if (b > 0) {
-      float* prow = rec_psi(P.t, b);
-      const int* nrow = rec_n(P.t, b);
-      unsigned long long* crow = rec_c(P.t, b);
-      unsigned long long* wrow = rec_w(P.t, b);
-      BeliefHot* mt = rec_hot(P.t, b);
-      // Two rounds of loads, both before the belief's first store (a wait for
-      // a load also waits for the stores issued before it): the hot fields
-      // and the visit counts, then -- for a belief with an action node -- its
-      // preference row and the C and W of its visited actions only.
-      const uint4 hq = *reinterpret_cast<const uint4*>(mt);   // V, N_b, parent
-      int n[AM];
+  const int i = base + threadIdx.x;
+  const bool have = i < S.n;
+  const int b = have ? full_id(S, i) : 0;
+  float* prow = rec_psi(T, b);
+  const int* nrow = rec_n(T, b);
+  unsigned long long* crow = rec_c(T, b);
+  unsigned long long* wrow = rec_w(T, b);
+  BeliefInfo in{0, 0, 0ull};
+  float V = 0.0f;
+  int n[AM];
+  float psi[AM];
+  unsigned long long cf[AM], wf[AM];
 #pragma unroll
-      for (int j = 0; j < AM; j += 4) {
-        int4 c = make_int4(0, 0, 0, 0);
-        if (j < A) c = *reinterpret_cast<const int4*>(nrow + j);
-        n[j] = c.x; n[j + 1] = c.y; n[j + 2] = c.z; n[j + 3] = c.w;
-      }
-      const float V0 = __uint_as_float(hq.x);
-      const int N0 = (int)hq.y;
-      const unsigned long long par = ((unsigned long long)hq.w << 32) | hq.z;
-      float psi[AM];
-      unsigned long long cf[AM], wf[AM];
+  for (int j = 0; j < AM; ++j) { n[j] = 0; psi[j] = 0.0f; cf[j] = 0ull; wf[j] = 0ull; }
+  // Two rounds of loads, both before the belief's first store (a wait for a
+  // load also waits for the stores issued before it): the parent, value and
+  // visit counts, then -- for a belief with an action node -- its preference
+  // row and the C of its visited actions only.
+  if (have) {
+    in = T.info[b];
+    V = T.node[b].V;
 #pragma unroll
-      for (int j = 0; j < AM; ++j) { psi[j] = 0.0f; cf[j] = 0ull; wf[j] = 0ull; }
-      bool any = false;
-#pragma unroll
-      for (int j = 0; j < AM; ++j) any = any || (j < A && n[j] > 0);
-      if (any) {
-#pragma unroll
-        for (int j = 0; j < AM; j += 4) {
-          float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-          if (j < A) q = *reinterpret_cast<const float4*>(prow + j);
-          psi[j] = q.x; psi[j + 1] = q.y; psi[j + 2] = q.z; psi[j + 3] = q.w;
-        }
-#pragma unroll
-        for (int j = 0; j < AM; ++j)
-          if (j < A && n[j] > 0) { cf[j] = crow[j]; wf[j] = wrow[j]; }
-        // V_curr = L_eta Psi (Eq. 3) before the update.
-        float m = psi[0];
-#pragma unroll
-        for (int j = 1; j < AM; ++j)
-          if (j < A) m = fmaxf(m, psi[j]);
-        float se = 0.0f;
-#pragma unroll
-        for (int j = 0; j < AM; ++j)
-          if (j < A) se = se + expf(eta * (psi[j] - m));
-        const float vc = m + logf(se) / eta;
-        // Q = C/N + gamma W with W = sum_children V N_b / N; Psi <- Psi - V_curr + Q.
-        int nsum = 0;
-#pragma unroll
-        for (int j = 0; j < AM; ++j) {
-          if (j < A && n[j] > 0) {
-            const float c = from_fix(cf[j], inv);
-            const float w = from_fix(wf[j], inv);
-            const float fn = (float)n[j];
-            const float q = c / fn + gamma * (w / fn);
-            psi[j] = (psi[j] - vc) + q;
-            nsum += n[j];
-          }
-        }
-        // V = L_eta Psi after the update; N_b = sum_a N(b, a).
-        float m2 = psi[0];
-#pragma unroll
-        for (int j = 1; j < AM; ++j)
-          if (j < A) m2 = fmaxf(m2, psi[j]);
-        float se2 = 0.0f;
-#pragma unroll
-        for (int j = 0; j < AM; ++j)
-          if (j < A) se2 = se2 + expf(eta * (psi[j] - m2));
-        V = m2 + logf(se2) / eta;
-        N = nsum;
-#pragma unroll
-        for (int j = 0; j < AM; j += 4)
-          if (j < A)
-            *reinterpret_cast<float4*>(prow + j) =
-                make_float4(psi[j], psi[j + 1], psi[j + 2], psi[j + 3]);
-        // W is rebuilt by the children's pushes of the next sweep.
-#pragma unroll
-        for (int j = 0; j < AM; ++j)
-          if (j < A && n[j] > 0 && wf[j]) wrow[j] = 0ull;
-        mt->V = V;
-        mt->Nb = N;
-        ++internal;
-      } else {
-        V = V0;
-        N = N0;
-      }
-      parent = resolve_link(P.t, mt, par);
-#pragma unroll
-      for (int j = 0; j < AM; ++j) nodes += (j < A && n[j] > 0) ? 1ull : 0ull;
-      ++beliefs;
+    for (int j = 0; j < AM; j += 4) {
+      int4 c = make_int4(0, 0, 0, 0);
+      if (j < A) c = *reinterpret_cast<const int4*>(nrow + j);
+      n[j] = c.x; n[j + 1] = c.y; n[j + 2] = c.z; n[j + 3] = c.w;
     }
-    push_values(P, sm.agg, dep - 1 < kPushDirectDepth, parent, V, N);
   }
+  int N = in.Nb;
+  bool any = false;
+#pragma unroll
+  for (int j = 0; j < AM; ++j) any = any || (j < A && n[j] > 0);
+  if (any) {
+#pragma unroll
+    for (int j = 0; j < AM; j += 4) {
+      float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (j < A) q = *reinterpret_cast<const float4*>(prow + j);
+      psi[j] = q.x; psi[j + 1] = q.y; psi[j + 2] = q.z; psi[j + 3] = q.w;
+    }
+#pragma unroll
+    for (int j = 0; j < AM; ++j)
+      if (j < A && n[j] > 0) cf[j] = crow[j];
+  }
+  wait();
+  unsigned long long target = 0, f = 0;
+  if (any) {
+#pragma unroll
+    for (int j = 0; j < AM; ++j)
+      if (j < A && n[j] > 0) wf[j] = read_shared(wrow + j);
+    // V_curr = L_eta Psi (Eq. 3) before the update.
+    float m = psi[0];
+#pragma unroll
+    for (int j = 1; j < AM; ++j)
+      if (j < A) m = fmaxf(m, psi[j]);
+    float se = 0.0f;
+#pragma unroll
+    for (int j = 0; j < AM; ++j)
+      if (j < A) se = se + expf(eta * (psi[j] - m));
+    const float vc = m + logf(se) / eta;
+    // Q = C/N + gamma W with W = sum_children V N_b / N; Psi <- Psi - V_curr + Q.
+    int nsum = 0;
+#pragma unroll
+    for (int j = 0; j < AM; ++j) {
+      if (j < A && n[j] > 0) {
+        const float c = from_fix(cf[j], inv);
+        const float w = from_fix(wf[j], inv);
+        const float fn = (float)n[j];
+        const float q = c / fn + gamma * (w / fn);
+        psi[j] = (psi[j] - vc) + q;
+        nsum += n[j];
+        ++cnt.nodes;
+      }
+    }
+    // V = L_eta Psi after the update; N_b = sum_a N(b, a).
+    float m2 = psi[0];
+#pragma unroll
+    for (int j = 1; j < AM; ++j)
+      if (j < A) m2 = fmaxf(m2, psi[j]);
+    float se2 = 0.0f;
+#pragma unroll
+    for (int j = 0; j < AM; ++j)
+      if (j < A) se2 = se2 + expf(eta * (psi[j] - m2));
+    V = m2 + logf(se2) / eta;
+    N = nsum;
+    ++cnt.internal;
+  }
+  if (have) {
+    target = parent_of(in.own, P.m.obs_bits);
+    f = push_value(P, V, N);
+    ++cnt.beliefs;
+  }
+  // The push first: the next depth waits for it, not for the stores.
+  if (dep >= kPushDirectDepth) {
+    if (f) push_one(T, target, f);
+  } else {
+    push_shared(T, sm.agg, target, f);
+  }
+  if (any) {
+#pragma unroll
+    for (int j = 0; j < AM; j += 4)
+      if (j < A)
+        *reinterpret_cast<float4*>(prow + j) =
+            make_float4(psi[j], psi[j + 1], psi[j + 2], psi[j + 3]);
+    // W is rebuilt by the children's pushes of the next iteration.
+#pragma unroll
+    for (int j = 0; j < AM; ++j)
+      if (j < A && n[j] > 0 && wf[j]) wrow[j] = 0ull;
+    T.node[b].V = V;
+    T.info[b].Nb = N;
+  }
+}
+
+template <typename Wait>
+__device__ void dev_backup_root(const PlanView& P, int k, Smem& sm, Wait wait);
+
+// The full beliefs of every depth and the root, in one launch.  Blocks take
+// items (kBlock beliefs of one depth; the root last) from a counter, deepest
+// depth first; an item waits until every item of the deeper depths is done,
+// with everything but W already read.  Items are taken in that order by blocks
+// that run, so whatever the residency the lowest unfinished item waits for
+// nothing.  Only the W accumulators pass from one depth to the next: they are
+// added to and read past the caches, so an item needs no cache write-back or
+// invalidation, only its own adds to have arrived.  Most depths hold no full
+// belief: they cost nothing here and about 4.4 us each as a launch of their
+// own (nav2d, depth 10: nine of them and the root's, in every iteration).
+template <int AM>
+__device__ void dev_full(const PlanView& P, int k, int blk, Smem& sm) {
+  const TreeView& T = P.t;
+  const int D = depth_at(P, k);
+  const int lane = threadIdx.x & 63;
+  const FullSet leaves = full_set(P, D);
+  const int n_leaf = (leaves.n + kBlock - 1) / kBlock;
+  // Lane l: the first item of depth D - 1 - l; lane D - 1: the root's.
+  const int my_dep = D - 1 - lane;
+  int n = 0;
+  if (my_dep >= 1) n = (full_set(P, my_dep).n + kBlock - 1) / kBlock;
+  int start = n_leaf + (int)wave_incl_scan((unsigned long long)n) - n;
+  if (my_dep < 0) start = INT_MAX;
+  SweepCount cnt{0, 0, 0};
+  unsigned long long leaf_cnt = 0;
+  for (;;) {
+    if (threadIdx.x == 0) sm.n[0] = (unsigned int)atomicAdd(&T.counters[2], 1ull);
+    __syncthreads();
+    const int item = (int)sm.n[0];
+    const int l = __popcll(__ballot(start <= item)) - 1;
+    const int first = l < 0 ? 0 : __shfl(start, l, 64);
+    const int dep = D - 1 - l;                    // D: the leaves
+    if (dep == 0 && item > first) break;          // past the root: uniform
+    auto wait = [&]() {
+      if (threadIdx.x == 0 && first > 0)
+        while (read_shared(&T.counters[3]) < (unsigned long long)first) __builtin_amdgcn_s_sleep(1);
+      __syncthreads();
+    };
+    if (dep == 0) {
+      dev_backup_root(P, k, sm, wait);
+      break;
+    }
+    if (dep == D) {
+      full_leaves(P, leaves, D, item * kBlock, sm);
+      leaf_cnt += min(kBlock, leaves.n - item * kBlock);
+    } else {
+      full_level<AM>(P, full_set(P, dep), dep, (item - first) * kBlock, sm, cnt, wait);
+    }
+    stores_done();                                // this wavefront's adds
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&T.counters[3], 1ull);
+  }
+  __syncthreads();
   // The sweep's work over the plan (every iteration), then the tree
   // statistics (the last iteration).  A block visits fewer than 2^32 beliefs.
-  const unsigned long long vi = block_sum(beliefs | (internal << 32), sm.wave);
-  const unsigned long long nd = block_sum(nodes, sm.wave);
+  const unsigned long long vi = block_sum(cnt.beliefs | (cnt.internal << 32), sm.wave);
+  const unsigned long long nd = block_sum(cnt.nodes, sm.wave);
   if (threadIdx.x == 0) {
-    unsigned long long* sw = P.t.stats + (size_t)kStatSweep * kStripes + blk % kStripes;
+    unsigned long long* sw = T.stats + (size_t)kStatSweep * kStripes + blk % kStripes;
     if (vi & 0xffffffffull) atomicAdd(sw, vi & 0xffffffffull);
     if (vi >> 32) atomicAdd(sw + kStripes, vi >> 32);
     if (nd) atomicAdd(sw + 2 * kStripes, nd);
     if (counts_tree(P, k)) {
       unsigned long long* bank = stat_bank(P, k);
+      const unsigned long long nb = (vi & 0xffffffffull) + leaf_cnt;
       if (nd) atomicAdd(&bank[blk % kStripes], nd);
-      if (vi & 0xffffffffull) atomicAdd(&bank[kStripes + blk % kStripes], vi & 0xffffffffull);
+      if (nb) atomicAdd(&bank[kStripes + blk % kStripes], nb);
     }
   }
 }
@@ -1248,15 +1446,12 @@ __device__ __forceinline__ float wave_sumf(float v) {
 // batch of loads for Psi, N and its metadata, one batch of C and W loads per
 // four quads of the lane, and the stores at the end: no load waits behind a
 // store of the same belief.
-constexpr int kWideChunk = 16;              // positions a wavefront scans at once
-
 template <int QPL>
 __device__ void dev_backup_level_wide(const PlanView& P, int dep, int k, int blk, int nblk,
                                       Smem& sm) {
   static_assert(QPL % 4 == 0 && 4 * QPL <= 64, "quads per lane");
-  Ranges& R = sm.ranges;
-  load_ranges(P, dep - 1, k, R);
   const TreeView& T = P.t;
+  const FullSet S = full_set(P, dep - 1);
   const int A = P.m.nA;
   const int nq = T.ra / 4;
   const float gamma = P.m.gamma, eta = P.eta, inv = P.fix_inv;
@@ -1264,25 +1459,15 @@ __device__ void dev_backup_level_wide(const PlanView& P, int dep, int k, int blk
   const int waves = kBlock / 64;
   unsigned long long nodes = 0, beliefs = 0;  // tree statistics (lane 0 counts)
   unsigned long long internal = 0;            // beliefs with an action node
-  // Each wavefront takes kWideChunk positions of one level step at a time and
-  // visits the beliefs among them one after the other.
-  const int per = (P.n_p + kWideChunk - 1) / kWideChunk;
-  for (long long c = (long long)blk * waves + (threadIdx.x >> 6); c < (long long)R.n * per;
-       c += (long long)nblk * waves) {
-    const int r = (int)(c / per);
-    const int ep = (int)(c - (long long)r * per) * kWideChunk + lane;
-    const int bl = (lane < kWideChunk && ep < P.n_p) ? record_at(P, R.step[r], ep) : -1;
-    unsigned long long todo = __ballot(bl > 0);
-    while (todo) {
+  {
+    for (int i = blk * waves + (int)(threadIdx.x >> 6); i < S.n; i += nblk * waves) {
       // b is uniform: addresses are a scalar base plus 32-bit lane offsets.
-      const int b = __builtin_amdgcn_readfirstlane(__shfl(bl, __ffsll((long long)todo) - 1, 64));
-      todo &= todo - 1;
+      const int b = __builtin_amdgcn_readfirstlane(full_id(S, i));
       const float4* p4 = reinterpret_cast<const float4*>(rec_psi(T, b));
       const uint32_t* bits = rec_bits(T, b);
       const int* nrow = rec_n(T, b);
       const unsigned long long* crow = rec_c(T, b);
       unsigned long long* wrow = rec_w(T, b);
-      BeliefHot* mt = rec_hot(T, b);
       // Psi and the visited flags (the bitmap's nibble of each quad).
       float pf[4 * QPL];
       uint32_t vb[QPL];
@@ -1300,9 +1485,9 @@ __device__ void dev_backup_level_wide(const PlanView& P, int dep, int k, int blk
       }
       // Read after the row: these uniform values are moved to scalar
       // registers at once, which waits for them.
-      const float V0 = mt->V;
-      const int N0 = mt->Nb;
-      const unsigned long long par = mt->parent;
+      const float V0 = T.node[b].V;
+      const int N0 = T.info[b].Nb;
+      const unsigned long long own = T.info[b].own;
 #pragma unroll
       for (int i = 0; i < QPL; ++i) vb[i] = (vb[i] >> (4 * ((lane + 64 * i) & 7))) & 15u;
       bool vis = false;                         // padding is never visited
@@ -1326,10 +1511,10 @@ __device__ void dev_backup_level_wide(const PlanView& P, int dep, int k, int blk
           if (4 * (lane + 64 * (i >> 2)) + (i & 3) < A) se = se + expf(eta * (pf[i] - m));
         const float vc = m + logf(wave_sumf(se)) / eta;
         // Psi <- Psi - V_curr + Q, Q = C/N + gamma W/N (Eq. 5), for visited
-        // actions.  An unvisited action reads the belief's hot fields instead
-        // (read above), so the loads issue without branches.
-        const int* spare_n = reinterpret_cast<const int*>(mt);
-        const unsigned long long* spare_l = &mt->parent;
+        // actions.  An unvisited action reads the belief's info instead (read
+        // above), so the loads issue without branches.
+        const int* spare_n = &T.info[b].Nb;
+        const unsigned long long* spare_l = &T.info[b].own;
         int nsum = 0, nn = 0;
 #pragma unroll
         for (int i0 = 0; i0 < QPL; i0 += 4) {
@@ -1385,20 +1570,13 @@ __device__ void dev_backup_level_wide(const PlanView& P, int dep, int k, int blk
       }
       if (lane == 0) {
         ++beliefs;
-        const unsigned long long parent = resolve_link(T, mt, par);
-        if (parent != kEmptyKey && N > 0) {
-          const unsigned long long f = to_fix(V * (float)N, P.fix_scale);
-          if (f) {
-            const int pr = (int)(parent >> kActBits), a = (int)(parent & kActMask);
-            if (pr == 0) atomicAdd(root_stripe(T, 2, a), f);
-            else atomicAdd(&rec_w(T, pr)[a], f);
-          }
-        }
+        const unsigned long long f = push_value(P, V, N);
+        if (f) push_one(T, parent_of(own, P.m.obs_bits), f);
       }
       // The record's stores come last, so that nothing above waits for them.
       if (upd) {
-        mt->V = V;                              // the same value in every lane
-        mt->Nb = N;
+        T.node[b].V = V;                        // the same value in every lane
+        T.info[b].Nb = N;
         float4* pw4 = reinterpret_cast<float4*>(rec_psi(T, b));
 #pragma unroll
         for (int i = 0; i < QPL; ++i)
@@ -1419,6 +1597,135 @@ __device__ void dev_backup_level_wide(const PlanView& P, int dep, int k, int blk
       unsigned long long* bank = stat_bank(P, k);
       if (nodes) atomicAdd(&bank[blk % kStripes], nodes);
       if (beliefs) atomicAdd(&bank[kStripes + blk % kStripes], beliefs);
+    }
+  }
+}
+
+// The single-visit beliefs of long rows (dev_chain), one wavefront per run,
+// kWideRuns runs of one iteration per wavefront: the lanes hold the initial row
+// in registers and evaluate L_eta of it with one entry replaced, in the order
+// of the level sweep, so no row is read or written.  The records of the runs
+// are read by the lanes together, kChainAhead levels at a time.
+constexpr int kWideRuns = 16;
+
+template <int QPL>
+__device__ __forceinline__ float wave_row_value(const float (&p0)[4 * QPL], int A, int a, float pa,
+                                                float eta, int lane) {
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 4 * QPL; ++i) {
+    const int j = 4 * (lane + 64 * (i >> 2)) + (i & 3);
+    if (j < A) m = fmaxf(m, j == a ? pa : p0[i]);
+  }
+  m = wave_maxf(m);
+  float se = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4 * QPL; ++i) {
+    const int j = 4 * (lane + 64 * (i >> 2)) + (i & 3);
+    if (j < A) se = se + expf(eta * ((j == a ? pa : p0[i]) - m));
+  }
+  return m + logf(wave_sumf(se)) / eta;
+}
+
+template <int QPL>
+__device__ void dev_chain_wide(const PlanView& P, int k, int blk, int nblk) {
+  const TreeView& T = P.t;
+  const int A = P.m.nA, ob = P.m.obs_bits, D = depth_at(P, k);
+  const int nq = T.ra / 4;
+  const float gamma = P.m.gamma, eta = P.eta;
+  const int lane = threadIdx.x & 63;
+  const int waves = kBlock / 64;
+  float p0[4 * QPL];
+#pragma unroll
+  for (int i = 0; i < QPL; ++i) {
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (lane + 64 * i < nq) v = reinterpret_cast<const float4*>(T.psi0)[lane + 64 * i];
+    p0[4 * i] = v.x; p0[4 * i + 1] = v.y; p0[4 * i + 2] = v.z; p0[4 * i + 3] = v.w;
+  }
+  const float v0 = wave_row_value<QPL>(p0, A, -1, 0.0f, eta, lane);
+  unsigned long long visits = 0, inner = 0, leaves = 0;
+  const int per = (P.n_p + kWideRuns - 1) / kWideRuns;
+  for (int c = blk * waves + (int)(threadIdx.x >> 6); c < k * per; c += nblk * waves) {
+    const int kk = c / per + 1;
+    const int ep = (c - (kk - 1) * per) * kWideRuns + lane;
+    uint32_t run = 0;
+    if (lane < kWideRuns && ep < P.n_p) run = T.run[(size_t)(kk - 1) * (size_t)P.n_p + ep];
+    const int my_len = (int)((run >> kRunLenShift) & kRunMask);
+    const int my_top = (int)(run & kRunMask) - 1;
+    const int my_id = 1 + (first_step(P, kk) + my_top) * P.n_p + ep;   // its first belief
+    uint4 q[kChainAhead];
+#pragma unroll
+    for (int j = 0; j < kChainAhead; ++j)
+      q[j] = my_len > 0 ? *reinterpret_cast<const uint4*>(
+                              &T.node[my_id + max(my_len - 1 - j, 0) * P.n_p])
+                        : make_uint4(0u, 0u, 0u, 0u);
+    unsigned long long todo = __ballot(my_len > 0);
+    while (todo) {
+      const int src = __ffsll((long long)todo) - 1;
+      todo &= todo - 1;
+      const int len = __builtin_amdgcn_readfirstlane(__shfl(my_len, src, 64));
+      const int top = __builtin_amdgcn_readfirstlane(__shfl(my_top, src, 64));
+      const int id_top = __builtin_amdgcn_readfirstlane(__shfl(my_id, src, 64));
+      unsigned long long target = 0, f = 0;
+      bool open = true, first = true;
+      float V = 0.0f;
+      for (int i0 = len - 1; i0 >= 0 && open; i0 -= kChainAhead) {
+#pragma unroll
+        for (int j = 0; j < kChainAhead; ++j) {
+          const int i = i0 - j;
+          if (i < 0 || !open) continue;
+          const int id = id_top + i * P.n_p;
+          uint4 n;
+          if (i0 == len - 1) {
+            n = make_uint4(__shfl(q[j].x, src, 64), __shfl(q[j].y, src, 64),
+                           __shfl(q[j].z, src, 64), __shfl(q[j].w, src, 64));
+          } else {
+            n = *reinterpret_cast<const uint4*>(&T.node[id]);
+          }
+          const uint32_t link = __builtin_amdgcn_readfirstlane(n.y);
+          const int a = (int)((link & kLinkKey) >> ob);
+          if (link & (kLinkFull | kLinkClaim)) {
+            if (!first) {
+              target = ((unsigned long long)(uint32_t)id << kActBits) | (uint32_t)a;
+              f = push_value(P, V, 1);
+            }
+            open = false;
+            continue;
+          }
+          if (top + i + 1 == D) ++leaves;
+          else ++visits;
+          if (link & kLinkAct) {
+            const float vc = kk == k ? v0 : __uint_as_float(n.x);
+            const float r = fix_round(__uint_as_float(n.z), P.fix_scale, P.fix_inv);
+            const float w = first ? 0.0f : fix_round(V, P.fix_scale, P.fix_inv);
+            const float pa = (__uint_as_float(n.w) - vc) + (r + gamma * w);
+            V = wave_row_value<QPL>(p0, A, a, pa, eta, lane);
+            if (lane == 0)
+              *reinterpret_cast<uint4*>(&T.node[id]) =
+                  make_uint4(__float_as_uint(V), link, n.z, __float_as_uint(pa));
+            ++inner;
+          } else {
+            V = __uint_as_float(n.x);
+          }
+          first = false;
+        }
+      }
+      if (open && lane == 0) {
+        target = parent_of(T.info[id_top].own, ob);
+        f = push_value(P, V, 1);
+      }
+      if (f && lane == 0) push_one(T, target, f);
+    }
+  }
+  if (lane == 0) {
+    unsigned long long* sw = T.stats + (size_t)kStatSweep * kStripes + blk % kStripes;
+    if (visits) atomicAdd(sw, visits);
+    if (inner) atomicAdd(sw + kStripes, inner);
+    if (inner) atomicAdd(sw + 2 * kStripes, inner);
+    if (counts_tree(P, k)) {
+      unsigned long long* bank = stat_bank(P, k);
+      if (inner) atomicAdd(&bank[blk % kStripes], inner);
+      if (visits + leaves) atomicAdd(&bank[kStripes + blk % kStripes], visits + leaves);
     }
   }
 }
@@ -1583,59 +1890,84 @@ __device__ void dev_backup_root_wide(const PlanView& P, int k, double* buf) {
   if (any && threadIdx.x == 0) {
     const double v = mm + log(run) / eta;
     T.v_root[0] = v;
-    BeliefHot* mt = rec_hot(T, 0);
-    mt->V = (float)v;
-    mt->Nb = (int)cnt[1];
+    T.node[0].V = (float)v;
+    T.info[0].Nb = (int)cnt[1];
     if (counts_tree(P, k)) atomicAdd(&stat_bank(P, k)[0], cnt[0]);
   }
 }
 
-// The root row in double precision, updated in place (one thread).
-// Run by the block's first wavefront.  Lane s sums stripe s of the root's
-// action nodes; lane j then owns action j: it evaluates that action's
-// exponentials, and lane 0 adds them up in action order (the order of the
-// serial definition, so every sum rounds exactly as it would there).
+// The root row in double precision, updated in place, by one block (rows of up
+// to kMaxA actions).  Sixteen lanes sum the 64 stripes of one of the 3|A| sums
+// (N, C, W of each action); lane j of the first wavefront then owns action j:
+// it evaluates that action's exponentials, and every lane adds them up in
+// action order (the order of the serial definition, so every sum rounds
+// exactly as it would there).
 
-// Sum of x over lanes 0..A-1 in lane order, broadcast to the wave.
-__device__ __forceinline__ double ordered_sum(double x, int A) {
+// Lane j's value in every lane (j uniform).
+__device__ __forceinline__ double lane_value(double x, int j) {
+  const unsigned long long v = (unsigned long long)__double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, j);
+  const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), j);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// Sum of x over lanes 0..A-1 in lane order; upto: the sum up to this lane.
+__device__ __forceinline__ double ordered_sum(double x, int A, double& upto) {
+  const int lane = threadIdx.x & 63;
   double s = 0.0;
-  for (int j = 0; j < A; ++j) s = s + __shfl(x, j, 64);
+  for (int j = 0; j < A; ++j) {
+    s = s + lane_value(x, j);
+    if (lane == j) upto = s;
+  }
   return s;
 }
 
-__device__ void dev_backup_root(const PlanView& P, int k) {
-  if (threadIdx.x >= 64) return;
+template <typename Wait>
+__device__ void dev_backup_root(const PlanView& P, int k, Smem& sm, Wait wait) {
+  const TreeView& T = P.t;
   const int A = P.m.nA;
+  double p_me = -INFINITY;
+  if ((int)threadIdx.x < A) p_me = T.psi_root[threadIdx.x];
+  wait();
+  static_assert(3 * kMaxA <= kAggSlots && kStripes == 64, "sums fit the table");
+  unsigned long long* sums = sm.agg.a;          // [3][A]
+  for (int r0 = 0; r0 < 3 * A; r0 += kBlock / 16) {
+    const int r = r0 + (int)threadIdx.x / 16, l = threadIdx.x & 15;
+    unsigned long long v = 0;
+    if (r < 3 * A) {
+      const int q = r / A, a = r - q * A;
+      unsigned long long* p = T.root_acc + ((size_t)q * T.ra + a) * kStripes + l;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // W was added to in this launch; N and C in earlier ones.
+        v += read_shared(p + 16 * i);
+        if (q == 2) p[16 * i] = 0ull;
+      }
+    }
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
+    if (r < 3 * A && l == 0) sums[r] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
   const int lane = threadIdx.x;
   root_gate(P, k, lane);
   const bool act = lane < A;
-  unsigned long long* acc = P.t.root_acc;
-  long long n_me = 0, c_me = 0, w_me = 0;     // sums of action `lane`
-  for (int j = 0; j < A; ++j) {
-    unsigned long long* w = &acc[((size_t)2 * P.t.ra + j) * kStripes + lane];
-    const unsigned long long n = wave_sum(acc[((size_t)0 * P.t.ra + j) * kStripes + lane]);
-    const unsigned long long c = wave_sum(acc[((size_t)1 * P.t.ra + j) * kStripes + lane]);
-    const unsigned long long wv = wave_sum(*w);
-    *w = 0ull;
-    if (lane == j) {
-      n_me = (long long)n;
-      c_me = (long long)c;
-      w_me = (long long)wv;
-    }
-  }
-  double* psi = P.t.psi_root;
+  const long long n_me = act ? (long long)sums[lane] : 0;
+  const long long c_me = act ? (long long)sums[A + lane] : 0;
+  const long long w_me = act ? (long long)sums[2 * A + lane] : 0;
+  double* psi = T.psi_root;
   const double eta = P.eta64;
-  const double p_me = act ? psi[lane] : -INFINITY;
-  if (act) {                                  // record 0 keeps the totals
-    rec_n(P.t, 0)[lane] = (int)n_me;
-    rec_c(P.t, 0)[lane] = (unsigned long long)c_me;
+  if (act) {                                  // belief 0 keeps the totals
+    rec_n(T, 0)[lane] = (int)n_me;
+    rec_c(T, 0)[lane] = (unsigned long long)c_me;
   }
   const int nodes = __popcll(__ballot(act && n_me > 0));
   if (counts_tree(P, k) && lane == 0) atomicAdd(&stat_bank(P, k)[0], (unsigned long long)nodes);
   if (nodes == 0) return;
   // V_curr = L_eta Psi before the update (Eq. 3).
   const double m = wave_max64(p_me);
-  const double vc = m + log(ordered_sum(act ? exp(eta * (p_me - m)) : 0.0, A)) / eta;
+  double upto = 0.0;
+  const double vc = m + log(ordered_sum(act ? exp(eta * (p_me - m)) : 0.0, A, upto)) / eta;
   // Psi <- Psi - V_curr + Q for the actions with an action node (Eq. 5).
   double p_new = p_me;
   if (act && n_me > 0) {
@@ -1647,24 +1979,18 @@ __device__ void dev_backup_root(const PlanView& P, int k) {
   }
   // V = L_eta Psi after the update, and the running sums of the root draw.
   const double m2 = wave_max64(act ? p_new : -INFINITY);
-  const double e2 = act ? exp(eta * (p_new - m2)) : 0.0;
-  double run = 0.0;
-  for (int j = 0; j < A; ++j) {
-    run = run + __shfl(e2, j, 64);
-    if (lane == 0) P.t.root_cdf[j] = run;
-  }
+  const double run = ordered_sum(act ? exp(eta * (p_new - m2)) : 0.0, A, upto);
+  if (act) T.root_cdf[lane] = upto;
   const long long nsum = (long long)wave_sum((unsigned long long)n_me);
   if (lane != 0) return;
   const double v = m2 + log(run) / eta;
-  P.t.v_root[0] = v;
-  BeliefHot* mt = rec_hot(P.t, 0);
-  mt->V = (float)v;
-  mt->Nb = (int)nsum;
+  T.v_root[0] = v;
+  T.node[0].V = (float)v;
+  T.info[0].Nb = (int)nsum;
 }
 
 // Alg. 1: argmax of the root preferences (lowest index on ties) and the
-// result record; also keeps this plan's list lengths for the next set-up.
-// Run by the block's first wavefront (64 lanes, one per stripe).
+// result record.  Run by the block's first wavefront (64 lanes, one per stripe).
 __device__ void dev_select(const PlanView& P) {
   static_assert(kStripes == 64, "one lane per stripe");
   if (threadIdx.x >= 64) return;
@@ -1709,21 +2035,7 @@ __device__ void dev_select(const PlanView& P) {
   out[A + 8] = (double)sw_i;
   out[A + 9] = (double)sw_n;
   // The allocation-free entry point's result holds |A| + 10 values.
-  if (!P.clear_all) out[A + 10] = (double)T.counters[4];
-  T.counters[2] = nb;
-  T.counters[3] = 0ull;
-  T.counters[5] = (unsigned long long)(P.timed ? T.step_base[k_last] : P.steps);
-  T.counters[6] = (unsigned long long)P.n_p;
-}
-
-__device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    unsigned long long n = __shfl_up(v, off, 64);
-    if (lane >= off) v += n;
-  }
-  return v;
+  if (!P.short_out) out[A + 10] = (double)T.counters[4];
 }
 
 // ---------------------------------------------------------------------------
@@ -1791,7 +2103,8 @@ __device__ void dev_pf_weight(const PlanView& P, int t, int blk) {
     const int s = ((const int*)P.f.part)[i];
     const int sn = tabular_next(P.m, s, a, x.y);
     ((int*)P.f.prop)[i] = sn;
-    const uint32_t* zr = P.m.thrZ + ((size_t)sn * P.m.nA + a) * P.m.nO;
+    const uint32_t* zr =
+        row_leaves(P.m.thrZ + ((size_t)sn * P.m.nA + a) * P.m.rZ.stride, P.m.rZ);
     wt = (unsigned long long)(zr[o] - (o > 0 ? zr[o - 1] : 0u));
   } else {
     const float* pf = (const float*)P.f.part;
@@ -1872,9 +2185,6 @@ __device__ void dev_pf_resample(const PlanView& P, int t, int blk) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Single-plan kernels (one launch per phase).
-// ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // Forward search for long action rows (|A| > kMaxA, tabular models): one
 // half wavefront per episode.  The episode's state is the same in every lane
@@ -1959,22 +2269,33 @@ __device__ int draw_long_cdf(const double* __restrict__ cdf, int A, uint32_t x0,
 constexpr int kLongChunks = kMaxAWide / (4 * kHalf);   // chunks of 128 actions
 
 // qs: this half's LDS area of kLongChunks * kHalf quad sums (single-precision
-// bits).  near: t lies within kTieRel * total of a boundary next to it (rows
+// bits).  Entry a1 of the row (a1 < 0: none) is p1 instead.  near: t lies within
+// kTieRel * total of a boundary next to it (rows
 // whose entries are all equal never count).
-__device__ int draw_long_row(const float* __restrict__ row, int A, float eta, uint32_t x0,
-                             int lane, uint32_t* qs, bool& near) {
+__device__ int draw_long_row(const float* __restrict__ row, int a1, float p1, int A, float eta,
+                             uint32_t x0, int lane, uint32_t* qs, bool& near) {
   // Lane l of the half holds the quads l, l + 32, ... (the row is padded to
   // a multiple of 4; padding is masked off).  Each weight is evaluated once:
   // the lane keeps its quad sum of every chunk (in LDS, for registers), the
   // half scans those once the total is known, and only the chosen quad is
   // evaluated again.
   const float4* r4 = reinterpret_cast<const float4*>(row);
+  auto read = [&](int q) {
+    float4 v = r4[q];
+    if (a1 >> 2 == q) {
+      if ((a1 & 3) == 0) v.x = p1;
+      if ((a1 & 3) == 1) v.y = p1;
+      if ((a1 & 3) == 2) v.z = p1;
+      if ((a1 & 3) == 3) v.w = p1;
+    }
+    return v;
+  };
   const int nq = (A + 3) / 4;
   const int nc = (nq + kHalf - 1) / kHalf;
   float m = -INFINITY, mn = INFINITY;
 #pragma unroll 4
   for (int q = lane; q < nq; q += kHalf) {
-    const float4 v = r4[q];
+    const float4 v = read(q);
     const int j = 4 * q;
     m = fmaxf(m, v.x);
     mn = fminf(mn, v.x);
@@ -1985,7 +2306,7 @@ __device__ int draw_long_row(const float* __restrict__ row, int A, float eta, ui
   m = half_maxf(m);
   const bool flat = -half_maxf(-mn) == m;
   auto quad = [&](int q, float (&w)[4]) {
-    const float4 v = r4[q];
+    const float4 v = read(q);
     const int j = 4 * q;
     w[0] = long_row_weight(v.x, m, eta);
     w[1] = j + 1 < A ? long_row_weight(v.y, m, eta) : 0.0f;
@@ -2038,142 +2359,265 @@ __device__ int draw_long_row(const float* __restrict__ row, int A, float eta, ui
   return A - 1;
 }
 
+// The rows of a long-row belief that becomes full, by the half (make_full):
+// Psi, the bitmap and the one action node it has; the other columns are
+// cleared by their first visit.
+__device__ __forceinline__ void make_full_wide(const PlanView& P, int id, uint32_t link, float r,
+                                               float psi, unsigned long long own, bool fresh,
+                                               int lane) {
+  const TreeView& T = P.t;
+  const int a = (link & kLinkAct) ? (int)((link & kLinkKey) >> P.m.obs_bits) : -1;
+  float4* q = reinterpret_cast<float4*>(rec_psi(T, id));
+  const float4* p0 = reinterpret_cast<const float4*>(T.psi0);
+  for (int i = lane; i < T.ra / 4; i += kHalf) {
+    float4 v = p0[i];
+    if (a >> 2 == i) {
+      if ((a & 3) == 0) v.x = psi;
+      if ((a & 3) == 1) v.y = psi;
+      if ((a & 3) == 2) v.z = psi;
+      if ((a & 3) == 3) v.w = psi;
+    }
+    q[i] = v;
+  }
+  uint32_t* bits = rec_bits(T, id);
+  for (int i = lane; i < T.bw; i += kHalf) bits[i] = a >> 5 == i ? 1u << (a & 31) : 0u;
+  if (lane == 0) {
+    const unsigned long long fx = to_fix(r, P.fix_scale);
+    if (a >= 0) {
+      rec_n(T, id)[a] = 1;
+      rec_c(T, id)[a] = fx;
+      rec_w(T, id)[a] = 0ull;
+    }
+    const bool leaf = fresh && a < 0;
+    if (!(link & kLinkHead)) T.info[id] = BeliefInfo{leaf ? 1 : 0, 1, own};
+    else if (leaf) atomicAdd(&T.info[id].leaf_cnt, 1);
+    if (a < 0) T.node[id].u.leaf_h = leaf ? fx : 0ull;
+  }
+}
+
+// search() on half a wavefront: the episode's state is the same in every lane.
+__device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episode& e0,
+                            uint32_t* qs, unsigned long long& g, unsigned long long& nt) {
+  const TreeView& T = P.t;
+  const int lane = threadIdx.x & (kHalf - 1);
+  const int t0 = first_step(P, k);
+  const int first_new = 1 + t0 * P.n_p;
+  const int A = P.m.nA, ob = P.m.obs_bits;
+  const size_t n_p = (size_t)P.n_p;
+  const unsigned long long stamp = (unsigned long long)(k - 1) << kStampShift;
+  int s = e0.s, id = 0, d = 0;
+  uint32_t link = 0;
+  float nr = 0.0f, npsi = 0.0f;
+  unsigned long long own = 0;
+  auto arrive = [&]() {
+    uint4 q;
+    if (id >= first_new) q = load_seen(&T.node[id]);
+    else q = *reinterpret_cast<const uint4*>(&T.node[id]);
+    link = q.y;
+    nr = __uint_as_float(q.z);
+    npsi = __uint_as_float(q.w);
+  };
+  bool tail = false;
+  uint32_t head = 0;
+  int tl = 0;
+  uint32_t slot = 0;
+  int id_head = 0, to_publish = 0, waits = 0;
+  bool alive = true;
+  // One level of the search.
+  auto level = [&]() {
+    const U4 w = draw(P, (uint32_t)ep, kTagStep, (uint32_t)d, (uint32_t)k);
+    bool tie = false;
+    int a;
+    if (id == 0) {
+      a = draw_long_cdf(T.root_cdf, A, w.x, lane);
+      tie = (k > 1 || P.carry) && near_tie64(T.root_cdf, A, w.x, a);
+    } else if (id >= first_new) {
+      a = draw_long_cdf(T.psi0_cdf64, A, w.x, lane);
+    } else {
+      const bool full = (link & kLinkFull) != 0;
+      const int a1 = !full && (link & kLinkAct) ? (int)((link & kLinkKey) >> ob) : -1;
+      a = draw_long_row(full ? rec_psi(T, id) : T.psi0, a1, npsi, A, P.eta, w.x, lane, qs, tie);
+    }
+    nt += tie ? 1u : 0u;
+    const int drawn = a;
+    const size_t di = (size_t)(t0 + d - P.carry_steps) * n_p + ep;
+    if (T.dbg_force) {
+      const short f = T.dbg_force[di];
+      if (f >= 0 && f < A) a = f;
+    }
+    int sn, obs;
+    float r;
+    tabular_step(P.m, s, a, w, sn, obs, r);
+    s = sn;
+    ++g;
+    if (T.dbg_act && lane == 0) {
+      T.dbg_act[di] = (short)drawn;
+      T.dbg_obs[di] = obs;
+    }
+    const uint32_t low = key_low(a, obs, ob);
+    if (tail) {
+      if (lane == 0)
+        store_seen(&T.node[id], 0u, low | kLinkAct | kLinkChild | head, __float_as_uint(r),
+                   __float_as_uint(T.psi0[a]));
+      if (to_publish) to_publish = 2;
+      id += P.n_p;
+      head = 0;
+      ++d;
+      return;
+    }
+    const int b = id;
+    const uint32_t blink = link;
+    const float b_r = nr, b_psi = npsi;
+    const unsigned long long b_own = own;
+    const unsigned long long bk = belief_key(b, low);
+    int first = 0;
+    if (lane == 0) first = claim(T, b, blink);
+    int won = 0, fresh = 0, old = -1;
+    uint32_t h = 0;
+    if ((blink & kLinkChild) && (blink & kLinkKey) == low) {
+      id = b + P.n_p;
+      own = bk;
+      if (b >= first_new) waits = 2;
+    } else {
+      // AppendBeliefs by lane 0 of the half; the outcome goes to the half.
+      if (lane == 0) {
+        Bucket line;
+        bucket_read(T, bk, line);
+        bool bw = false, bf = false;
+        h = probe(T, line, bk, stamp, bw, bf, old);
+        won = bw;
+        fresh = bf;
+      }
+      h = __shfl(h, 0, kHalf);
+      won = __shfl(won, 0, kHalf);
+      fresh = __shfl(fresh, 0, kHalf);
+      old = __shfl(old, 0, kHalf);
+      if (h == ~0u) {
+        if (lane == 0) atomicOr((unsigned int*)&T.counters[1], 2u);
+        alive = false;
+        tl = d + 1;
+      } else if (won) {
+        tail = true;
+        head = kLinkHead;
+        tl = d + 1;
+        id = 1 + (t0 + d) * P.n_p + ep;
+        id_head = id;
+        slot = h;
+        to_publish = 1;
+      } else if (fresh) {
+        slot = h;
+        waits = 1;
+      } else {
+        id = old;
+      }
+    }
+    if (alive && !tail && !waits) arrive();
+    first = __shfl(first, 0, kHalf);
+    if (lane == 0) {
+      // Every visit goes to the trace: the first visit of (b, a) clears its
+      // columns in the claim pass, before any count is added.
+      T.tr_key[(size_t)d * n_p + ep] = ((unsigned long long)(uint32_t)b << kActBits) |
+                                       (uint32_t)a | (first ? kTraceClaim : 0ull);
+      T.tr_val[(size_t)d * n_p + ep] = r;
+      if (won) store_seen(&T.info[id], bk);
+    }
+    if (first) make_full_wide(P, b, blink, b_r, b_psi, b_own, b >= first_new, lane);
+    if (alive) ++d;
+  };
+  // The end of the episode: its leaf, its run word.
+  auto finish = [&]() {
+    uint32_t run = (uint32_t)tl;
+    if (alive) {
+      const float hv = P.m.H ? P.m.H[s] : 0.0f;
+      const unsigned long long fx = to_fix(hv, P.fix_scale);
+      if (tail) {
+        if (lane == 0)
+          store_seen(&T.node[id], __float_as_uint(from_fix(fx, P.fix_inv)), head,
+                     __float_as_uint(hv), 0u);
+        run = (uint32_t)tl | (uint32_t)(D - tl + 1) << kRunLenShift;
+      } else {
+        run = (uint32_t)D;
+        int first = 0;
+        if (lane == 0) first = claim(T, id, link);
+        first = __shfl(first, 0, kHalf);
+        if (D >= kDirectLevel && (link & kLinkFull)) {
+          if (lane == 0) {
+            atomicAdd(&T.info[id].leaf_cnt, 1);
+            if (fx) atomicAdd(&T.node[id].u.leaf_h, fx);
+          }
+        } else {
+          run |= kRunLeaf;
+          if (lane == 0) {
+            T.tr_key[(size_t)D * n_p + ep] =
+                (unsigned long long)(uint32_t)id | (first ? kTraceClaim : 0ull);
+            T.tr_val[(size_t)D * n_p + ep] = hv;
+          }
+        }
+        if (first) make_full_wide(P, id, link, nr, npsi, own, id >= first_new, lane);
+      }
+    }
+    stores_done();
+    if (lane == 0) {
+      if (to_publish)
+        __hip_atomic_store(&T.h_slot[slot].id, id_head, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&T.run[(size_t)(k - 1) * n_p + ep], (unsigned short)run, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+    to_publish = 0;
+  };
+  // The loop ends for the whole wavefront at once, so that a lane that has ended
+  // has published its run before any lane of the wavefront waits again.
+  bool done = false;
+  do {
+    if (to_publish == 2) {
+      stores_done();
+      if (lane == 0)
+        __hip_atomic_store(&T.h_slot[slot].id, id_head, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      to_publish = 0;
+    }
+    if (!done) {
+      if (waits) {                                // every lane of the half reads the same
+        if (waits == 1) {
+          const int got = __shfl(__hip_atomic_load(&T.h_slot[slot].id, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT), 0, kHalf);
+          if (got >= 0) {
+            id = got;
+            waits = 0;
+          }
+        } else {
+          const int owner = (id - 1) % P.n_p;
+          if (__shfl((int)__hip_atomic_load(&T.run[(size_t)(k - 1) * n_p + owner],
+                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), 0, kHalf))
+            waits = 0;
+        }
+        if (!waits) arrive();
+        else if (__all(waits)) __builtin_amdgcn_s_sleep(1);
+      } else if (alive && d < D) {
+        level();
+      } else {
+        finish();
+        done = true;
+      }
+    }
+  } while (__ballot(!done));
+}
+
 // Four wavefronts per SIMD (128 registers, a few spilled): each episode is a
 // chain of dependent reads, so residency is what hides them.
 __global__ __launch_bounds__(kBlock, 4) void k_forward_wide(PlanView P, int k, int D) {
   __shared__ unsigned long long red[kBlock / 64];
   __shared__ uint32_t qsum[kBlock / kHalf][kLongChunks * kHalf];
   if (budget_spent(P)) return;
-  const TreeView& T = P.t;
   const int lane = threadIdx.x & (kHalf - 1);
   const int ep = blockIdx.x * (kBlock / kHalf) + (threadIdx.x / kHalf);   // uniform per half
-  const bool ep_ok = ep < P.n_p;
-  const int t0 = T.step_base[k - 1];
-  const int A = P.m.nA;
-  const size_t n_p = (size_t)P.n_p;
-  const unsigned long long stamp = (unsigned long long)(k - 1) << kStampShift;
-  int s = 0, sid = 0, rid = 0;
-  bool fresh = false, alive = false;
-  if (ep_ok) {
-    const U4 w = draw(P, (uint32_t)ep, kTagRoot, 0, (uint32_t)k);
-    const uint32_t idx = __umulhi(w.x, (uint32_t)P.e.n_belief);
-    s = ((const int*)P.e.belief)[idx];
-    if ((unsigned)s >= (unsigned)P.m.nS) {
-      if (lane == 0) atomicOr((unsigned int*)&T.counters[1], 1u);
-      s = 0;
-    }
-    alive = true;
-  }
   unsigned long long g = 0, nt = 0;
-  for (int d = 0; d < D; ++d) {
-    unsigned long long tk = kEmptyKey, link = kEmptyKey;
-    float r = 0.0f;
-    bool won = false;
-    int obs = 0, a = 0;
-    uint32_t h = 0;
-    const bool drew = alive;
-    int own = 0;
-    if (alive) {
-      const U4 w = draw(P, (uint32_t)ep, kTagStep, (uint32_t)d, (uint32_t)k);
-      bool tie = false;
-      if (sid == 0) {
-        a = draw_cdf64_bisect(T.root_cdf, A, w.x);
-        tie = (k > 1 || P.carry) && near_tie64(T.root_cdf, A, w.x, a);
-      } else if (fresh) {
-        a = draw_long_cdf(T.psi0_cdf64, A, w.x, lane);
-      } else {
-        a = draw_long_row(rec_psi(T, rid), A, P.eta, w.x, lane, qsum[threadIdx.x / kHalf], tie);
-      }
-      nt += tie ? 1u : 0u;
-      own = a;
-      if (T.dbg_force) {
-        const short f = T.dbg_force[(size_t)(t0 + d - T.dbg_step0) * n_p + ep];
-        if (f >= 0 && f < A) a = f;
-      }
-      int sn;
-      tabular_step(P.m, s, a, w, sn, obs, r);
-      s = sn;
-      ++g;
-      // Every visit goes to the trace: the first visit of (b, a) clears its
-      // columns in the claim pass, before any count is added.
-      tk = rid >= 0 ? (((unsigned long long)(uint32_t)rid << kActBits) | (uint32_t)a | kTraceRec)
-                    : (((unsigned long long)(uint32_t)sid << kActBits) | (uint32_t)a);
-      link = rid >= 0 ? (((unsigned long long)(uint32_t)rid << kActBits) | (uint32_t)a)
-                      : (kLinkSlot | ((unsigned long long)(uint32_t)sid << kActBits) | (uint32_t)a);
-      // AppendBeliefs by lane 0 of the half; the outcome goes to the half.
-      int fr = 0, id = -1, wn = 0;
-      if (lane == 0) {
-        bool b_won = false, b_fr = false;
-        h = probe(T, belief_key(sid, a, obs, P.m.obs_bits), stamp, b_won, b_fr, id);
-        wn = b_won;
-        fr = b_fr;
-      }
-      h = __shfl(h, 0, kHalf);
-      wn = __shfl(wn, 0, kHalf);
-      fr = __shfl(fr, 0, kHalf);
-      id = __shfl(id, 0, kHalf);
-      won = wn != 0;
-      if (h == ~0u) {
-        if (lane == 0) atomicOr((unsigned int*)&T.counters[1], 2u);
-        alive = false;
-      } else {
-        sid = (int)h + 1;
-        fresh = fr != 0;
-        rid = won ? 1 + (t0 + d) * P.n_p + ep : id;
-      }
-    }
-    if (ep_ok) {
-      if (lane == 0) {
-        const int t = t0 + d;
-        T.tr_key[(size_t)d * n_p + ep] = tk;
-        T.tr_val[(size_t)d * n_p + ep] = r;
-        T.list[(size_t)t * n_p + ep] = won ? sid : 0;
-        if (won) T.h_slot[h].id = rid;
-        if (T.dbg_act) {
-          const size_t i = (size_t)(t - T.dbg_step0) * n_p + ep;
-          T.dbg_act[i] = drew ? (short)own : (short)-1;
-          T.dbg_obs[i] = drew ? obs : -1;
-        }
-      }
-      if (won) {                                // the new record, by the half
-        // Psi, the metadata and a cleared bitmap; N, C and W of (b, a) are
-        // cleared by its first visit.
-        uint4* q = reinterpret_cast<uint4*>(rec_psi(T, rid));
-        const uint4* p0 = reinterpret_cast<const uint4*>(T.psi0);
-        const int nq = T.ra / 4, nbq = rec_bitmap_quads(T.ra);
-        for (int i = lane; i < nq; i += kHalf) q[i] = p0[i];
-        if (lane == 0) {
-          *rec_hot(T, rid) = BeliefHot{0.0f, 0, link};
-          *rec_leaf(T, rid) = BeliefLeaf{0, obs, 0ull};
-        }
-        uint4* bq = reinterpret_cast<uint4*>(rec_bits(T, rid));
-        for (int i = lane; i < nbq; i += kHalf) bq[i] = make_uint4(0u, 0u, 0u, 0u);
-      }
-    }
+  if (ep < P.n_p) {
+    const Episode e = at_root(P, k, ep, lane == 0);
+    search_wide(P, k, D, ep, e, qsum[threadIdx.x / kHalf], g, nt);
   }
-  if (ep_ok && lane == 0) {
-    unsigned long long tk = kEmptyKey;
-    float hv = 0.0f;
-    if (alive) {
-      if (P.m.H) hv = P.m.H[s];
-      if (D >= kDirectLevel && rid >= 0) {
-        BeliefLeaf* lf = rec_leaf(T, rid);
-        atomicAdd(&lf->leaf_cnt, 1);
-        const unsigned long long fx = to_fix(hv, P.fix_scale);
-        if (fx) atomicAdd(&lf->leaf_h, fx);
-      } else {
-        tk = rid >= 0 ? ((unsigned long long)(uint32_t)rid | kTraceRec)
-                      : (unsigned long long)(uint32_t)sid;
-      }
-    }
-    T.tr_key[(size_t)D * n_p + ep] = tk;
-    T.tr_val[(size_t)D * n_p + ep] = hv;
-  }
-  g = block_sum(lane == 0 ? (g | (nt << 32)) : 0ull, red);
-  if (threadIdx.x == 0 && (g & 0xffffffffull))
-    atomicAdd(&T.stats[blockIdx.x % kStripes], g & 0xffffffffull);
-  if (threadIdx.x == 0 && (g >> 32))
-    atomicAdd(&T.stats[kStatNear * kStripes + blockIdx.x % kStripes], g >> 32);
+  tally(P.t, blockIdx.x, lane == 0 ? g : 0ull, lane == 0 ? nt : 0ull, red);
 }
 
 __global__ void k_env(PlanView P, int t) { dev_env(P, t); }
@@ -2193,17 +2637,27 @@ __global__ __launch_bounds__(kBlock) void k_setup(PlanView P) {
 }
 // The phases of one iteration return at once when a time budget ran out
 // at the end of an earlier iteration.
-template <int AM>
+template <int AM, bool NAV, bool TRACE>
 __global__ __launch_bounds__(kBlock) void k_forward(PlanView P, int k, int D) {
-  __shared__ unsigned long long red[kBlock / 64];
-  __shared__ float psi0s[kMaxA];
+  __shared__ SearchSmem L;
   if (budget_spent(P)) return;
-  dev_forward<AM>(P, k, D, blockIdx.x, red, psi0s);
+  dev_forward<AM, NAV, TRACE>(P, k, D, blockIdx.x, L);
 }
-__global__ __launch_bounds__(kBlock) void k_accum(PlanView P, int D) {
+__global__ __launch_bounds__(kBlock) void k_accum(PlanView P, int k, int D) {
   __shared__ Smem sm;
   if (budget_spent(P)) return;
-  dev_accum(P, D, blockIdx.x, gridDim.x, sm);
+  dev_accum(P, k, D, blockIdx.x, gridDim.x, sm);
+}
+template <int AM>
+__global__ __launch_bounds__(kBlock) void k_fold(PlanView P, int k) {
+  __shared__ Smem sm;
+  if (budget_spent(P)) return;
+  dev_fold<AM>(P, k, blockIdx.x, gridDim.x, sm);
+}
+template <int QPL>
+__global__ __launch_bounds__(kBlock) void k_chain_wide(PlanView P, int k) {
+  if (budget_spent(P)) return;
+  dev_chain_wide<QPL>(P, k, blockIdx.x, gridDim.x);
 }
 __global__ __launch_bounds__(kBlock) void k_backup_leaf(PlanView P, int dep, int k) {
   __shared__ Smem sm;
@@ -2211,14 +2665,10 @@ __global__ __launch_bounds__(kBlock) void k_backup_leaf(PlanView P, int dep, int
   dev_backup_leaf(P, dep, k, blockIdx.x, gridDim.x, sm);
 }
 template <int AM>
-__global__ __launch_bounds__(kBlock) void k_backup_level(PlanView P, int dep, int k) {
+__global__ __launch_bounds__(kBlock) void k_full(PlanView P, int k) {
   __shared__ Smem sm;
   if (budget_spent(P)) return;
-  dev_backup_level<AM>(P, dep, k, blockIdx.x, gridDim.x, sm);
-}
-__global__ void k_backup_root(PlanView P, int k) {
-  if (budget_spent(P)) return;
-  dev_backup_root(P, k);
+  dev_full<AM>(P, k, blockIdx.x, sm);
 }
 template <int QPL>
 __global__ __launch_bounds__(kBlock) void k_backup_level_wide(PlanView P, int dep, int k) {
@@ -2237,38 +2687,50 @@ __global__ void k_select(PlanView P) { dev_select(P); }
 // Batched kernel: block -> (instance, phase) through the item list, sorted by
 // first block.  AMAX bounds the padded action count of the batch.
 // ---------------------------------------------------------------------------
+// A block runs one phase at a time.
+union BatchSmem {
+  Smem sm;
+  SearchSmem search;
+};
+
+// The phases whose code depends on the row length, for AM >= |A|.
+template <int AM>
+__device__ __forceinline__ void run_rows(const PlanView& P, const BatchItem& it, int blk,
+                                         BatchSmem& bs) {
+  Smem& sm = bs.sm;
+  SearchSmem& L = bs.search;
+  const int k = it.a0;
+  switch (it.kind) {
+    case kPhaseForward:
+      if (AM == 4 && P.m.kind == kNav) dev_forward<AM, true, false>(P, k, depth_at(P, k), blk, L);
+      else dev_forward<AM, false, false>(P, k, depth_at(P, k), blk, L);
+      break;
+    case kPhaseFold: dev_fold<AM>(P, k, blk, it.nblk, sm); break;
+    case kPhaseFull: dev_full<AM>(P, k, blk, sm); break;
+    default: break;
+  }
+}
 // One phase item of one instance, as block blk of its nblk (LDS in sm).
 template <int AMAX>
 __device__ __forceinline__ void run_item(const PlanView& P, const BatchItem& it, int blk,
-                                         Smem& sm) {
+                                         BatchSmem& bs) {
+  Smem& sm = bs.sm;
   const int Apad = P.m.Apad;
   switch (it.kind) {
     case kPhaseSetup: dev_setup(P, blk, it.nblk, nullptr); break;   // |A| <= 16
-    case kPhaseForward:
-      if (Apad <= 4) {
-        dev_forward_inorder<4>(P, it.a0, it.a1, blk, sm.wave, sm.psi0);
-      } else if constexpr (AMAX >= 8) {
-        if (Apad <= 8) dev_forward_inorder<8>(P, it.a0, it.a1, blk, sm.wave, sm.psi0);
-        else if constexpr (AMAX >= 16) dev_forward_inorder<16>(P, it.a0, it.a1, blk, sm.wave, sm.psi0);
-      }
-      break;
-    case kPhaseAccum: dev_accum(P, it.a0, blk, it.nblk, sm); break;
-    case kPhaseLeaf: dev_backup_leaf(P, it.a0, it.a1, blk, it.nblk, sm); break;
-    case kPhaseLevel:
-      if (Apad <= 4) {
-        dev_backup_level<4>(P, it.a0, it.a1, blk, it.nblk, sm);
-      } else if constexpr (AMAX >= 8) {
-        if (Apad <= 8) dev_backup_level<8>(P, it.a0, it.a1, blk, it.nblk, sm);
-        else if constexpr (AMAX >= 16) dev_backup_level<16>(P, it.a0, it.a1, blk, it.nblk, sm);
-      }
-      break;
-    case kPhaseRoot: dev_backup_root(P, it.a0); break;
     case kPhaseSelect: dev_select(P); break;
     case kPhaseEnv: dev_env(P, it.a0); break;
     case kPhasePFWeight: dev_pf_weight(P, it.a0, blk); break;
     case kPhasePFScan: dev_pf_scan(P, sm); break;
     case kPhasePFResample: dev_pf_resample(P, it.a0, blk); break;
-    default: break;
+    default:
+      if (Apad <= 4) {
+        run_rows<4>(P, it, blk, bs);
+      } else if constexpr (AMAX >= 8) {
+        if (Apad <= 8) run_rows<8>(P, it, blk, bs);
+        else if constexpr (AMAX >= 16) run_rows<16>(P, it, blk, bs);
+      }
+      break;
   }
 }
 
@@ -2276,7 +2738,7 @@ template <int AMAX>
 __global__ __launch_bounds__(kBlock) void k_batch(const PlanView* __restrict__ views,
                                                   const BatchItem* __restrict__ items,
                                                   int n_items) {
-  __shared__ Smem sm;
+  __shared__ BatchSmem sm;
   const int g = blockIdx.x;
   int lo = 0, hi = n_items - 1;
   while (lo < hi) {
@@ -2312,7 +2774,7 @@ __global__ void k_persist_reset(PersistView V) {
 template <int AMAX>
 __global__ __launch_bounds__(kBlock) void k_batch_persistent(const PlanView* __restrict__ views,
                                                              PersistView V) {
-  __shared__ Smem sm;
+  __shared__ BatchSmem sm;
   __shared__ int take[3];
   int cur = (int)(blockIdx.x % (unsigned)V.n);
   for (;;) {
@@ -2444,54 +2906,84 @@ hipError_t launch_setup(const PlanView& P, hipStream_t s) {
   plan_launch(k_setup, dim3(setup_blocks(P)), dim3(kBlock), 0, s, P);
   return hipGetLastError();
 }
-hipError_t launch_forward(const PlanView& P, int k, int D, hipStream_t s) {
+// Calls F<AM>'s launch for the smallest AM that holds the rows.
+#define VOPP_BY_ROW(F, g, b, s, ...)                                            \
+  do {                                                                         \
+    const int Ap_ = P.m.Apad;                                                  \
+    if (Ap_ <= 4) plan_launch(F<4>, g, b, 0, s, __VA_ARGS__);                  \
+    else if (Ap_ <= 8) plan_launch(F<8>, g, b, 0, s, __VA_ARGS__);             \
+    else if (Ap_ <= 16) plan_launch(F<16>, g, b, 0, s, __VA_ARGS__);           \
+    else if (Ap_ <= 32) plan_launch(F<32>, g, b, 0, s, __VA_ARGS__);           \
+    else plan_launch(F<kMaxA>, g, b, 0, s, __VA_ARGS__);                       \
+  } while (0)
+// The same for long rows, by quads per lane: rows of up to 1024, 2048, 3072,
+// 4096 actions.
+#define VOPP_BY_LONG_ROW(F, g, b, s, ...)                                       \
+  do {                                                                         \
+    const int qpl_ = (P.m.Apad / 4 + 63) / 64;                                 \
+    if (qpl_ <= 4) plan_launch(F<4>, g, b, 0, s, __VA_ARGS__);                 \
+    else if (qpl_ <= 8) plan_launch(F<8>, g, b, 0, s, __VA_ARGS__);            \
+    else if (qpl_ <= 12) plan_launch(F<12>, g, b, 0, s, __VA_ARGS__);          \
+    else plan_launch(F<16>, g, b, 0, s, __VA_ARGS__);                          \
+  } while (0)
+
+static dim3 wide_grid(const PlanView& P) {
+  return dim3((P.n_p + kBlock / kHalf - 1) / (kBlock / kHalf));
+}
+template <bool TRACE>
+static void launch_forward_rows(const PlanView& P, int k, int D, hipStream_t s) {
   const dim3 g(forward_blocks(P)), b(kBlock);
   const int Ap = P.m.Apad;
-  if (Ap <= 4) plan_launch(k_forward<4>, g, b, 0, s, P, k, D);
-  else if (Ap <= 8) plan_launch(k_forward<8>, g, b, 0, s, P, k, D);
-  else if (Ap <= 16) plan_launch(k_forward<16>, g, b, 0, s, P, k, D);
-  else if (Ap <= 32) plan_launch(k_forward<32>, g, b, 0, s, P, k, D);
-  else if (Ap <= kMaxA) plan_launch(k_forward<64>, g, b, 0, s, P, k, D);
-  else
-    plan_launch(k_forward_wide, dim3((P.n_p + kBlock / kHalf - 1) / (kBlock / kHalf)), b, 0, s,
-                P, k, D);
+  if (P.m.kind == kNav) plan_launch(k_forward<4, true, TRACE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 4) plan_launch(k_forward<4, false, TRACE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 8) plan_launch(k_forward<8, false, TRACE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 16) plan_launch(k_forward<16, false, TRACE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 32) plan_launch(k_forward<32, false, TRACE>, g, b, 0, s, P, k, D);
+  else plan_launch(k_forward<kMaxA, false, TRACE>, g, b, 0, s, P, k, D);
+}
+hipError_t launch_forward(const PlanView& P, int k, hipStream_t s) {
+  const int D = depth_at(P, k);
+  const dim3 b(kBlock);
+  if (P.m.Apad > kMaxA) plan_launch(k_forward_wide, wide_grid(P), b, 0, s, P, k, D);
+  else if (P.t.dbg_act) launch_forward_rows<true>(P, k, D, s);
+  else launch_forward_rows<false>(P, k, D, s);
   return hipGetLastError();
 }
-hipError_t launch_accum(const PlanView& P, int D, int grid, hipStream_t s) {
-  if (P.t.ra > kMaxA) {
-    plan_launch(k_claim_wide, dim3(blocks_for(std::min((long long)D * P.n_p, 1ll << 24))),
-                dim3(kBlock), 0, s, P, D);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  plan_launch(k_accum, dim3(grid), dim3(kBlock), 0, s, P, D);
+hipError_t launch_accum(const PlanView& P, int k, int grid, hipStream_t s) {
+  const int D = depth_at(P, k);
+  plan_launch(k_claim_wide, dim3(blocks_for(std::min((long long)D * P.n_p, 1ll << 24))),
+              dim3(kBlock), 0, s, P, k, D);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  plan_launch(k_accum, dim3(grid), dim3(kBlock), 0, s, P, k, D);
+  return hipGetLastError();
+}
+hipError_t launch_fold(const PlanView& P, int k, int grid, hipStream_t s) {
+  const dim3 g(grid), b(kBlock);
+  VOPP_BY_ROW(k_fold, g, b, s, P, k);
+  return hipGetLastError();
+}
+hipError_t launch_chain(const PlanView& P, int k, int grid, hipStream_t s) {
+  const dim3 g(grid), b(kBlock);
+  VOPP_BY_LONG_ROW(k_chain_wide, g, b, s, P, k);
   return hipGetLastError();
 }
 hipError_t launch_backup_leaf(const PlanView& P, int dep, int k, int grid, hipStream_t s) {
   plan_launch(k_backup_leaf, dim3(grid), dim3(kBlock), 0, s, P, dep, k);
   return hipGetLastError();
 }
+hipError_t launch_full(const PlanView& P, int k, int grid, hipStream_t s) {
+  const dim3 g(grid), b(kBlock);
+  VOPP_BY_ROW(k_full, g, b, s, P, k);
+  return hipGetLastError();
+}
 hipError_t launch_backup_level(const PlanView& P, int dep, int k, int grid, hipStream_t s) {
   const dim3 g(grid), b(kBlock);
-  const int Ap = P.m.Apad;
-  if (Ap <= 4) plan_launch(k_backup_level<4>, g, b, 0, s, P, dep, k);
-  else if (Ap <= 8) plan_launch(k_backup_level<8>, g, b, 0, s, P, dep, k);
-  else if (Ap <= 16) plan_launch(k_backup_level<16>, g, b, 0, s, P, dep, k);
-  else if (Ap <= 32) plan_launch(k_backup_level<32>, g, b, 0, s, P, dep, k);
-  else if (Ap <= kMaxA) plan_launch(k_backup_level<64>, g, b, 0, s, P, dep, k);
-  else {
-    // Quads of the row per lane: rows of up to 1024, 2048, 3072, 4096 actions.
-    const int qpl = (Ap / 4 + 63) / 64;
-    if (qpl <= 4) plan_launch(k_backup_level_wide<4>, g, b, 0, s, P, dep, k);
-    else if (qpl <= 8) plan_launch(k_backup_level_wide<8>, g, b, 0, s, P, dep, k);
-    else if (qpl <= 12) plan_launch(k_backup_level_wide<12>, g, b, 0, s, P, dep, k);
-    else plan_launch(k_backup_level_wide<16>, g, b, 0, s, P, dep, k);
-  }
+  VOPP_BY_LONG_ROW(k_backup_level_wide, g, b, s, P, dep, k);
   return hipGetLastError();
 }
 hipError_t launch_backup_root(const PlanView& P, int k, hipStream_t s) {
-  if (P.m.Apad > kMaxA) plan_launch(k_backup_root_wide, dim3(1), dim3(kBlock), 0, s, P, k);
-  else plan_launch(k_backup_root, dim3(1), dim3(64), 0, s, P, k);
+  plan_launch(k_backup_root_wide, dim3(1), dim3(kBlock), 0, s, P, k);
   return hipGetLastError();
 }
 hipError_t launch_select(const PlanView& P, hipStream_t s) {
@@ -2514,40 +3006,69 @@ hipError_t launch_pf(const PlanView& P, int t, hipStream_t s) {
   for (int part = 0; part < 3 && e == hipSuccess; ++part) e = launch_pf_part(P, part, t, s);
   return e;
 }
+// The parent and key of belief id in a finished plan's tree (link: its
+// record's): inside a run, the belief before it.
+__device__ __forceinline__ unsigned long long own_of(const TreeView& t, int id, uint32_t link,
+                                                     int n_p) {
+  if (link & (kLinkHead | kLinkClaim | kLinkFull)) return t.info[id].own;
+  const int par = id - n_p;
+  return ((unsigned long long)(uint32_t)par << kKeyLowBits) | (t.node[par].link & kLinkKey);
+}
+// Action and N, C of the action node of a single-visit belief.
+struct OneNode {
+  int a, n;                  // a = -1: none
+  unsigned long long c;
+  float psi;
+};
+__device__ __forceinline__ OneNode one_node(const BeliefNode& b, int ob, float scale) {
+  OneNode o{-1, 0, 0ull, 0.0f};
+  if (b.link & kLinkAct) {
+    o.a = (int)((b.link & kLinkKey) >> ob);
+    o.n = 1;
+    o.c = to_fix(b.u.one.r, scale);
+    o.psi = b.u.one.psi;
+  }
+  return o;
+}
+
 // The tree dump: belief ids[i]'s fields packed at out + i * dump_bytes(ra)
 // (layout in vopp_device.hpp), one thread per belief.
-__global__ __launch_bounds__(kBlock) void k_gather(TreeView t, const int* ids, int n,
-                                                   unsigned char* out) {
+__global__ __launch_bounds__(kBlock) void k_gather(TreeView t, int n_p, int ob, float scale,
+                                                   const int* ids, int n, unsigned char* out) {
   const int ra = t.ra;
   const size_t db = (size_t)dump_bytes(ra);
   for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n;
        i += (long long)gridDim.x * kBlock) {
     const int id = ids[i];
+    const BeliefNode b = t.node[id];
+    const bool full = (b.link & kLinkFull) != 0;
+    const OneNode one = one_node(b, ob, scale);
     unsigned char* o = out + (size_t)i * db;
     float* po = reinterpret_cast<float*>(o);
     int* no = reinterpret_cast<int*>(o + dump_n_off(ra));
     unsigned long long* co = reinterpret_cast<unsigned long long*>(o + dump_c_off(ra));
     for (int j = 0; j < ra; ++j) {
-      po[j] = rec_psi(t, id)[j];
-      no[j] = rec_n(t, id)[j];
-      co[j] = rec_c(t, id)[j];
+      po[j] = full ? rec_psi(t, id)[j] : j == one.a ? one.psi : t.psi0[j];
+      no[j] = full ? rec_n(t, id)[j] : j == one.a ? one.n : 0;
+      co[j] = full ? rec_c(t, id)[j] : j == one.a ? one.c : 0ull;
     }
-    const BeliefHot h = *rec_hot(t, id);
-    const BeliefLeaf l = *rec_leaf(t, id);
+    const unsigned long long own = id == 0 ? kEmptyKey : own_of(t, id, b.link, n_p);
     unsigned char* tl = o + dump_tail_off(ra);
-    *reinterpret_cast<float*>(tl) = h.V;
-    *reinterpret_cast<int*>(tl + 4) = h.Nb;
-    *reinterpret_cast<int*>(tl + 8) = l.obs;
+    *reinterpret_cast<float*>(tl) = b.V;
+    *reinterpret_cast<int*>(tl + 4) = full ? t.info[id].Nb : 1;
+    *reinterpret_cast<int*>(tl + 8) = (int)(own & ((1ull << ob) - 1));
     *reinterpret_cast<int*>(tl + 12) = 0;
-    *reinterpret_cast<unsigned long long*>(tl + 16) = h.parent;
+    *reinterpret_cast<unsigned long long*>(tl + 16) =
+        id == 0 ? kEmptyKey : parent_of(own, ob);
     uint32_t* bo = reinterpret_cast<uint32_t*>(o + dump_bits_off(ra));
-    for (int j = 0; j < t.bw; ++j) bo[j] = rec_bits(t, id)[j];
+    for (int j = 0; j < t.bw; ++j)
+      bo[j] = full ? rec_bits(t, id)[j] : one.a >> 5 == j ? 1u << (one.a & 31) : 0u;
   }
 }
-hipError_t launch_gather(const TreeView& t, const int* ids, int n, unsigned char* out,
-                         hipStream_t s) {
+hipError_t launch_gather(const TreeView& t, int n_p, int ob, float scale, const int* ids, int n,
+                         unsigned char* out, hipStream_t s) {
   const int g = (int)std::max(1ll, std::min(((long long)n + kBlock - 1) / kBlock, 4096ll));
-  hipLaunchKernelGGL(k_gather, dim3(g), dim3(kBlock), 0, s, t, ids, n, out);
+  hipLaunchKernelGGL(k_gather, dim3(g), dim3(kBlock), 0, s, t, n_p, ob, scale, ids, n, out);
   return hipGetLastError();
 }
 // ---------------------------------------------------------------------------
@@ -2559,21 +3080,21 @@ hipError_t launch_gather(const TreeView& t, const int* ids, int n, unsigned char
 // ---------------------------------------------------------------------------
 
 // Slot of `key` (any stamp) in a table no kernel is inserting into, or ~0u.
-// An insert takes the first empty-or-matching slot of the key's line in the
-// key's rotated order and moves to the next line only when the line is full,
+// An insert takes the first empty-or-matching slot of the key's bucket in the
+// key's rotated order and moves to the next bucket only when it is full,
 // and slots are never emptied during a plan, so the first such slot decides.
 __device__ uint32_t find_slot(const TreeView& t, unsigned long long key) {
   const unsigned long long hk = mix64(key);
-  uint32_t base = (uint32_t)hk & t.h_mask & ~7u;
-  const uint32_t rot = (uint32_t)(hk >> 40) & 7u;
-  const uint32_t lines = (t.h_mask >> 3) + 1;
+  uint32_t base = (uint32_t)hk & t.h_mask & ~(kBucket - 1);
+  const uint32_t rot = (uint32_t)(hk >> 40) & (kBucket - 1);
+  const uint32_t lines = (t.h_mask + 1) / kBucket;
   for (uint32_t n = 0; n < lines; ++n) {
-    uint32_t best = 8;
+    uint32_t best = kBucket;
     int at = -1;
     bool empty = false;
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < (int)kBucket; ++j) {
       const unsigned long long cur = t.h_slot[base + j].key;
-      const uint32_t pos = ((uint32_t)j - rot) & 7u;
+      const uint32_t pos = ((uint32_t)j - rot) & (kBucket - 1);
       if ((cur == kEmptyKey || (cur & ~kStampMask) == key) && pos < best) {
         best = pos;
         at = j;
@@ -2581,32 +3102,30 @@ __device__ uint32_t find_slot(const TreeView& t, unsigned long long key) {
       }
     }
     if (at >= 0) return empty ? ~0u : base + (uint32_t)at;
-    base = (base + 8u) & t.h_mask;
+    base = (base + kBucket) & t.h_mask;
   }
   return ~0u;
 }
 
 __global__ void k_reroot_find(TreeView t, int a, int obs, int ob, int* out) {
   if (threadIdx.x != 0) return;
-  const uint32_t h = find_slot(t, belief_key(0, a, obs, ob));
+  const uint32_t h = find_slot(t, belief_key(0, key_low(a, obs, ob)));
   out[0] = h == ~0u ? -1 : t.h_slot[h].id;
 }
 
-// Source record of position i of the launch's level steps, or -1.
+// Source belief of position i of the launch's level steps, or -1.
 __device__ __forceinline__ int reroot_record(const RerootView& V, long long i) {
-  const int s = V.steps[i / V.src_n_p];
-  const size_t pos = (size_t)s * (size_t)V.src_n_p + (size_t)(i % V.src_n_p);
-  return V.src.list[pos] ? (int)(1 + pos) : -1;
-}
-
-// The parent link (record << kActBits | action) of a source record, resolved.
-__device__ __forceinline__ unsigned long long reroot_parent(const TreeView& T, int r) {
-  unsigned long long par = rec_hot(T, r)->parent;
-  if (par != kEmptyKey && (par & kLinkSlot)) {
-    const int psid = (int)((par & ~kLinkSlot) >> kActBits);
-    par = ((unsigned long long)(uint32_t)record_of(T, psid) << kActBits) | (par & kActMask);
+  const RerootStep st = V.steps[i / V.src_n_p];
+  const int ep = (int)(i % V.src_n_p);
+  bool there;
+  if (st.iter < 0) {                          // a kept subtree's step: packed
+    there = ep < st.n;
+  } else {
+    const uint32_t run = V.src.run[(size_t)st.iter * (size_t)V.src_n_p + ep];
+    const int top = (int)(run & kRunMask) - 1;
+    there = st.level >= top && st.level < top + (int)((run >> kRunLenShift) & kRunMask);
   }
-  return par;
+  return there ? (int)(1 + (size_t)st.step * (size_t)V.src_n_p + (size_t)ep) : -1;
 }
 
 // Mark pass: kept[r] for the beliefs of one source depth, with counts of the
@@ -2621,16 +3140,17 @@ __global__ __launch_bounds__(kBlock) void k_reroot_mark(RerootView V) {
       if (V.src_depth == 1) {
         keep = r == V.root_rec;
       } else {
-        const unsigned long long par = reroot_parent(V.src, r);
-        keep = par != kEmptyKey && V.kept[par >> kActBits] != 0;
+        keep = V.kept[own_of(V.src, r, V.src.node[r].link, V.src_n_p) >> kKeyLowBits] != 0;
       }
       if (keep) {
         V.kept[r] = 1;
         nb = 1;
+        const uint32_t link = V.src.node[r].link;
         const int* n = rec_n(V.src, r);
         const uint32_t* bits = rec_bits(V.src, r);
         const bool wide = V.src.ra > kMaxA;   // long rows: columns valid per bitmap
-        for (int j = 0; j < V.A; ++j) {
+        if (!(link & kLinkFull)) nn = nv = (link & kLinkAct) ? 1ull : 0ull;
+        for (int j = 0; (link & kLinkFull) && j < V.A; ++j) {
           const int c = (!wide || ((bits[j >> 5] >> (j & 31)) & 1u)) ? n[j] : 0;
           nn += c > 0 ? 1ull : 0ull;
           nv += (unsigned long long)(c > 0 ? c : 0);
@@ -2665,52 +3185,50 @@ __global__ __launch_bounds__(kBlock) void k_reroot_copy(RerootView V) {
     nr = (int)(1 + t * V.dst_n_p + (long long)(q % (unsigned long long)V.dst_n_p));
   }
   V.new_id[r] = nr;
-  {                                           // every field of the belief
-    const int ra = V.src.ra;
-    for (int j = 0; j < ra; ++j) {
-      rec_psi(V.dst, nr)[j] = rec_psi(V.src, r)[j];
-      rec_n(V.dst, nr)[j] = rec_n(V.src, r)[j];
-      rec_c(V.dst, nr)[j] = rec_c(V.src, r)[j];
-      rec_w(V.dst, nr)[j] = rec_w(V.src, r)[j];
-    }
-    for (int j = 0; j < V.src.bw; ++j) rec_bits(V.dst, nr)[j] = rec_bits(V.src, r)[j];
-    *rec_hot(V.dst, nr) = *rec_hot(V.src, r);
-    *rec_leaf(V.dst, nr) = *rec_leaf(V.src, r);
-  }
+  const BeliefNode b = V.src.node[r];
+  const bool full = (b.link & kLinkFull) != 0;
+  const OneNode one = one_node(b, V.obs_bits, V.src_scale);
+  const int ra = V.src.ra;
+  const bool wide = ra > kMaxA;             // long rows: columns valid per bitmap
+  for (int j = 0; j < V.src.bw; ++j)
+    rec_bits(V.dst, nr)[j] =
+        full ? rec_bits(V.src, r)[j] : one.a >> 5 == j ? 1u << (one.a & 31) : 0u;
   unsigned long long* c = rec_c(V.dst, nr);
   unsigned long long* w = rec_w(V.dst, nr);
-  const uint32_t* bits = rec_bits(V.dst, nr);
-  const bool wide = V.dst.ra > kMaxA;       // long rows: columns valid per bitmap
-  for (int j = 0; j < V.dst.ra; ++j) {
-    if (wide && !((bits[j >> 5] >> (j & 31)) & 1u)) continue;
-    if (V.rescale != 1.0 && c[j])
-      c[j] = (unsigned long long)llrint((double)(long long)c[j] * V.rescale);
+  for (int j = 0; j < ra; ++j) {
+    rec_psi(V.dst, nr)[j] = full ? rec_psi(V.src, r)[j] : j == one.a ? one.psi : V.src.psi0[j];
+    if (wide && !((rec_bits(V.dst, nr)[j >> 5] >> (j & 31)) & 1u)) continue;
+    rec_n(V.dst, nr)[j] = full ? rec_n(V.src, r)[j] : j == one.a ? one.n : 0;
+    unsigned long long cj = full ? rec_c(V.src, r)[j] : j == one.a ? one.c : 0ull;
+    if (V.rescale != 1.0 && cj)
+      cj = (unsigned long long)llrint((double)(long long)cj * V.rescale);
+    c[j] = cj;
     w[j] = 0ull;
   }
-  BeliefHot* mt = rec_hot(V.dst, nr);
-  BeliefLeaf* lf = rec_leaf(V.dst, nr);
-  lf->leaf_cnt = 0;
-  lf->leaf_h = 0ull;
+  BeliefNode nb;
+  nb.V = b.V;
+  nb.link = kLinkFull;
+  nb.u.leaf_h = 0ull;
+  V.dst.node[nr] = nb;
+  const int Nb = full ? V.src.info[r].Nb : 1;
   if (d_new == 0) {
-    lf->obs = -1;
-    mt->parent = kEmptyKey;
+    V.dst.info[nr] = BeliefInfo{0, Nb, kEmptyKey};
     return;
   }
-  const unsigned long long par = reroot_parent(V.src, r);
-  const int a_par = (int)(par & kActMask);
-  const int np = V.new_id[(int)(par >> kActBits)];
-  const int psid = np == 0 ? 0 : V.dst.list[np - 1];
-  const unsigned long long key = belief_key(psid, a_par, lf->obs, V.obs_bits);
+  const unsigned long long own = own_of(V.src, r, b.link, V.src_n_p);
+  const int np = V.new_id[(int)(own >> kKeyLowBits)];
+  const unsigned long long key = belief_key(np, (uint32_t)(own & kLinkKey));
+  V.dst.info[nr] = BeliefInfo{0, Nb, key};
   bool won = false, fresh = false;
   int id = -1;
-  const uint32_t h = probe(V.dst, key, kCarryStamp, won, fresh, id);
+  Bucket line;
+  bucket_read(V.dst, key, line);
+  const uint32_t h = probe(V.dst, line, key, kCarryStamp, won, fresh, id);
   if (h == ~0u || !won) {
     atomicOr((unsigned int*)&V.cnt[4 * kRerootCnt], 1u);
     return;
   }
-  V.dst.list[nr - 1] = (int)h + 1;
   V.dst.h_slot[h].id = nr;
-  mt->parent = ((unsigned long long)(uint32_t)np << kActBits) | (unsigned long long)a_par;
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill16(uint4* p, size_t n, uint4 v) {

@@ -25,8 +25,15 @@ int forward_blocks(const PlanView& P);
 // Blocks of a sweep over the trace of an iteration with D levels (at most cap).
 int accum_blocks(const PlanView& P, int D, int cap);
 hipError_t launch_setup(const PlanView& P, hipStream_t s);
-hipError_t launch_forward(const PlanView& P, int k, int D, hipStream_t s);
-hipError_t launch_accum(const PlanView& P, int D, int grid, hipStream_t s);
+hipError_t launch_forward(const PlanView& P, int k, hipStream_t s);
+// Rows of up to kMaxA actions: the trace and the walk along the runs.  Long
+// rows: the two apart.
+hipError_t launch_fold(const PlanView& P, int k, int grid, hipStream_t s);
+hipError_t launch_accum(const PlanView& P, int k, int grid, hipStream_t s);
+hipError_t launch_chain(const PlanView& P, int k, int grid, hipStream_t s);
+// Rows of up to kMaxA actions: the full beliefs and the root.  Long rows: the
+// leaves, one depth, the root.
+hipError_t launch_full(const PlanView& P, int k, int grid, hipStream_t s);
 hipError_t launch_backup_leaf(const PlanView& P, int dep, int k, int grid, hipStream_t s);
 hipError_t launch_backup_level(const PlanView& P, int dep, int k, int grid, hipStream_t s);
 hipError_t launch_backup_root(const PlanView& P, int k, hipStream_t s);
@@ -36,31 +43,38 @@ hipError_t launch_env(const PlanView& P, int t, hipStream_t s);
 hipError_t launch_pf(const PlanView& P, int t, hipStream_t s);
 // One of the three: 0 weight, 1 scan, 2 resample.
 hipError_t launch_pf_part(const PlanView& P, int part, int t, hipStream_t s);
-// Copy the records of beliefs ids[0..n) (device) to out[n * rs] (device).
-hipError_t launch_gather(const TreeView& t, const int* ids, int n, unsigned char* out,
-                         hipStream_t s);
+// Pack the beliefs ids[0..n) (device) of a finished plan's tree (n_p episodes,
+// ob observation bits, fixed-point scale) into out (device).
+hipError_t launch_gather(const TreeView& t, int n_p, int ob, float scale, const int* ids, int n,
+                         unsigned char* out, hipStream_t s);
 // Tree re-rooting between real steps.  One launch of the mark or copy pass
 // covers the source beliefs of one depth (src_depth), in the source's level
 // steps steps[0 .. n_steps).
+struct RerootStep {
+  int step;                   // level step
+  int iter, level;            // iteration (0-based) and level that created it, or
+  int n;                      // iter < 0: a kept subtree's step with n beliefs
+};
 struct RerootView {
   TreeView src, dst;
   int src_n_p, dst_n_p;
   int A;
   int obs_bits;               // observation field of the belief keys
-  const int* steps;
+  const RerootStep* steps;
   int n_steps;
   int src_depth;
-  int root_rec;               // source record of the new root (depth 1)
+  int root_rec;               // source belief of the new root (depth 1)
   int first_step;             // copy: first destination step of depth src_depth-1
   double rescale;             // copy: 2^(S_dst - S_src) for the fixed-point sums
-  unsigned char* kept;        // [source records] 1: in the kept subtree
-  int* new_id;                // [source records] destination record
+  float src_scale;            // 2^S_src
+  unsigned char* kept;        // [source beliefs] 1: in the kept subtree
+  int* new_id;                // [source beliefs] destination belief
   // [4][kMaxDepth + 1]: kept beliefs, their action nodes, the root's visits
   // (depth 1) and the copy's fill counters; [4 * (kMaxDepth + 1)] error flags.
   unsigned long long* cnt;
 };
 constexpr int kRerootCnt = kMaxDepth + 1;
-// Record of the root's child belief for (a, obs) in a finished plan's table,
+// The root's child belief for (a, obs) in a finished plan's table,
 // or -1 (one thread; out is a device int).
 hipError_t launch_reroot_find(const TreeView& t, int a, int obs, int ob, int* out,
                               hipStream_t s);

@@ -66,15 +66,18 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
 
   // Source level steps grouped by depth.
   const int n_src_steps = src->last_steps;
-  if ((int)src->step_depth.size() != n_src_steps)
+  if ((int)src->steps.size() != n_src_steps)
     return fail(VOPP_E_INTERNAL, "source tree layout is inconsistent");
   int max_d = 0;
-  for (int d : src->step_depth) max_d = std::max(max_d, d);
-  std::vector<int> steps_host, off(max_d + 2, 0);
+  for (const auto& st : src->steps) max_d = std::max(max_d, st.depth);
+  std::vector<RerootStep> steps_host;
+  std::vector<int> off(max_d + 2, 0);
   for (int d = 1; d <= max_d; ++d) {
     off[d] = (int)steps_host.size();
-    for (int t = 0; t < n_src_steps; ++t)
-      if (src->step_depth[t] == d) steps_host.push_back(t);
+    for (int t = 0; t < n_src_steps; ++t) {
+      const auto& st = src->steps[t];
+      if (st.depth == d) steps_host.push_back({t, st.iter, d - 1, st.n});
+    }
   }
   off[max_d + 1] = (int)steps_host.size();
 
@@ -82,7 +85,8 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
   const size_t n_rec = (size_t)src->z.cap_b;
   const size_t n_cnt = 4 * (size_t)kRerootCnt + 1;
   const size_t b_kept = align256(n_rec), b_new = align256(n_rec * 4),
-               b_cnt = align256(n_cnt * 8), b_steps = align256(steps_host.size() * 4 + 4);
+               b_cnt = align256(n_cnt * 8),
+               b_steps = align256((steps_host.size() + 1) * sizeof(RerootStep));
   Scratch sc;
   hipError_t e = hipMalloc(&sc.base, b_kept + b_new + b_cnt + b_steps + 256);
   if (e != hipSuccess) return fail(VOPP_E_NOMEM, "re-rooting scratch: %s", hipGetErrorString(e));
@@ -90,15 +94,15 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
   unsigned char* kept = (unsigned char*)q;
   int* new_id = (int*)(q + b_kept);
   unsigned long long* cnt = (unsigned long long*)(q + b_kept + b_new);
-  int* steps_dev = (int*)(q + b_kept + b_new + b_cnt);
+  RerootStep* steps_dev = (RerootStep*)(q + b_kept + b_new + b_cnt);
   int* found_dev = (int*)(q + b_kept + b_new + b_cnt + b_steps);
   e = hipMemsetAsync(kept, 0, n_rec, s);
   if (e == hipSuccess) e = hipMemsetAsync(cnt, 0, n_cnt * 8, s);
   if (e == hipSuccess && !steps_host.empty())
-    e = hipMemcpyAsync(steps_dev, steps_host.data(), steps_host.size() * 4,
+    e = hipMemcpyAsync(steps_dev, steps_host.data(), steps_host.size() * sizeof(RerootStep),
                        hipMemcpyHostToDevice, s);
   if (e == hipSuccess)
-    e = launch_reroot_find(src->tree, action, obs, p->view.obs_bits, found_dev, s);
+    e = launch_reroot_find(src->last_tree, action, obs, p->view.obs_bits, found_dev, s);
   int root_rec = -1;
   if (e == hipSuccess) e = hipMemcpyAsync(&root_rec, found_dev, 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -108,7 +112,8 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
   // Mark the kept subtree depth by depth and count it.
   RerootView V;
   std::memset(&V, 0, sizeof(V));
-  V.src = src->tree;
+  V.src = src->last_tree;
+  V.src_scale = (float)(1.0 / src->last_fix_inv64);
   V.src_n_p = src->last_n_p;
   V.A = p->nA;
   V.obs_bits = p->view.obs_bits;
@@ -167,14 +172,12 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
     vopp_workspace_free(grown);
   }
   dst->n_prev_beliefs = 0;                      // its old tree is gone
-  dst->hash_dirty = true;                       // until the copy has finished
 
-  // Clear the destination's table and the kept steps' lists, then copy.
-  const size_t hcap = (size_t)dst->tree.h_mask + 1;
-  e = launch_fill16(dst->tree.h_slot, hcap, make_uint4(~0u, ~0u, ~0u, ~0u), s);
-  if (e == hipSuccess && carry_steps > 0)
-    e = hipMemsetAsync(dst->tree.list, 0, (size_t)carry_steps * n_p * sizeof(int), s);
+  // Clear the table that the next plan uses, then copy.
+  cy.h_mask = table_mask(n_p, (long long)next_budget + carry_steps);
   V.dst = dst->tree;
+  V.dst.h_mask = cy.h_mask;
+  e = launch_fill16(dst->tree.h_slot, (size_t)cy.h_mask + 1, make_uint4(~0u, ~0u, ~0u, ~0u), s);
   V.dst_n_p = n_p;
   V.rescale = std::ldexp(1.0, cy.shift) * src->last_fix_inv64;
   for (int d = 1; d <= max_d && e == hipSuccess; ++d) {
@@ -187,7 +190,7 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
   int rng[2 * (kMaxDepth + 1)] = {0};
   for (int d = 1; d <= kMaxDepth; ++d) {
     rng[2 * d] = cy.first[d];
-    rng[2 * d + 1] = cy.count[d];
+    rng[2 * d + 1] = (int)cy.beliefs[d];
   }
   if (e == hipSuccess)
     e = hipMemcpyAsync(dst->carry_rng_dev, rng, sizeof(rng), hipMemcpyHostToDevice, s);
@@ -199,7 +202,6 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
   if (err) return fail(VOPP_E_INTERNAL, "re-rooting: a kept belief could not be inserted");
   cy.pending = true;
   dst->carry = cy;
-  dst->hash_dirty = false;
   if (kept_out) *kept_out = kept_total;
   return VOPP_OK;
 }

@@ -197,12 +197,7 @@ vopp_status admit(vopp_server* s, int id) {
   s->slot_ep[slot] = id;
   s->used += e.footprint;
   e.admitted = true;
-  // Upload the iteration schedule, the initial particles and the true state.
-  int* sb = e.res.ws->step_host;
-  sb[0] = 0;
-  for (int k = 1; k <= e.d.budget; ++k)
-    sb[k] = sb[k - 1] + (e.d.params.schedule == VOPP_SCHEDULE_FIXED ? e.d.depth
-                                                                    : std::min(k, e.d.depth));
+  // Upload the initial particles and the true state.
   void *part, *prop;
   unsigned long long* w;
   int* env;
@@ -213,10 +208,8 @@ vopp_status admit(vopp_server* s, int id) {
   env_init[0] = e.init_state[0];
   env_init[1] = e.init_state[1];
   for (int i = 2; i < 8; ++i) env_init[i] = 0;
-  hipError_t err = hipMemcpyAsync(e.res.ws->step_base_dev, sb, (e.d.budget + 1) * sizeof(int),
-                                  hipMemcpyHostToDevice, s->stream);
-  if (err == hipSuccess)
-    err = hipMemcpyAsync(part, e.init, e.init_bytes, hipMemcpyHostToDevice, s->stream);
+  hipError_t err =
+      hipMemcpyAsync(part, e.init, e.init_bytes, hipMemcpyHostToDevice, s->stream);
   if (err == hipSuccess)
     err = hipMemcpyAsync(env, env_init, 8 * sizeof(int), hipMemcpyHostToDevice, s->stream);
   if (err != hipSuccess) return hip_fail(err, "episode admission");
@@ -438,11 +431,9 @@ extern "C" vopp_status vopp_server_tick(vopp_server* s, int32_t* pending) {
       const Phase& f = e.phases[e.next++];
       switch (f.kind) {
         case kPhaseSetup: err = launch_setup(P, s->stream); break;
-        case kPhaseForward: err = launch_forward(P, f.a0, f.a1, s->stream); break;
-        case kPhaseAccum: err = launch_accum(P, f.a0, f.nblk, s->stream); break;
-        case kPhaseLeaf: err = launch_backup_leaf(P, f.a0, f.a1, f.nblk, s->stream); break;
-        case kPhaseLevel: err = launch_backup_level(P, f.a0, f.a1, f.nblk, s->stream); break;
-        case kPhaseRoot: err = launch_backup_root(P, f.a0, s->stream); break;
+        case kPhaseForward: err = launch_forward(P, f.a0, s->stream); break;
+        case kPhaseFold: err = launch_fold(P, f.a0, f.nblk, s->stream); break;
+        case kPhaseFull: err = launch_full(P, f.a0, f.nblk, s->stream); break;
         case kPhaseEnv: err = launch_env(P, f.a0, s->stream); break;
         case kPhasePFWeight: err = launch_pf_part(P, 0, f.a0, s->stream); break;
         case kPhasePFScan: err = launch_pf_part(P, 1, f.a0, s->stream); break;
