@@ -575,9 +575,11 @@ int backup_grid(const PlanView& P, int dep, int k, int cap, long long kept) {
 // Grid of dev_full after iteration k: the items it may find, up to the cap
 // (each block takes as many as it finds).
 int full_grid(const PlanView& P, int k, const std::function<long long(int)>& kept) {
+  // Lanes per belief (kRowLanes of the row's width).
+  const int A = P.m.Apad, lanes = A <= 4 ? 1 : A <= 8 ? 2 : A <= 16 ? 4 : A <= 32 ? 8 : 16;
   long long items = 1;
   for (int dep = 1; dep <= depth_at(P, k); ++dep)
-    items += backup_grid(P, dep, k, kFullCap, kept ? kept(dep) : 0);
+    items += (long long)lanes * backup_grid(P, dep, k, kFullCap, kept ? kept(dep) : 0);
   return (int)std::min(items, (long long)kFullCap);
 }
 

@@ -80,6 +80,7 @@ constexpr uint32_t kLinkHead = 1u << 28;    // first of its run (in the table)
 constexpr uint32_t kLinkClaim = 1u << 29;   // another episode reached it
 constexpr uint32_t kLinkFull = 1u << 30;    // its rows hold it (set after the
                                             // iteration that claimed it)
+constexpr uint32_t kLinkInner = 1u << 31;   // full, and so is a child of it
 
 // An episode's run of one iteration (TreeView::run): levels 0 .. tl-1 were
 // visits of existing beliefs (trace rows), then len beliefs were created, at

@@ -35,6 +35,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "vopp_device.hpp"
 #include "vopp_launch.hpp"
@@ -911,7 +912,10 @@ __device__ void dev_accum(const PlanView& P, int k, int D, int blk, int nblk, Sm
         unsigned int at = sm.n[0] + (unsigned int)__popcll(cm & ((1ull << (threadIdx.x & 63)) - 1));
         for (int i = 0; i < wv; ++i) at += (unsigned int)sm.wave[i];
         T.full[full_first(P, lvl) + at] = id;
-        T.node[id].link |= kLinkFull;
+        // (atomic: its own children may become full in this launch, too)
+        atomicOr(&T.node[id].link, kLinkFull);
+        const int up = (int)(T.info[id].own >> kKeyLowBits);
+        if (up) atomicOr(&T.node[up].link, kLinkInner);
       }
     }
     for (int j = threadIdx.x; j < kAggSlots; j += kBlock) {
@@ -1202,133 +1206,174 @@ struct SweepCount {
   unsigned long long beliefs, internal, nodes;
 };
 
-// Full beliefs of depth dep >= 1, base .. base + kBlock - 1 of the set.
-// AM >= |A| keeps the row in registers.  wait() returns once the deeper
-// depths' adds to W are done; every thread of the block calls it, after its other
-// loads are on their way.
-template <int AM, typename Wait>
-__device__ __forceinline__ void full_level(const PlanView& P, const FullSet& S, int dep, int base,
-                                           Smem& sm, SweepCount& cnt, Wait wait) {
+// Lanes that share a full belief in the sweep below, a quad of its row each.
+template <int AM>
+constexpr int kRowLanes = AM / 4;
+
+// Full beliefs of depth dep >= 1, base .. base + kBlock / kRowLanes - 1 of the
+// set, AM >= |A|.  wait() returns once the deeper depths' adds to W are done;
+// every thread of the block calls it, after its other loads are on their way.
+// pushed() tells the next depth that this item's adds have arrived; the row's
+// stores come after it and take their time beside the next depth's work (10 us
+// of 45 for the 89,700 beliefs at depth 2 of nav2d).  V and N_b are kept
+// only by the last iteration's sweep, for the caller: a belief with an
+// action node computes both anew in every iteration.
+//
+// Bound by latency and by the requests of rows at random ids, so a row is read
+// in 16-byte pieces by as many lanes as it has quads: with a thread per row, a
+// row of 40 actions took 24 us a depth, nearly all of it one thread's
+// arithmetic.  The exponentials are the lane's own four; every
+// lane adds up the row's in action order, so the sums round as before.  Only
+// a belief with a full child (kLinkInner) is added to in this launch and
+// reads W past the caches after the wait (about 23 G requests/s); the others,
+// all but 281 of the 89,700 at depth 2 of nav2d, read it with the rest of the
+// row.
+template <int AM, typename Wait, typename Done>
+__device__ __forceinline__ void full_level(const PlanView& P, const FullSet& S, int dep, int k,
+                                           int base, Smem& sm, SweepCount& cnt, Wait wait,
+                                           Done pushed) {
+  constexpr int kLanes = kRowLanes<AM>;
   const TreeView& T = P.t;
   const int A = P.m.nA;
   const float gamma = P.m.gamma, eta = P.eta, inv = P.fix_inv;
-  const int i = base + threadIdx.x;
+  const int g = (int)threadIdx.x & (kLanes - 1), j0 = 4 * g;
+  const int i = base + (int)threadIdx.x / kLanes;
   const bool have = i < S.n;
   const int b = have ? full_id(S, i) : 0;
-  float* prow = rec_psi(T, b);
-  const int* nrow = rec_n(T, b);
-  unsigned long long* crow = rec_c(T, b);
-  unsigned long long* wrow = rec_w(T, b);
+  const bool mine = have && j0 < A;
+  float* prow = rec_psi(T, b) + j0;
+  unsigned long long* wrow = rec_w(T, b) + j0;
   BeliefInfo in{0, 0, 0ull};
   float V = 0.0f;
-  int n[AM];
-  float psi[AM];
-  unsigned long long cf[AM], wf[AM];
-#pragma unroll
-  for (int j = 0; j < AM; ++j) { n[j] = 0; psi[j] = 0.0f; cf[j] = 0ull; wf[j] = 0ull; }
+  bool inner = false;
+  int n[4] = {0, 0, 0, 0};
+  float psi[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  unsigned long long cf[4] = {0, 0, 0, 0}, wf[4] = {0, 0, 0, 0};
   // Two rounds of loads, both before the belief's first store (a wait for a
   // load also waits for the stores issued before it): the parent, value and
-  // visit counts, then -- for a belief with an action node -- its preference
-  // row and the C of its visited actions only.
+  // visit counts, then the rest of the row of a belief with an action node.
   if (have) {
     in = T.info[b];
-    V = T.node[b].V;
-#pragma unroll
-    for (int j = 0; j < AM; j += 4) {
-      int4 c = make_int4(0, 0, 0, 0);
-      if (j < A) c = *reinterpret_cast<const int4*>(nrow + j);
-      n[j] = c.x; n[j + 1] = c.y; n[j + 2] = c.z; n[j + 3] = c.w;
+    const uint2 q = *reinterpret_cast<const uint2*>(&T.node[b]);
+    V = __uint_as_float(q.x);
+    inner = i < S.n_kept || (q.y & kLinkInner) != 0u;
+    if (mine) {
+      const int4 c = *reinterpret_cast<const int4*>(rec_n(T, b) + j0);
+      n[0] = c.x; n[1] = c.y; n[2] = c.z; n[3] = c.w;
     }
   }
   int N = in.Nb;
-  bool any = false;
+  bool vis[4];
+  int nsum = 0;
 #pragma unroll
-  for (int j = 0; j < AM; ++j) any = any || (j < A && n[j] > 0);
-  if (any) {
-#pragma unroll
-    for (int j = 0; j < AM; j += 4) {
-      float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (j < A) q = *reinterpret_cast<const float4*>(prow + j);
-      psi[j] = q.x; psi[j + 1] = q.y; psi[j + 2] = q.z; psi[j + 3] = q.w;
-    }
-#pragma unroll
-    for (int j = 0; j < AM; ++j)
-      if (j < A && n[j] > 0) cf[j] = crow[j];
+  for (int j = 0; j < 4; ++j) {
+    vis[j] = j0 + j < A && n[j] > 0;
+    nsum += vis[j] ? n[j] : 0;
   }
+#pragma unroll
+  for (int off = kLanes / 2; off > 0; off >>= 1) nsum += __shfl_xor(nsum, off, 64);
+  const bool any = nsum > 0;
+  if (any && mine) {
+    const float4 q = *reinterpret_cast<const float4*>(prow);
+    psi[0] = q.x; psi[1] = q.y; psi[2] = q.z; psi[3] = q.w;
+    const ulonglong2* c2 = reinterpret_cast<const ulonglong2*>(rec_c(T, b) + j0);
+    const ulonglong2 c01 = c2[0], c23 = c2[1];
+    cf[0] = c01.x; cf[1] = c01.y; cf[2] = c23.x; cf[3] = c23.y;
+    if (!inner) {
+      const ulonglong2* w2 = reinterpret_cast<const ulonglong2*>(wrow);
+      const ulonglong2 w01 = w2[0], w23 = w2[1];
+      wf[0] = w01.x; wf[1] = w01.y; wf[2] = w23.x; wf[3] = w23.y;
+    }
+  }
+  // Sum over the row in action order, in every lane of the row.
+  auto row_sum = [&](const float (&e)[4]) {
+    float se = 0.0f;
+    if constexpr (kLanes == 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j < A) se = se + e[j];
+    } else {
+      const int l0 = ((int)threadIdx.x & 63) - g;
+      for (int q = 0; 4 * q < A; ++q) {
+        float x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = __shfl(e[j], l0 + q, 64);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (4 * q + j < A) se = se + x[j];
+      }
+    }
+    return se;
+  };
+  // L_eta of the row.
+  auto row_value = [&]() {
+    float m = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j0 + j < A) m = fmaxf(m, psi[j]);
+#pragma unroll
+    for (int off = kLanes / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    float e[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e[j] = j0 + j < A ? expf(eta * (psi[j] - m)) : 0.0f;
+    return m + logf(row_sum(e)) / eta;
+  };
   wait();
   unsigned long long target = 0, f = 0;
   if (any) {
+    if (inner) {
 #pragma unroll
-    for (int j = 0; j < AM; ++j)
-      if (j < A && n[j] > 0) wf[j] = read_shared(wrow + j);
+      for (int j = 0; j < 4; ++j)
+        if (vis[j]) wf[j] = read_shared(wrow + j);
+    }
     // V_curr = L_eta Psi (Eq. 3) before the update.
-    float m = psi[0];
-#pragma unroll
-    for (int j = 1; j < AM; ++j)
-      if (j < A) m = fmaxf(m, psi[j]);
-    float se = 0.0f;
-#pragma unroll
-    for (int j = 0; j < AM; ++j)
-      if (j < A) se = se + expf(eta * (psi[j] - m));
-    const float vc = m + logf(se) / eta;
+    const float vc = row_value();
     // Q = C/N + gamma W with W = sum_children V N_b / N; Psi <- Psi - V_curr + Q.
-    int nsum = 0;
 #pragma unroll
-    for (int j = 0; j < AM; ++j) {
-      if (j < A && n[j] > 0) {
+    for (int j = 0; j < 4; ++j) {
+      if (vis[j]) {
         const float c = from_fix(cf[j], inv);
         const float w = from_fix(wf[j], inv);
         const float fn = (float)n[j];
         const float q = c / fn + gamma * (w / fn);
         psi[j] = (psi[j] - vc) + q;
-        nsum += n[j];
         ++cnt.nodes;
       }
     }
     // V = L_eta Psi after the update; N_b = sum_a N(b, a).
-    float m2 = psi[0];
-#pragma unroll
-    for (int j = 1; j < AM; ++j)
-      if (j < A) m2 = fmaxf(m2, psi[j]);
-    float se2 = 0.0f;
-#pragma unroll
-    for (int j = 0; j < AM; ++j)
-      if (j < A) se2 = se2 + expf(eta * (psi[j] - m2));
-    V = m2 + logf(se2) / eta;
+    V = row_value();
     N = nsum;
-    ++cnt.internal;
   }
-  if (have) {
+  if (have && g == 0) {
     target = parent_of(in.own, P.m.obs_bits);
     f = push_value(P, V, N);
     ++cnt.beliefs;
+    if (any) ++cnt.internal;
   }
-  // The push first: the next depth waits for it, not for the stores.
   if (dep >= kPushDirectDepth) {
     if (f) push_one(T, target, f);
   } else {
     push_shared(T, sm.agg, target, f);
   }
-  if (any) {
-#pragma unroll
-    for (int j = 0; j < AM; j += 4)
-      if (j < A)
-        *reinterpret_cast<float4*>(prow + j) =
-            make_float4(psi[j], psi[j + 1], psi[j + 2], psi[j + 3]);
+  pushed();
+  if (any && mine) {
+    *reinterpret_cast<float4*>(prow) = make_float4(psi[0], psi[1], psi[2], psi[3]);
     // W is rebuilt by the children's pushes of the next iteration.
-#pragma unroll
-    for (int j = 0; j < AM; ++j)
-      if (j < A && n[j] > 0 && wf[j]) wrow[j] = 0ull;
-    T.node[b].V = V;
-    T.info[b].Nb = N;
+    ulonglong2* w2 = reinterpret_cast<ulonglong2*>(wrow);
+    if ((vis[0] && wf[0]) || (vis[1] && wf[1])) w2[0] = make_ulonglong2(0ull, 0ull);
+    if ((vis[2] && wf[2]) || (vis[3] && wf[3])) w2[1] = make_ulonglong2(0ull, 0ull);
+    if (g == 0 && counts_tree(P, k)) {
+      T.node[b].V = V;
+      T.info[b].Nb = N;
+    }
   }
 }
 
-template <typename Wait>
+template <int AM, typename Wait>
 __device__ void dev_backup_root(const PlanView& P, int k, Smem& sm, Wait wait);
 
 // The full beliefs of every depth and the root, in one launch.  Blocks take
-// items (kBlock beliefs of one depth; the root last) from a counter, deepest
+// items (a block's beliefs of one depth; the root last) from a counter, deepest
 // depth first; an item waits until every item of the deeper depths is done,
 // with everything but W already read.  Items are taken in that order by blocks
 // that run, so whatever the residency the lowest unfinished item waits for
@@ -1347,7 +1392,8 @@ __device__ void dev_full(const PlanView& P, int k, int blk, Smem& sm) {
   // Lane l: the first item of depth D - 1 - l; lane D - 1: the root's.
   const int my_dep = D - 1 - lane;
   int n = 0;
-  if (my_dep >= 1) n = (full_set(P, my_dep).n + kBlock - 1) / kBlock;
+  constexpr int per = kBlock / kRowLanes<AM>;     // beliefs of a level's item
+  if (my_dep >= 1) n = (full_set(P, my_dep).n + per - 1) / per;
   int start = n_leaf + (int)wave_incl_scan((unsigned long long)n) - n;
   if (my_dep < 0) start = INT_MAX;
   SweepCount cnt{0, 0, 0};
@@ -1366,18 +1412,21 @@ __device__ void dev_full(const PlanView& P, int k, int blk, Smem& sm) {
       __syncthreads();
     };
     if (dep == 0) {
-      dev_backup_root(P, k, sm, wait);
+      dev_backup_root<AM>(P, k, sm, wait);
       break;
     }
+    auto pushed = [&]() {
+      stores_done();                              // this wavefront's adds
+      __syncthreads();
+      if (threadIdx.x == 0) atomicAdd(&T.counters[3], 1ull);
+    };
     if (dep == D) {
       full_leaves(P, leaves, D, item * kBlock, sm);
       leaf_cnt += min(kBlock, leaves.n - item * kBlock);
+      pushed();
     } else {
-      full_level<AM>(P, full_set(P, dep), dep, (item - first) * kBlock, sm, cnt, wait);
+      full_level<AM>(P, full_set(P, dep), dep, k, (item - first) * per, sm, cnt, wait, pushed);
     }
-    stores_done();                                // this wavefront's adds
-    __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(&T.counters[3], 1ull);
   }
   __syncthreads();
   // The sweep's work over the plan (every iteration), then the tree
@@ -1921,33 +1970,50 @@ __device__ __forceinline__ double ordered_sum(double x, int A, double& upto) {
   return s;
 }
 
-template <typename Wait>
+template <int AM, typename Wait>
 __device__ void dev_backup_root(const PlanView& P, int k, Smem& sm, Wait wait) {
   const TreeView& T = P.t;
   const int A = P.m.nA;
   double p_me = -INFINITY;
   if ((int)threadIdx.x < A) p_me = T.psi_root[threadIdx.x];
-  wait();
   static_assert(3 * kMaxA <= kAggSlots && kStripes == 64, "sums fit the table");
   unsigned long long* sums = sm.agg.a;          // [3][A]
-  for (int r0 = 0; r0 < 3 * A; r0 += kBlock / 16) {
-    const int r = r0 + (int)threadIdx.x / 16, l = threadIdx.x & 15;
-    unsigned long long v = 0;
-    if (r < 3 * A) {
-      const int q = r / A, a = r - q * A;
-      unsigned long long* p = T.root_acc + ((size_t)q * T.ra + a) * kStripes + l;
+  // Sums first .. first + n - 1 of them; every load is issued before the first
+  // is waited for (40 actions, one after the other: 8 us of the root's 13).
+  auto stripes = [&](auto rounds, int first, int n, auto read) {
+    constexpr int R = decltype(rounds)::value;
+    unsigned long long v[R][4];
+#pragma unroll
+    for (int x = 0; x < R; ++x) {
+      const int r = x * (kBlock / 16) + (int)threadIdx.x / 16;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        // W was added to in this launch; N and C in earlier ones.
-        v += read_shared(p + 16 * i);
-        if (q == 2) p[16 * i] = 0ull;
+        v[x][i] = 0;
+        if (r < n) {
+          const int q = (first + r) / A, a = first + r - q * A;
+          v[x][i] = read(T.root_acc + ((size_t)q * T.ra + a) * kStripes + (threadIdx.x & 15) + 16 * i);
+        }
       }
     }
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
-    if (r < 3 * A && l == 0) sums[r] = v;
-  }
+    for (int x = 0; x < R; ++x) {
+      const int r = x * (kBlock / 16) + (int)threadIdx.x / 16;
+      unsigned long long t = (v[x][0] + v[x][1]) + (v[x][2] + v[x][3]);
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 16);
+      if (r < n && (threadIdx.x & 15) == 0) sums[first + r] = t;
+    }
+  };
+  constexpr int kPer = kBlock / 16;             // sums of one round
+  // N and C were added to in earlier launches, W in this one.
+  stripes(std::integral_constant<int, (2 * AM + kPer - 1) / kPer>{}, 0, 2 * A,
+          [](const unsigned long long* p) { return *p; });
+  wait();
+  stripes(std::integral_constant<int, (AM + kPer - 1) / kPer>{}, 2 * A, A,
+          [](const unsigned long long* p) { return read_shared(p); });
   __syncthreads();
+  for (int r = threadIdx.x; r < A * kStripes; r += kBlock)
+    T.root_acc[(size_t)2 * T.ra * kStripes + r] = 0ull;
   if (threadIdx.x >= 64) return;
   const int lane = threadIdx.x;
   root_gate(P, k, lane);
