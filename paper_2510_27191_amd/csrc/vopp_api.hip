@@ -402,6 +402,10 @@ void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, doub
   const size_t cb = (size_t)z.cap_b;
   t.ra = z.Apad;
   t.bw = rec_bitmap_words(z.Apad);
+  // Rows longer than a memory line (the counts of 32 actions) keep their order.
+  t.row_bits = 16;
+  while (t.row_bits > kRowSpread && (cb >> t.row_bits) == 0) --t.row_bits;
+  t.row_end = z.Apad <= kRowSpreadMaxA ? (uint32_t)(cb >> t.row_bits << t.row_bits) : 0u;
   t.psi = c.take<float>(cb * z.Apad);
   t.nv = c.take<int>(cb * z.Apad);
   t.cv = c.take<unsigned long long>(cb * z.Apad);

@@ -196,6 +196,8 @@ struct TreeView {
   int* full;                     // full beliefs by depth (full_first); a full
                                  // belief has two visits or more, so half the
                                  // level steps' episodes bound them
+  uint32_t row_bits, row_end;    // rows of ids below row_end are permuted within
+                                 // blocks of 2^row_bits (row_at)
   unsigned int* full_cnt;        // [kMaxDepth + 1] how many of each depth
   unsigned long long* counters;  // [1] error flags [2], [3] items taken and
                                  // done of dev_full [4] insert re-probes
@@ -237,14 +239,28 @@ __host__ __device__ inline int rec_bytes(int ra) {
 __device__ __forceinline__ float* rec_psi(const TreeView& t, int id) {
   return t.psi + (size_t)id * (size_t)t.ra;
 }
-__device__ __forceinline__ int* rec_n(const TreeView& t, int id) {
-  return t.nv + (size_t)id * (size_t)t.ra;
+// Where the counts, C and W of belief id are: neighbouring ids are 2^(row_bits
+// - kRowSpread) rows apart.  The atomics of a phase go to the beliefs that many
+// episodes share, and those were mostly inserted by the episodes that started
+// first, neighbours; adds to one 128-byte line, or to lines of one memory
+// channel, take their turns.  With rows in the order of the ids a plan took
+// 1180 us (nav2d) and 2579 us (sparse4096), with these 1058 and 2240.
+constexpr int kRowSpread = 4;
+constexpr int kRowSpreadMaxA = 8;
+__device__ __forceinline__ size_t row_at(const TreeView& t, int id) {
+  uint32_t row = (uint32_t)id;
+  if (row < t.row_end) {
+    const uint32_t mask = (1u << t.row_bits) - 1u, lo = row & mask;
+    row = (row ^ lo) | ((lo << kRowSpread) & mask) | (lo >> (t.row_bits - kRowSpread));
+  }
+  return (size_t)row * (size_t)t.ra;
 }
+__device__ __forceinline__ int* rec_n(const TreeView& t, int id) { return t.nv + row_at(t, id); }
 __device__ __forceinline__ unsigned long long* rec_c(const TreeView& t, int id) {
-  return t.cv + (size_t)id * (size_t)t.ra;
+  return t.cv + row_at(t, id);
 }
 __device__ __forceinline__ unsigned long long* rec_w(const TreeView& t, int id) {
-  return t.wv + (size_t)id * (size_t)t.ra;
+  return t.wv + row_at(t, id);
 }
 __device__ __forceinline__ uint32_t* rec_bits(const TreeView& t, int id) {
   return t.bits + (size_t)id * (size_t)t.bw;
