@@ -1293,9 +1293,10 @@ extern "C" vopp_status vopp_belief_update(const vopp_pomdp* p, void* particles, 
   int host_env[8] = {0, 0, obs, action, 0, 0, 0, 0};
   hipError_t e = hipMemcpyAsync(env, host_env, sizeof(host_env), hipMemcpyHostToDevice, s);
   PlanView P = filter_view(p, out, env, w, prop, particles, n, seed);
-  if (e == hipSuccess) e = launch_pf(P, (int)step, s);
+  if (e == hipSuccess) e = launch_pf_weight(P, (int)step, s);
+  if (e == hipSuccess) e = launch_pf_resample(P, (int)step, s);
   unsigned long long tot = 0;
-  if (e == hipSuccess) e = hipMemcpyAsync(&tot, w + (n - 1), 8, hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(&tot, env + 6, 8, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "belief update");
   if (total_weight) *total_weight = tot;

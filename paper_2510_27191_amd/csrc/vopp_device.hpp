@@ -296,13 +296,20 @@ constexpr int kAccumCap = 4096;             // default block cap of the accumula
 struct FilterView {
   void* part;              // M belief particles (the plan's root belief)
   void* prop;              // M propagated particles, same layout
-  unsigned long long* w;   // [M] integer weights, then their inclusive sums
+  unsigned long long* w;   // [M] inclusive sums of the integer weights, by segment
   int M;
   int* env;                // [0] state (tabular) or x bits, [1] y bits,
                            // [2] last observation, [3] last action,
-                           // [4] last reward bits, [5] terminal flag
+                           // [4] last reward bits, [5] terminal flag,
+                           // [6], [7] total weight of the last update
   uint32_t env_seed_lo, env_seed_hi;
 };
+// Segments of the particles whose weights are summed apart.
+constexpr int kPfSegs = 1024;
+__host__ __device__ inline int pf_segment(int M) {
+  return kBlock * ((M + kBlock * kPfSegs - 1) / (kBlock * kPfSegs));
+}
+__host__ __device__ inline int pf_segments(int M) { return (M + pf_segment(M) - 1) / pf_segment(M); }
 
 struct PlanView {
   ModelView m;
@@ -375,7 +382,7 @@ constexpr int kOutStride = kMaxA + 12;
 enum : int {
   kPhaseForward = 0, kPhaseSetup = 5, kPhaseSelect = 6,
   // Served episodes: true-environment step and SIR belief update.
-  kPhaseEnv = 7, kPhasePFWeight = 8, kPhasePFScan = 9, kPhasePFResample = 10,
+  kPhaseEnv = 7, kPhasePFWeight = 8, kPhasePFResample = 10,
   // The trace together with the walk along single-visit beliefs; the full
   // beliefs and the root.
   kPhaseFold = 11, kPhaseFull = 12

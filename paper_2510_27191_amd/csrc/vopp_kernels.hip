@@ -2158,83 +2158,105 @@ __device__ __forceinline__ unsigned nav_cell_count(const ModelView& m, float nx,
   return (unsigned)(lo - first);
 }
 
-__device__ void dev_pf_weight(const PlanView& P, int t, int blk) {
-  const int i = blk * kBlock + threadIdx.x;
+// Propagates particle i and returns its integer weight.
+__device__ __forceinline__ unsigned long long pf_weight(const PlanView& P, int t, int i) {
   const int M = P.f.M;
-  if (i >= M) return;
   const int a = P.f.env[3], o = P.f.env[2];
   const U4 x = philox((uint32_t)i, kTagPF << 24, 0u, (uint32_t)t, P.seed_lo, P.seed_hi);
-  unsigned long long wt;
   if (P.m.kind == kTabular) {
     const int s = ((const int*)P.f.part)[i];
     const int sn = tabular_next(P.m, s, a, x.y);
     ((int*)P.f.prop)[i] = sn;
     const uint32_t* zr =
         row_leaves(P.m.thrZ + ((size_t)sn * P.m.nA + a) * P.m.rZ.stride, P.m.rZ);
-    wt = (unsigned long long)(zr[o] - (o > 0 ? zr[o - 1] : 0u));
-  } else {
-    const float* pf = (const float*)P.f.part;
-    float nx, ny;
-    nav_move(P.m, pf[i], pf[M + i], a, x.y, nx, ny);
-    float* q = (float*)P.f.prop;
-    q[i] = nx;
-    q[M + i] = ny;
-    const float sd = nav_obs_sd(P.m.nav, nx);
-    const int kn = P.m.nav.key_n;
-    wt = (unsigned long long)nav_cell_count(P.m, nx, sd, o / kn) *
+    return (unsigned long long)(zr[o] - (o > 0 ? zr[o - 1] : 0u));
+  }
+  const float* pf = (const float*)P.f.part;
+  float nx, ny;
+  nav_move(P.m, pf[i], pf[M + i], a, x.y, nx, ny);
+  float* q = (float*)P.f.prop;
+  q[i] = nx;
+  q[M + i] = ny;
+  const float sd = nav_obs_sd(P.m.nav, nx);
+  const int kn = P.m.nav.key_n;
+  return (unsigned long long)nav_cell_count(P.m, nx, sd, o / kn) *
          (unsigned long long)nav_cell_count(P.m, ny, sd, o % kn);
-  }
-  P.f.w[i] = wt;
 }
 
-// In-place inclusive scan of the M weights by one block.
-__device__ void dev_pf_scan(const PlanView& P, Smem& sm) {
-  const int M = P.f.M;
-  unsigned long long* w = P.f.w;
-  unsigned long long carry = 0;
+// Inclusive scan over the block; *total: its sum.  red holds kBlock / 64 words
+// of LDS; every thread of the block calls.
+__device__ __forceinline__ unsigned long long block_incl_scan(unsigned long long v,
+                                                              unsigned long long* red,
+                                                              unsigned long long* total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  for (int base = 0; base < M; base += kBlock * 4) {
-    unsigned long long v[4];
-    unsigned long long mine = 0;
+  const unsigned long long incl = wave_incl_scan(v);
+  if (lane == 63) red[wid] = incl;
+  __syncthreads();
+  unsigned long long off = 0, tot = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = base + threadIdx.x * 4 + q;
-      v[q] = i < M ? w[i] : 0ull;
-      mine += v[q];
-    }
-    const unsigned long long incl = wave_incl_scan(mine);
-    if (lane == 63) sm.wave[wid] = incl;
-    __syncthreads();
-    unsigned long long off = carry, tot = 0;
-#pragma unroll
-    for (int q = 0; q < kBlock / 64; ++q) {
-      if (q < wid) off += sm.wave[q];
-      tot += sm.wave[q];
-    }
-    unsigned long long run = off + incl - mine;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = base + threadIdx.x * 4 + q;
-      run += v[q];
-      if (i < M) w[i] = run;
-    }
+  for (int q = 0; q < kBlock / 64; ++q) {
+    if (q < wid) off += red[q];
+    tot += red[q];
+  }
+  __syncthreads();
+  *total = tot;
+  return off + incl;
+}
+
+// The particles are cut into at most kPfSegs segments (pf_segment(M) each); w
+// holds the weights' inclusive sums within a segment, so a segment's total is
+// its last word.  Each block of the resampling adds up the totals for
+// itself: at 65,536 particles 256 loads and a scan in LDS, where a launch of one
+// block that scanned all the weights took 63 us of the update's 111.
+__device__ void dev_pf_weight(const PlanView& P, int t, int blk, unsigned long long* red) {
+  const int M = P.f.M, seg = pf_segment(M);
+  unsigned long long carry = 0;
+  for (int base = blk * seg; base < min(M, (blk + 1) * seg); base += kBlock) {
+    const int i = base + threadIdx.x;
+    unsigned long long tot;
+    const unsigned long long incl =
+        block_incl_scan(i < M ? pf_weight(P, t, i) : 0ull, red, &tot);
+    if (i < M) P.f.w[i] = carry + incl;
     carry += tot;
-    __syncthreads();
   }
 }
 
-__device__ void dev_pf_resample(const PlanView& P, int t, int blk) {
+// pre: kPfSegs + kBlock / 64 words of LDS.
+__device__ void dev_pf_resample(const PlanView& P, int t, int blk, unsigned long long* pre) {
   const int j = blk * kBlock + threadIdx.x;
-  const int M = P.f.M;
+  const int M = P.f.M, seg = pf_segment(M), n_seg = pf_segments(M);
+  constexpr int kPer = kPfSegs / kBlock;
+  unsigned long long v[kPer], mine = 0, total;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int g = (int)threadIdx.x * kPer + q;
+    v[q] = g < n_seg ? P.f.w[min((g + 1) * seg, M) - 1] : 0ull;
+    mine += v[q];
+  }
+  unsigned long long run = block_incl_scan(mine, pre + kPfSegs, &total) - mine;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    run += v[q];
+    pre[(int)threadIdx.x * kPer + q] = run;
+  }
+  __syncthreads();
+  if (j == 0) *reinterpret_cast<unsigned long long*>(P.f.env + 6) = total;
   if (j >= M) return;
-  const unsigned long long total = P.f.w[M - 1];
   int src = j;                                   // zero total: keep propagation
   if (total > 0ull) {
     const U4 y = philox((uint32_t)j, kTagResample << 24, 0u, (uint32_t)t, P.seed_lo,
                         P.seed_hi);
     const unsigned long long u = ((unsigned long long)y.x << 32) | y.y;
-    const unsigned long long target = __umul64hi(u, total);
-    int lo = 0, hi = M - 1;                      // first i with w[i] > target
+    unsigned long long target = __umul64hi(u, total);
+    // First i whose running sum is > target: its segment, then its place.
+    int lo = 0, hi = n_seg - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (pre[mid] > target) hi = mid; else lo = mid + 1;
+    }
+    if (lo > 0) target -= pre[lo - 1];
+    hi = min((lo + 1) * seg, M) - 1;
+    lo *= seg;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
       if (P.f.w[mid] > target) hi = mid; else lo = mid + 1;
@@ -2688,14 +2710,12 @@ __global__ __launch_bounds__(kBlock, 4) void k_forward_wide(PlanView P, int k, i
 
 __global__ void k_env(PlanView P, int t) { dev_env(P, t); }
 __global__ __launch_bounds__(kBlock) void k_pf_weight(PlanView P, int t) {
-  dev_pf_weight(P, t, blockIdx.x);
-}
-__global__ __launch_bounds__(kBlock) void k_pf_scan(PlanView P) {
-  __shared__ Smem sm;
-  dev_pf_scan(P, sm);
+  __shared__ unsigned long long red[kBlock / 64];
+  dev_pf_weight(P, t, blockIdx.x, red);
 }
 __global__ __launch_bounds__(kBlock) void k_pf_resample(PlanView P, int t) {
-  dev_pf_resample(P, t, blockIdx.x);
+  __shared__ unsigned long long pre[kPfSegs + kBlock / 64];
+  dev_pf_resample(P, t, blockIdx.x, pre);
 }
 __global__ __launch_bounds__(kBlock) void k_setup(PlanView P) {
   __shared__ SetupSmem ss;
@@ -2786,9 +2806,12 @@ __device__ __forceinline__ void run_item(const PlanView& P, const BatchItem& it,
     case kPhaseSetup: dev_setup(P, blk, it.nblk, nullptr); break;   // |A| <= 16
     case kPhaseSelect: dev_select(P); break;
     case kPhaseEnv: dev_env(P, it.a0); break;
-    case kPhasePFWeight: dev_pf_weight(P, it.a0, blk); break;
-    case kPhasePFScan: dev_pf_scan(P, sm); break;
-    case kPhasePFResample: dev_pf_resample(P, it.a0, blk); break;
+    case kPhasePFWeight: dev_pf_weight(P, it.a0, blk, sm.wave); break;
+    case kPhasePFResample:
+      static_assert(sizeof(AggTable) >= (kPfSegs + kBlock / 64) * sizeof(unsigned long long),
+                    "the segment sums fit the table");
+      dev_pf_resample(P, it.a0, blk, reinterpret_cast<unsigned long long*>(&sm.agg));
+      break;
     default:
       if (Apad <= 4) {
         run_rows<4>(P, it, blk, bs);
@@ -3060,17 +3083,13 @@ hipError_t launch_env(const PlanView& P, int t, hipStream_t s) {
   hipLaunchKernelGGL(k_env, dim3(1), dim3(64), 0, s, P, t);
   return hipGetLastError();
 }
-hipError_t launch_pf_part(const PlanView& P, int part, int t, hipStream_t s) {
-  const dim3 g(blocks_for(P.f.M)), b(kBlock);
-  if (part == 0) hipLaunchKernelGGL(k_pf_weight, g, b, 0, s, P, t);
-  else if (part == 1) hipLaunchKernelGGL(k_pf_scan, dim3(1), b, 0, s, P);
-  else hipLaunchKernelGGL(k_pf_resample, g, b, 0, s, P, t);
+hipError_t launch_pf_weight(const PlanView& P, int t, hipStream_t s) {
+  hipLaunchKernelGGL(k_pf_weight, dim3(pf_segments(P.f.M)), dim3(kBlock), 0, s, P, t);
   return hipGetLastError();
 }
-hipError_t launch_pf(const PlanView& P, int t, hipStream_t s) {
-  hipError_t e = hipSuccess;
-  for (int part = 0; part < 3 && e == hipSuccess; ++part) e = launch_pf_part(P, part, t, s);
-  return e;
+hipError_t launch_pf_resample(const PlanView& P, int t, hipStream_t s) {
+  hipLaunchKernelGGL(k_pf_resample, dim3(blocks_for(P.f.M)), dim3(kBlock), 0, s, P, t);
+  return hipGetLastError();
 }
 // The parent and key of belief id in a finished plan's tree (link: its
 // record's): inside a run, the belief before it.

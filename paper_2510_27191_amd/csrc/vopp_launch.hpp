@@ -39,10 +39,9 @@ hipError_t launch_backup_level(const PlanView& P, int dep, int k, int grid, hipS
 hipError_t launch_backup_root(const PlanView& P, int k, hipStream_t s);
 hipError_t launch_select(const PlanView& P, hipStream_t s);
 hipError_t launch_env(const PlanView& P, int t, hipStream_t s);
-// SIR update of P.f: weight, scan, resample (three launches).
-hipError_t launch_pf(const PlanView& P, int t, hipStream_t s);
-// One of the three: 0 weight, 1 scan, 2 resample.
-hipError_t launch_pf_part(const PlanView& P, int part, int t, hipStream_t s);
+// SIR update of P.f: the particles moved and weighted, then resampled.
+hipError_t launch_pf_weight(const PlanView& P, int t, hipStream_t s);
+hipError_t launch_pf_resample(const PlanView& P, int t, hipStream_t s);
 // Pack the beliefs ids[0..n) (device) of a finished plan's tree (n_p episodes,
 // ob observation bits, fixed-point scale) into out (device).
 hipError_t launch_gather(const TreeView& t, int n_p, int ob, float scale, const int* ids, int n,

@@ -174,8 +174,7 @@ void start_request(vopp_server* s, Episode& e, double arrival) {
     const int t = e.step - 1;
     const int pb = (e.d.n_particles + kBlock - 1) / kBlock;
     e.phases.push_back({kPhaseEnv, t, 0, 1});
-    e.phases.push_back({kPhasePFWeight, t, 0, pb});
-    e.phases.push_back({kPhasePFScan, 0, 0, 1});
+    e.phases.push_back({kPhasePFWeight, t, 0, pf_segments(e.d.n_particles)});
     e.phases.push_back({kPhasePFResample, t, 0, pb});
   }
   std::vector<Phase> plan = plan_phases(e.d.pomdp, P, kAccumCap, kBackupCap);
@@ -435,9 +434,8 @@ extern "C" vopp_status vopp_server_tick(vopp_server* s, int32_t* pending) {
         case kPhaseFold: err = launch_fold(P, f.a0, f.nblk, s->stream); break;
         case kPhaseFull: err = launch_full(P, f.a0, f.nblk, s->stream); break;
         case kPhaseEnv: err = launch_env(P, f.a0, s->stream); break;
-        case kPhasePFWeight: err = launch_pf_part(P, 0, f.a0, s->stream); break;
-        case kPhasePFScan: err = launch_pf_part(P, 1, f.a0, s->stream); break;
-        case kPhasePFResample: err = launch_pf_part(P, 2, f.a0, s->stream); break;
+        case kPhasePFWeight: err = launch_pf_weight(P, f.a0, s->stream); break;
+        case kPhasePFResample: err = launch_pf_resample(P, f.a0, s->stream); break;
         case kPhaseSelect:
           err = launch_select(P, s->stream);
           e.waiting = true;
