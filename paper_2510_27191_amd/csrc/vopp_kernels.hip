@@ -175,6 +175,7 @@ struct Smem {
   AggTable agg;
   unsigned long long wave[kBlock / 64];
   alignas(16) float psi0[kMaxA];   // the initial row
+  float e0[kMaxA];                 // and its weights (RowBase)
   unsigned int n[2];
 };
 
@@ -1044,11 +1045,20 @@ __device__ void dev_backup_leaf(const PlanView& P, int dep, int k, int blk, int 
 // L_eta Psi of a row whose entry is psi0s[j] but for entry a (a < 0: none),
 // in the order of the level sweep's sums.  flat: psi0s is one value (the
 // uniform reference policy): one exponential serves the whole row, since the
-// weight of the largest entry is exp(0) = 1.
+// weight of the largest entry is exp(0) = 1.  Otherwise, for rows of more than
+// 8 actions, the entries' weights against the row's largest are kept in LDS (B)
+// and serve every row whose largest entry that still is; the loops stay loops,
+// since 64 exponentials written out spilled 724 bytes a thread (a walk of 5
+// levels of 40 actions under a prior: a launch took 32 us, now 21).
+struct RowBase {
+  float m0, m1;              // the largest entry, and the largest besides entry top
+  int top;                   // the first of that value
+  const float* e0;           // exp(eta (psi0s[j] - m0))
+};
 template <int AM>
 __device__ __forceinline__ float one_row_value(const float (&p0)[AM <= 8 ? AM : 1],
                                                const float* psi0s, int A, int a, float pa,
-                                               float eta, bool flat) {
+                                               float eta, bool flat, const RowBase& B) {
   auto at = [&](int j) { return j == a ? pa : (AM <= 8 ? p0[AM <= 8 ? j : 0] : psi0s[j]); };
   float m, se = 0.0f;
   if (flat) {
@@ -1060,6 +1070,16 @@ __device__ __forceinline__ float one_row_value(const float (&p0)[AM <= 8 ? AM : 
 #pragma unroll
     for (int j = 0; j < AM; ++j)
       if (j < A) se = se + (j == a ? ea : ep);
+  } else if constexpr (AM > 8) {
+    m = a < 0 ? B.m0 : fmaxf(a == B.top ? B.m1 : B.m0, pa);
+    if (m == B.m0) {
+      const float ea = expf(eta * (pa - m));
+#pragma unroll 4
+      for (int j = 0; j < A; ++j) se = se + (j == a ? ea : B.e0[j]);
+    } else {
+#pragma unroll 1
+      for (int j = 0; j < A; ++j) se = se + expf(eta * (at(j) - m));
+    }
   } else {
     m = at(0);
 #pragma unroll
@@ -1093,7 +1113,23 @@ __device__ void dev_chain(const PlanView& P, int k, int blk, int nblk, Smem& sm)
   for (int j = 0; j < kRegs; ++j) p0[j] = sm.psi0[j < A ? j : 0];
   bool flat = true;
   for (int j = 1; j < A; ++j) flat = flat && sm.psi0[j] == sm.psi0[0];
-  const float v0 = one_row_value<AM>(p0, sm.psi0, A, -1, 0.0f, eta, flat);
+  RowBase B{0.0f, 0.0f, 0, sm.e0};
+  if constexpr (AM > 8) {
+    if (!flat) {                                // uniform
+      B.m0 = -INFINITY;
+      for (int j = 0; j < A; ++j)
+        if (sm.psi0[j] > B.m0) {
+          B.m0 = sm.psi0[j];
+          B.top = j;
+        }
+      B.m1 = -INFINITY;
+      for (int j = 0; j < A; ++j)
+        if (j != B.top) B.m1 = fmaxf(B.m1, sm.psi0[j]);
+      if ((int)threadIdx.x < A) sm.e0[threadIdx.x] = expf(eta * (sm.psi0[threadIdx.x] - B.m0));
+      __syncthreads();
+    }
+  }
+  const float v0 = one_row_value<AM>(p0, sm.psi0, A, -1, 0.0f, eta, flat, B);
   const int per = (P.n_p + kBlock - 1) / kBlock;
   unsigned long long visits = 0, inner = 0, leaves = 0;
   for (int c = blk; c < k * per; c += nblk) {
@@ -1143,7 +1179,7 @@ __device__ void dev_chain(const PlanView& P, int k, int blk, int nblk, Smem& sm)
             const float r = fix_round(__uint_as_float(q[j].z), P.fix_scale, P.fix_inv);
             const float w = first ? 0.0f : fix_round(V, P.fix_scale, P.fix_inv);
             const float pa = (__uint_as_float(q[j].w) - vc) + (r + gamma * w);
-            V = one_row_value<AM>(p0, sm.psi0, A, a, pa, eta, flat);
+            V = one_row_value<AM>(p0, sm.psi0, A, a, pa, eta, flat, B);
             *reinterpret_cast<uint4*>(&T.node[id]) =
                 make_uint4(__float_as_uint(V), link, q[j].z, __float_as_uint(pa));
             ++inner;

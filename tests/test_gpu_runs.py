@@ -94,3 +94,15 @@ def test_obstacle_counts(V, orc, n_disks):
     c = np.random.default_rng(9).uniform(0.0, 10.0, size=(n_disks, 2))
     inst = dict(inst, disks=c.astype(np.float32), disk_r2=0.04)
     forced_parity(V, orc, inst, I.nav_belief(3, 128), 1500, 5, 5, seed=4)
+
+
+# Reference policies that are not uniform: one largest entry, and two.
+@pytest.mark.parametrize("nA", [5, 8, 9, 16, 17, 40, 64])
+@pytest.mark.parametrize("ties", [False, True])
+def test_runs_under_a_prior(V, orc, nA, ties):
+    inst = I.tabular_dense(31, 9, nA, 2, with_heuristic=True)
+    pi0 = np.random.default_rng(nA).uniform(0.5, 1.5, size=(nA,))
+    pi0[nA // 2] = 2.0
+    if ties:
+        pi0[nA - 1] = 2.0
+    forced_parity(V, orc, inst, I.tabular_belief(inst), 900, 4, 4, seed=6, pi0=pi0 / pi0.sum())
