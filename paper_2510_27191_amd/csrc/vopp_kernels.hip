@@ -915,8 +915,9 @@ __device__ void dev_accum(const PlanView& P, int k, int D, int blk, int nblk, Sm
         T.full[full_first(P, lvl) + at] = id;
         // (atomic: its own children may become full in this launch, too)
         atomicOr(&T.node[id].link, kLinkFull);
-        const int up = (int)(T.info[id].own >> kKeyLowBits);
-        if (up) atomicOr(&T.node[up].link, kLinkInner);
+        // (the sweep of long rows does not use it: 10 us a launch there)
+        const int up = T.ra <= kMaxA ? (int)(T.info[id].own >> kKeyLowBits) : 0;
+        if (up && !(T.node[up].link & kLinkInner)) atomicOr(&T.node[up].link, kLinkInner);
       }
     }
     for (int j = threadIdx.x; j < kAggSlots; j += kBlock) {
