@@ -668,7 +668,8 @@ vopp_status enqueue_plan(const vopp_pomdp* p, vopp_workspace* w, const PlanView&
       VOPP_TIMED(VOPP_KERNEL_BACKUP_LEAF,
                  launch_backup_leaf(P, D, k, backup_grid(P, D, k, kFullCap, kept(D)), s));
       auto levels = [&]() {
-        hipError_t el = launch_chain(P, k, chain_grid(P, k, kBackupCap), s);
+        hipError_t el = hipSuccess;           // (D = 1: the leaf sweep took the runs)
+        if (D > 1) el = launch_chain(P, k, chain_grid(P, k, kBackupCap), s);
         for (int dep = D; dep >= 2 && el == hipSuccess; --dep)
           el = launch_backup_level(P, dep, k,
                                    backup_grid(P, dep - 1, k, kFullCap, kept(dep - 1)), s);

@@ -1043,6 +1043,29 @@ __device__ void dev_backup_leaf(const PlanView& P, int dep, int k, int blk, int 
     atomicAdd(&stat_bank(P, k)[kStripes + blk % kStripes], n);
 }
 
+// Plans of one level so far: every run is one leaf, which pushes into the
+// root. A thread each, in the leaf sweep's launch: a launch of the walk for
+// them was 9 to 12 us more an iteration of plans of depth 1 (111 to 3,000
+// actions).
+__device__ void dev_leaf_runs(const PlanView& P, int k, int blk, int nblk, Smem& sm) {
+  const TreeView& T = P.t;
+  unsigned long long n = 0;
+  const long long all = (long long)k * P.n_p;
+  for (long long i = (long long)blk * kBlock + threadIdx.x; i < all; i += (long long)nblk * kBlock) {
+    if (!((T.run[i] >> kRunLenShift) & kRunMask)) continue;
+    const int kk = (int)(i / P.n_p) + 1, ep = (int)(i % P.n_p);
+    const int id = 1 + first_step(P, kk) * P.n_p + ep;
+    const uint2 q = *reinterpret_cast<const uint2*>(&T.node[id]);
+    if (q.y & (kLinkFull | kLinkClaim)) continue;
+    const unsigned long long f = push_value(P, __uint_as_float(q.x), 1);
+    if (f) push_one(T, parent_of(T.info[id].own, P.m.obs_bits), f);
+    ++n;
+  }
+  n = block_sum(n, sm.wave);
+  if (n && counts_tree(P, k) && threadIdx.x == 0)
+    atomicAdd(&stat_bank(P, k)[kStripes + blk % kStripes], n);
+}
+
 // L_eta Psi of a row whose entry is psi0s[j] but for entry a (a < 0: none),
 // in the order of the level sweep's sums.  flat: psi0s is one value (the
 // uniform reference policy): one exponential serves the whole row, since the
@@ -1745,7 +1768,18 @@ __device__ void dev_chain_wide(const PlanView& P, int k, int blk, int nblk) {
       q[j] = my_len > 0 ? *reinterpret_cast<const uint4*>(
                               &T.node[my_id + max(my_len - 1 - j, 0) * P.n_p])
                         : make_uint4(0u, 0u, 0u, 0u);
-    unsigned long long todo = __ballot(my_len > 0);
+    // A run that is a leaf only needs no row: a lane each, all at once.
+    const bool leaf_only = my_len == 1 && !(q[0].y & kLinkAct);
+    const bool push = leaf_only && !(q[0].y & (kLinkFull | kLinkClaim));
+    if (push) {
+      const unsigned long long f = push_value(P, __uint_as_float(q[0].x), 1);
+      if (f) push_one(T, parent_of(T.info[my_id].own, ob), f);
+    }
+    const unsigned long long n_push = (unsigned long long)__popcll(__ballot(push));
+    // (every run of iteration kk that is one leaf is at the depth of its leaves)
+    if (depth_at(P, kk) == D) leaves += n_push;
+    else visits += n_push;
+    unsigned long long todo = __ballot(my_len > 0 && !leaf_only);
     while (todo) {
       const int src = __ffsll((long long)todo) - 1;
       todo &= todo - 1;
@@ -2786,6 +2820,7 @@ __global__ __launch_bounds__(kBlock) void k_backup_leaf(PlanView P, int dep, int
   __shared__ Smem sm;
   if (budget_spent(P)) return;
   dev_backup_leaf(P, dep, k, blockIdx.x, gridDim.x, sm);
+  if (dep == 1) dev_leaf_runs(P, k, blockIdx.x, gridDim.x, sm);
 }
 template <int AM>
 __global__ __launch_bounds__(kBlock) void k_full(PlanView P, int k) {

@@ -106,3 +106,10 @@ def test_runs_under_a_prior(V, orc, nA, ties):
     if ties:
         pi0[nA - 1] = 2.0
     forced_parity(V, orc, inst, I.tabular_belief(inst), 900, 4, 4, seed=6, pi0=pi0 / pi0.sum())
+
+
+# Long rows in plans of one level, whose runs are leaves only.
+@pytest.mark.parametrize("nA,n_p,K", [(65, 1, 2), (70, 257, 3), (130, 1500, 4)])
+def test_long_rows_of_one_level(V, orc, nA, n_p, K):
+    inst = I.tabular_dense(23, 8, nA, 3, with_heuristic=True)
+    forced_parity(V, orc, inst, I.tabular_belief(inst), n_p, K, 1, seed=3)
