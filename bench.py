@@ -52,23 +52,25 @@ def method_bytes(kind, nA, particle_steps, n_beliefs, n_actions, sweep, leaf_vis
     return {
         "forward": particle_steps * (state + 4 * nA + 4 + 16 + 12 + 8) + n_actions * 16
                    + (n_beliefs - 1) * (12 + 8 * nA + 16),
-        "backup_level": 20 * visits + (12 * nA + 8) * internal + 20 * nodes,
-        "backup_leaf": 20 * leaf_visits,
+        "backup": 20 * visits + (12 * nA + 8) * internal + 20 * nodes + 20 * leaf_visits,
     }
 
 
-# Bytes the present layout moves for the same work (the overhead against the
-# method's bytes).  The tree is one array per field indexed by belief id (ra =
-# |A| rounded up to a multiple of 4).  A level sweep visit reads the position's
-# list entry (4), the belief's hot fields {V, N_b, parent} (16) and its visit
-# counts (4*ra), and pushes into its parent's W (16: the atomic's read and
-# write); a belief with an action node also reads and writes its preference
-# row (8*ra) and writes V and N_b (8); each action node reads C and W (16) and
-# clears W (8).
-def layout_bytes_backup_level(nA, sweep):
-    ra = (nA + 3) // 4 * 4
-    visits, internal, nodes = sweep
-    return visits * (4 + 16 + 4 * ra + 16) + internal * (8 * ra + 8) + nodes * 24
+# The launches that share a kind of work: the backup's sweeps are the walk along
+# the runs of single-visit beliefs, which one launch does together with the
+# trace (kind "accumulate"), and the sweep of the others.
+KERNEL_GROUPS = {"accumulate": "backup", "backup_level": "backup", "backup_leaf": "backup",
+                 "backup_root": "backup"}
+
+
+def grouped(prof):
+    """{group: (milliseconds, launches)} of a profile by kernel kind."""
+    out = {}
+    for k, (ms, n) in prof.items():
+        g = KERNEL_GROUPS.get(k, k)
+        a = out.get(g, (0.0, 0))
+        out[g] = (a[0] + ms, a[1] + n)
+    return out
 
 
 def leaf_sweep_visits(n_p, K, depth, counts):
@@ -509,7 +511,8 @@ def bench_plain(V, I, name, steps, warmup, event_profile, cpu):
                ws=ws, stream=stream)
     if event_profile and warmup > 0:
         warm = V.profile_read(ws)
-        dom = max((k for k in warm if k != "setup"), key=lambda k: warm[k][0])
+        by_group = grouped(warm)
+        dom = max((k for k in by_group if k != "setup"), key=lambda k: by_group[k][0])
         warm_total = sum(v[0] for v in warm.values())
         warm_share = {k: v[0] / warm_total for k, v in warm.items() if v[1]}
     # Timed region: plain plans, no event brackets.
@@ -535,7 +538,7 @@ def bench_plain(V, I, name, steps, warmup, event_profile, cpu):
     prof = None
     if dom is not None:
         V.profile_reset(ws)
-        V.profile_enable(ws, [dom])
+        V.profile_enable(ws, [k for k in warm if KERNEL_GROUPS.get(k, k) == dom])
         for i in range(steps):
             V.plan(pom, belt, n_bel, K, depth, V.params(n_p, eta=eta, seed=1000 + i),
                    ws=ws, stream=stream)
@@ -552,7 +555,7 @@ def bench_plain(V, I, name, steps, warmup, event_profile, cpu):
         "near_ties_per_plan": float(np.mean([r.near_ties for r in results])),
     }
     if prof is not None:
-        kinds = {k: v for k, v in prof.items() if v[1] > 0}
+        kinds = {k: v for k, v in grouped(prof).items() if v[1] > 0}
         out["kernel_share_warmup"] = warm_share
         roof = {"kernel": dom, "bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "traffic": None}
@@ -575,13 +578,11 @@ def bench_plain(V, I, name, steps, warmup, event_profile, cpu):
                         timing="start and end timestamps of each launch's own dispatch "
                                "(HIP events taken by hipExtLaunchKernel on the plan stream), "
                                "over the timed plans run again")
-            if dom == "backup_level":
+            if dom == "backup":
                 sw = [sum(r.sweep[i] for r in results) / launches for i in range(3)]
                 roof["units_per_launch"] = {"belief_visits": sw[0],
                                             "internal_belief_visits": sw[1],
                                             "action_node_visits": sw[2]}
-                lay = sum(layout_bytes_backup_level(pom.nA, r.sweep) for r in results)
-                roof["layout_bytes_per_launch"] = lay / launches
             tr = MEASURED_TRAFFIC.get(dom, {}).get(name)
             if tr is not None and kernel_sources_hash() == MEASURED_TRAFFIC["sources_sha256_16"]:
                 roof["traffic"] = tr
