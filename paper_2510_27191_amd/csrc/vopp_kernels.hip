@@ -716,7 +716,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
       // belief in it), so a lane that waits looks up to kPolls times (0.3 us
       // each) before it lets the turn go by, and goes on in the same turn.  With
       // one look, and the own runs' levels in level()'s branches, a launch
-      // took 31 us instead of 22 (1,024 episodes of nav2d) and 44 instead of
+      // took 31 us instead of 22 (2,048 episodes of nav2d) and 44 instead of
       // 36 (65,536).
       for (int tries = 0; tries < kPolls && __any(waits); ++tries) {
         if (waits == 1) {
