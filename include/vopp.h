@@ -298,7 +298,10 @@ vopp_status vopp_plan_anytime(const vopp_pomdp* pomdp, const void* belief_partic
  *     on dst starts from it (its root preferences, visit counts and rewards
  *     included) instead of a fresh root.  dst is re-allocated (same handle)
  *     when it is too small for the subtree plus the next plan.  Its previous
- *     tree is discarded.
+ *     tree is discarded.  A call that is refused before it starts (arguments,
+ *     sizes) leaves the subtree where it is; a plan that started uses it up,
+ *     also one that then fails (a belief particle outside [0, nS), a device
+ *     error): the plan after that starts from a fresh root.
  *   kept (host, out, may be NULL): beliefs kept, the new root included; 0
  *     when the tree has no belief for (action, obs) -- dst then holds nothing
  *     and the next plan on it starts from a fresh root.

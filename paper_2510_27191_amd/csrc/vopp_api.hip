@@ -823,6 +823,11 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   }
   e = hipEventRecord(ws->ev0, s);
   if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
+  // From here on the table is written: a plan that fails has used the kept
+  // subtree up.  (Its table would still hold this plan's beliefs, with ids and
+  // the iterations' own stamps, and an episode that met its own would wait for
+  // itself.)
+  ws->carry.pending = false;
   int steps = 0;
   st = enqueue_plan(p, ws, P, s, &steps);
   if (st != VOPP_OK) return st;
@@ -867,7 +872,6 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
       }
   for (int k = 1; k <= k_run; ++k)
     for (int d = 0; d < depth_at(P, k); ++d) ws->steps.push_back({d + 1, k - 1, 0});
-  ws->carry.pending = false;
   *action = (int32_t)o[0];
   if (values) for (int j = 0; j < A; ++j) values[j] = o[1 + j];
   if (v_root) *v_root = o[A + 1];
