@@ -201,7 +201,9 @@ void vopp_workspace_free(vopp_workspace* ws);
  *   values (host, out, may be NULL): the root preferences Psi(root, .) [nA],
  *     kept in double precision.  v_root (host, may be NULL): L_eta Psi(root).
  *   stats (host, may be NULL).
- * The call returns after the result has reached the host. */
+ * The call returns after the result has reached the host.  A plan that started
+ * and then failed leaves no tree in the workspace: until the next plan,
+ * vopp_tree_dump, vopp_level_counts and vopp_reroot refuse it. */
 vopp_status vopp_plan(const vopp_pomdp* pomdp, const void* belief_particles,
                       int32_t n_belief, int32_t budget, int32_t depth,
                       const vopp_params* params, vopp_workspace* ws,

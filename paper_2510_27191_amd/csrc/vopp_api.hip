@@ -826,8 +826,10 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   // From here on the table is written: a plan that fails has used the kept
   // subtree up.  (Its table would still hold this plan's beliefs, with ids and
   // the iterations' own stamps, and an episode that met its own would wait for
-  // itself.)
+  // itself.)  Nor does it leave a tree to dump or to re-root: the layout kept
+  // here (steps, last_*) is that of the last plan that ended well.
   ws->carry.pending = false;
+  ws->n_prev_beliefs = 0;
   int steps = 0;
   st = enqueue_plan(p, ws, P, s, &steps);
   if (st != VOPP_OK) return st;
@@ -839,7 +841,6 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   if (e != hipSuccess) return hip_fail(e, "plan execution");
   prof_collect(ws);
   const double* o = ws->out_host;
-  ws->n_prev_beliefs = (int)o[A + 3];
   const int flags = (int)o[A + 5];
   if (flags & 1) return fail(VOPP_E_INVALID, "a belief particle holds a state outside [0, nS)");
   if (flags & 2) return fail(VOPP_E_INTERNAL, "belief table overflow");

@@ -106,3 +106,31 @@ def test_refused_call_leaves_the_kept_subtree(V):
         for w in (src, one, two):
             w.close()
         pom.close()
+
+
+# A failed plan of another size than the one before it leaves no tree.
+@pytest.mark.parametrize("nA", [3, 70])
+def test_failed_plan_leaves_no_tree(V, nA):
+    inst, bel = models(nA)
+    pom = V.Pomdp.from_instance(inst)
+    b = V.belief_tensor(inst, bel)
+    p1, p2 = V.params(700, seed=2), V.params(300, seed=5)
+    ws, dst = V.Workspace(pom, p1, 4, 4), V.Workspace(pom, p1, 4, 4)
+    try:
+        r1 = V.plan(pom, b, b.numel(), 4, 4, p1, ws=ws)
+        o = top_branch(V.tree_dump(ws, nA, r1.n_beliefs, r1.n_actions), r1.action)
+        with pytest.raises(V.VoppError):
+            V.plan(pom, with_bad_state(inst, b), b.numel(), 3, 3, p2, ws=ws)
+        for use in (lambda: V.level_counts(ws),
+                    lambda: V.tree_dump(ws, nA, r1.n_beliefs, r1.n_actions),
+                    lambda: V.reroot(pom, ws, r1.action, o, p1, 4, 4, dst)):
+            with pytest.raises(V.VoppError) as e:
+                use()
+            assert e.value.status == V.VOPP_E_INVALID and "no plan" in str(e.value)
+        r = V.plan(pom, b, b.numel(), 4, 4, p1, ws=ws)
+        f = V.plan(pom, b, b.numel(), 4, 4, p1, ws=dst)
+        same_plan(V, nA, r, ws, f, dst)
+    finally:
+        ws.close()
+        dst.close()
+        pom.close()
