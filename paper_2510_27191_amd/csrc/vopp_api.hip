@@ -395,17 +395,22 @@ bool fits(const WsSizes& have, const WsSizes& need) {
          have.hcap >= need.hcap;
 }
 
+// Rows of Apad actions in arrays of cap_b beliefs.
+void set_rows(TreeView& t, int Apad, long long cap_b) {
+  t.ra = Apad;
+  t.bw = rec_bitmap_words(Apad);
+  // Rows of more than kRowSpreadMaxA actions keep their order.
+  t.row_bits = 16;
+  while (t.row_bits > kRowSpread && (cap_b >> t.row_bits) == 0) --t.row_bits;
+  t.row_end = Apad <= kRowSpreadMaxA ? (uint32_t)(cap_b >> t.row_bits << t.row_bits) : 0u;
+}
+
 // Lays out the buffers of one plan's tree (sizes z) in device memory at base,
 // bytes_for(z) of it, in the order bytes_for counts them.
 void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, double** out) {
   Carver c(base);
   const size_t cb = (size_t)z.cap_b;
-  t.ra = z.Apad;
-  t.bw = rec_bitmap_words(z.Apad);
-  // Rows longer than a memory line (the counts of 32 actions) keep their order.
-  t.row_bits = 16;
-  while (t.row_bits > kRowSpread && (cb >> t.row_bits) == 0) --t.row_bits;
-  t.row_end = z.Apad <= kRowSpreadMaxA ? (uint32_t)(cb >> t.row_bits << t.row_bits) : 0u;
+  set_rows(t, z.Apad, z.cap_b);
   t.psi = c.take<float>(cb * z.Apad);
   t.nv = c.take<int>(cb * z.Apad);
   t.cv = c.take<unsigned long long>(cb * z.Apad);
@@ -537,6 +542,9 @@ PlanView make_view(const vopp_pomdp* p, vopp_workspace* w, const void* belief,
   std::memset(&P, 0, sizeof(P));
   P.m = p->view;
   P.t = w->tree;
+  // The rows are the model's, also in a workspace made for more actions: the
+  // kernels are chosen, and their shared memory is laid out, by the model's.
+  set_rows(P.t, p->view.Apad, w->z.cap_b);
   P.e.belief = belief;
   P.e.n_belief = n_belief;
   P.n_p = prm->n_particles;
@@ -1023,7 +1031,7 @@ extern "C" vopp_status vopp_tree_dump(vopp_workspace* w, int32_t* b_parent, int3
   clear_error();
   if (!w) return fail(VOPP_E_INVALID, "null workspace");
   if (w->n_prev_beliefs <= 0) return fail(VOPP_E_INVALID, "no plan has run in this workspace");
-  const int A = w->last_A, ra = w->tree.ra, rs = dump_bytes(w->tree.ra);
+  const int A = w->last_A, ra = w->last_tree.ra, rs = dump_bytes(ra);
   const int steps = w->last_steps, n_p = w->last_n_p;
   hipError_t e = hipDeviceSynchronize();
   auto cp = [&](void* dst, const void* src, size_t bytes) {

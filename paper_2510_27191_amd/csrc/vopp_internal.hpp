@@ -102,6 +102,8 @@ vopp_status check_params(const vopp_pomdp* p, const vopp_params* prm, int32_t bu
 vopp_status ws_alloc(const WsSizes& z, vopp_workspace** out);
 vopp_status ensure_ws(const vopp_pomdp* p, vopp_workspace** ws, const vopp_params* prm,
                       int K, int depth);
+// Rows of Apad actions (a model's) in arrays of cap_b beliefs.
+void set_rows(TreeView& t, int Apad, long long cap_b);
 PlanView make_view(const vopp_pomdp* p, vopp_workspace* w, const void* belief,
                    int n_belief, int K, int depth, const vopp_params* prm);
 // Blocks of a sweep over the full beliefs of depth dep after iteration k

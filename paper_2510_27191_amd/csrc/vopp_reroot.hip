@@ -159,12 +159,11 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
       kMaxBeliefs)
     return fail(VOPP_E_INVALID, "kept subtree and plan exceed 2^28 beliefs");
 
-  // The destination must hold the kept subtree and the next plan, with the
-  // source's record layout.
+  // The destination must hold the kept subtree and the next plan (and if it is
+  // allocated anew, models as wide as either workspace held).
   WsSizes need = sizes_for(p, n_p, next_budget, next_depth, next->schedule, carry_steps);
-  need.Apad = src->z.Apad;
-  need.rs = src->z.rs;
-  if (!fits(dst->z, need) || dst->z.Apad != src->z.Apad) {
+  need.Apad = std::max({need.Apad, src->z.Apad, dst->z.Apad});
+  if (!fits(dst->z, need)) {
     vopp_workspace* grown = nullptr;
     st = ws_alloc(need, &grown);
     if (st != VOPP_OK) return st;
@@ -176,6 +175,7 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
   // Clear the table that the next plan uses, then copy.
   cy.h_mask = table_mask(n_p, (long long)next_budget + carry_steps);
   V.dst = dst->tree;
+  set_rows(V.dst, p->view.Apad, dst->z.cap_b);   // the model's rows, as in the source
   V.dst.h_mask = cy.h_mask;
   e = launch_fill16(dst->tree.h_slot, (size_t)cy.h_mask + 1, make_uint4(~0u, ~0u, ~0u, ~0u), s);
   V.dst_n_p = n_p;
