@@ -294,8 +294,8 @@ vopp_status vopp_plan_anytime(const vopp_pomdp* pomdp, const void* belief_partic
  *   src: a workspace whose last plan (vopp_plan or vopp_plan_anytime) holds
  *     the tree; it is only read.
  *   next, next_budget, next_depth: the parameters of the next plan, which
- *     runs in dst.  That plan must use next->n_particles and at most
- *     next_budget (<= 255) iterations.
+ *     runs in dst.  That plan must use a model of as many actions,
+ *     next->n_particles and at most next_budget (<= 255) iterations.
  *   dst: receives the kept subtree; the next vopp_plan or vopp_plan_anytime
  *     on dst starts from it (its root preferences, visit counts and rewards
  *     included) instead of a fresh root.  dst is re-allocated (same handle)

@@ -787,6 +787,8 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   if (dev != p->device) return fail(VOPP_E_INVALID, "model lives on device %d, current is %d", p->device, dev);
   if (ws && ws->carry.pending) {
     // The plan starts from the subtree kept by vopp_reroot.
+    if (p->nA != ws->carry.nA)
+      return fail(VOPP_E_INVALID, "the kept subtree is of a model of %d actions", ws->carry.nA);
     if (prm->n_particles != ws->carry.n_p)
       return fail(VOPP_E_INVALID, "a plan from a kept subtree must use n_particles = %d",
                   ws->carry.n_p);

@@ -54,7 +54,7 @@ struct vopp_workspace {
   // the next plan starts from it.
   struct Carry {
     bool pending = false;
-    int n_p = 0, n_steps = 0;
+    int nA = 0, n_p = 0, n_steps = 0;
     int first[vopp::kMaxDepth + 1] = {0}, count[vopp::kMaxDepth + 1] = {0};
     long long beliefs[vopp::kMaxDepth + 1] = {0}, nodes[vopp::kMaxDepth + 1] = {0};
     long long root_visits = 0;

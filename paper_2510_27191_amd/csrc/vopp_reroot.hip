@@ -136,6 +136,7 @@ extern "C" vopp_status vopp_reroot(const vopp_pomdp* p, vopp_workspace* src, int
   // source's depth d + 1, packed into ceil(count / n_p) level steps.
   const int n_p = next->n_particles;
   vopp_workspace::Carry cy;
+  cy.nA = p->nA;
   cy.n_p = n_p;
   int carry_steps = 0;
   long long kept_total = 1;

@@ -134,3 +134,33 @@ def test_failed_plan_leaves_no_tree(V, nA):
         ws.close()
         dst.close()
         pom.close()
+
+
+# A kept subtree's beliefs are named by keys whose split into action and
+# observation is the model's.
+@pytest.mark.parametrize("nA,other", [(70, 300), (300, 70), (3, 8)])
+def test_kept_subtree_of_another_model_is_refused(V, nA, other):
+    inst, bel = models(nA)
+    inst2, bel2 = models(other)
+    pom, pom2 = V.Pomdp.from_instance(inst), V.Pomdp.from_instance(inst2)
+    b, b2 = V.belief_tensor(inst, bel), V.belief_tensor(inst2, bel2)
+    p1, p2 = V.params(300, seed=2), V.params(300, seed=9)
+    big = pom if nA > other else pom2
+    src = V.Workspace(pom, p1, 3, 3)
+    dst, two = (V.Workspace(big, p2, 6, 6) for _ in range(2))
+    try:
+        r1 = V.plan(pom, b, b.numel(), 3, 3, p1, ws=src)
+        o = top_branch(V.tree_dump(src, nA, r1.n_beliefs, r1.n_actions), r1.action)
+        for w in (dst, two):
+            assert V.reroot(pom, src, r1.action, o, p2, 3, 3, w) > 1
+        with pytest.raises(V.VoppError) as e:
+            V.plan(pom2, b2, b2.numel(), 3, 3, p2, ws=dst)
+        assert e.value.status == V.VOPP_E_INVALID and "kept subtree" in str(e.value)
+        x = V.plan(pom, b, b.numel(), 3, 3, p2, ws=dst)
+        y = V.plan(pom, b, b.numel(), 3, 3, p2, ws=two)
+        same_plan(V, nA, x, dst, y, two)
+    finally:
+        for w in (src, dst, two):
+            w.close()
+        pom.close()
+        pom2.close()
