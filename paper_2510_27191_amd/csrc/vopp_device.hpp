@@ -206,7 +206,8 @@ struct TreeView {
                                  // draws and the sweeps' work, striped over
                                  // blocks so that no address takes many atomics
   unsigned long long* gate;      // [4] plans with a time budget: [0] start on
-                                 // the wall clock, [1] stop flag, [2] iterations run
+                                 // the wall clock, [1] the last iteration once
+                                 // that is decided, else 0, [2] iterations run
   const int* carry_rng;          // [kMaxDepth + 1][2] a kept subtree by depth:
                                  // first level step, beliefs (packed from there)
   unsigned long long* tr_key;    // [(depth + 1) * n_p] trace words
@@ -366,10 +367,19 @@ __device__ __forceinline__ bool counts_tree(const PlanView& P, int k) {
 __device__ __forceinline__ unsigned long long* stat_bank(const PlanView& P, int k) {
   return P.t.stats + (size_t)(1 + 2 * (P.timed ? (k & 1) : 0)) * kStripes;
 }
-// The time budget ran out at the end of an earlier iteration: the phases of
-// later iterations return at once (uniform over the grid).
-__device__ __forceinline__ bool budget_spent(const PlanView& P) {
-  return P.timed && *reinterpret_cast<const volatile unsigned long long*>(&P.t.gate[1]) != 0ull;
+// The time budget ran out at the end of an earlier iteration (`last`, 0: it
+// has not): the phases of iteration k return at once.  The root backup sets
+// `last` while blocks of its own launch may still be starting, so a launch
+// of iteration `last` itself goes on: every wavefront of a launch decides alike.
+__host__ __device__ constexpr bool plan_over(unsigned long long last, int k) {
+  return last != 0ull && last < (unsigned long long)k;
+}
+static_assert(!plan_over(0, 1) && !plan_over(0, kMaxBudget), "runs on");
+static_assert(!plan_over(3, 2) && !plan_over(3, 3), "iteration 3 runs to its end");
+static_assert(plan_over(3, 4) && plan_over(1, 2), "and none after it");
+__device__ __forceinline__ bool budget_spent(const PlanView& P, int k) {
+  return P.timed &&
+         plan_over(*reinterpret_cast<const volatile unsigned long long*>(&P.t.gate[1]), k);
 }
 
 // Result record written by the select phase (doubles): [0] action,

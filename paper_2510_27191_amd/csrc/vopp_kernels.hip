@@ -849,7 +849,7 @@ __device__ __forceinline__ unsigned long long trace_word(const PlanView& P, int 
 // sets bit a of b's bitmap and clears N[a], C[a] and W[a] (the root keeps its
 // sums elsewhere).  It runs before the accumulate pass adds the visits.
 __global__ __launch_bounds__(kBlock) void k_claim_wide(PlanView P, int k, int D) {
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   const TreeView& T = P.t;
   const long long n = (long long)D * P.n_p;
   for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n;
@@ -1520,7 +1520,7 @@ __device__ __forceinline__ void root_gate(const PlanView& P, int k, int lane) {
     const unsigned long long now = (unsigned long long)wall_clock64();
     const unsigned long long stop =
         (k >= P.K || now - P.t.gate[0] >= P.budget_ticks) ? 1ull : 0ull;
-    P.t.gate[1] = stop;
+    P.t.gate[1] = stop ? (unsigned long long)k : 0ull;
     P.t.gate[2] = (unsigned long long)k;
     __hip_atomic_store(P.gate_host, (unsigned long long)k | (stop << 32), __ATOMIC_RELEASE,
                        __HIP_MEMORY_SCOPE_SYSTEM);
@@ -2768,7 +2768,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
 __global__ __launch_bounds__(kBlock, 4) void k_forward_wide(PlanView P, int k, int D) {
   __shared__ unsigned long long red[kBlock / 64];
   __shared__ uint32_t qsum[kBlock / kHalf][kLongChunks * kHalf];
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   const int lane = threadIdx.x & (kHalf - 1);
   const int ep = blockIdx.x * (kBlock / kHalf) + (threadIdx.x / kHalf);   // uniform per half
   unsigned long long g = 0, nt = 0;
@@ -2797,46 +2797,46 @@ __global__ __launch_bounds__(kBlock) void k_setup(PlanView P) {
 template <int AM, bool NAV, bool TRACE>
 __global__ __launch_bounds__(kBlock) void k_forward(PlanView P, int k, int D) {
   __shared__ SearchSmem L;
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_forward<AM, NAV, TRACE>(P, k, D, blockIdx.x, L);
 }
 __global__ __launch_bounds__(kBlock) void k_accum(PlanView P, int k, int D) {
   __shared__ Smem sm;
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_accum(P, k, D, blockIdx.x, gridDim.x, sm);
 }
 template <int AM>
 __global__ __launch_bounds__(kBlock) void k_fold(PlanView P, int k) {
   __shared__ Smem sm;
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_fold<AM>(P, k, blockIdx.x, gridDim.x, sm);
 }
 template <int QPL>
 __global__ __launch_bounds__(kBlock) void k_chain_wide(PlanView P, int k) {
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_chain_wide<QPL>(P, k, blockIdx.x, gridDim.x);
 }
 __global__ __launch_bounds__(kBlock) void k_backup_leaf(PlanView P, int dep, int k) {
   __shared__ Smem sm;
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_backup_leaf(P, dep, k, blockIdx.x, gridDim.x, sm);
   if (dep == 1) dev_leaf_runs(P, k, blockIdx.x, gridDim.x, sm);
 }
 template <int AM>
 __global__ __launch_bounds__(kBlock) void k_full(PlanView P, int k) {
   __shared__ Smem sm;
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_full<AM>(P, k, blockIdx.x, sm);
 }
 template <int QPL>
 __global__ __launch_bounds__(kBlock) void k_backup_level_wide(PlanView P, int dep, int k) {
   __shared__ Smem sm;
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_backup_level_wide<QPL>(P, dep, k, blockIdx.x, gridDim.x, sm);
 }
 __global__ __launch_bounds__(kBlock) void k_backup_root_wide(PlanView P, int k) {
   __shared__ double buf[kBlock];
-  if (budget_spent(P)) return;
+  if (budget_spent(P, k)) return;
   dev_backup_root_wide(P, k, buf);
 }
 __global__ void k_select(PlanView P) { dev_select(P); }
