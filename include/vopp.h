@@ -187,6 +187,14 @@ vopp_status vopp_workspace_create(const vopp_pomdp* pomdp,
                                   const vopp_params* params, int32_t budget,
                                   int32_t depth, vopp_workspace** out);
 void vopp_workspace_free(vopp_workspace* ws);
+/* Test hook: bounds every wait inside the launches of later plans in `ws` to
+ * `turns` looks at what is waited for (< 0: the default, about a second).
+ * Episodes of one launch that reach the same new belief wait for the one that
+ * created it, and the sweep of a depth waits for the deeper ones.  A wait
+ * that reaches the bound ends the episode, and the plan fails with
+ * VOPP_E_INTERNAL.  With the default that happens only where something else writes
+ * to the plan's tree at the same time. */
+vopp_status vopp_workspace_wait_limit(vopp_workspace* ws, int32_t turns);
 
 /* One planning step.
  *   pomdp: the model.  belief_particles: DEVICE pointer to n_belief particles
@@ -248,11 +256,12 @@ vopp_status vopp_plan_trace(const vopp_pomdp* pomdp, const void* belief_particle
  *     the end of the plan: [0] action, [1 .. nA] root preferences, [nA+1]
  *     V(root), [nA+2] particle steps, [nA+3] beliefs, [nA+4] action nodes,
  *     [nA+5] error flags (1: a belief particle outside [0, nS); 2: internal
- *     table overflow; 0 on success), [nA+6] near-tie draws, [nA+7 .. nA+9]
- *     the sweep counts of vopp_stats.
+ *     table overflow; 4: a wait between episodes did not end; 0 on success),
+ *     [nA+6] near-tie draws, [nA+7 .. nA+9] the sweep counts of vopp_stats.
  * The result equals vopp_plan's bit for bit.  Every call on one GPU uses
  * that GPU's one array: calls that overlap on one GPU (other streams or
- * threads) race and give undefined results; calls in stream order do not.
+ * threads) race and give undefined results (the waits between episodes end
+ * after a bound, with error flag 4); calls in stream order do not.
  * Every plan clears what it reads of the array first. */
 #define VOPP_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 vopp_status vopp_plan_noalloc(const vopp_pomdp* pomdp, const void* belief_particles,

@@ -569,7 +569,14 @@ PlanView make_view(const vopp_pomdp* p, vopp_workspace* w, const void* belief,
   P.t.run = reinterpret_cast<unsigned short*>(P.t.list);
   P.t.full = P.t.list + ((size_t)K * prm->n_particles + 1) / 2;
   P.out = w->out_dev;
+  P.wait_turns = w->wait_turns;
   return P;
+}
+
+vopp_status flags_status(int flags) {
+  return (flags & (kErrTable | kErrWait)) ? VOPP_E_INTERNAL
+         : (flags & kErrState)            ? VOPP_E_INVALID
+                                          : VOPP_OK;
 }
 
 // Grid for the sweep of the full beliefs of depth `dep` after iteration k: a
@@ -852,8 +859,12 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   prof_collect(ws);
   const double* o = ws->out_host;
   const int flags = (int)o[A + 5];
-  if (flags & 1) return fail(VOPP_E_INVALID, "a belief particle holds a state outside [0, nS)");
-  if (flags & 2) return fail(VOPP_E_INTERNAL, "belief table overflow");
+  if (flags & kErrWait)
+    return fail(VOPP_E_INTERNAL, "a wait between episodes did not end (is the workspace in use "
+                                 "by two plans at a time?)");
+  if (flags & kErrState)
+    return fail(VOPP_E_INVALID, "a belief particle holds a state outside [0, nS)");
+  if (flags & kErrTable) return fail(VOPP_E_INTERNAL, "belief table overflow");
   int k_run = budget;
   const int c0 = P.carry ? ws->carry.n_steps : 0;
   if (P.timed) {
@@ -1176,6 +1187,13 @@ extern "C" vopp_status vopp_level_counts(const vopp_workspace* w, int32_t* count
       counts[t] = c;
     }
   }
+  return VOPP_OK;
+}
+
+extern "C" vopp_status vopp_workspace_wait_limit(vopp_workspace* w, int32_t turns) {
+  clear_error();
+  if (!w) return fail(VOPP_E_INVALID, "null workspace");
+  w->wait_turns = turns < 0 ? kWaitTurns : (uint32_t)turns;
   return VOPP_OK;
 }
 

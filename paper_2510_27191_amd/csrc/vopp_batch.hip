@@ -247,8 +247,7 @@ void parse_results(const vopp_batch* b, vopp_result* res) {
     r.particle_steps = (int64_t)o[A + 2];
     r.n_beliefs = (int64_t)o[A + 3];
     r.n_actions = (int64_t)o[A + 4];
-    const int flags = (int)o[A + 5];
-    r.status = (flags & 2) ? VOPP_E_INTERNAL : (flags & 1) ? VOPP_E_INVALID : VOPP_OK;
+    r.status = flags_status((int)o[A + 5]);
   }
 }
 

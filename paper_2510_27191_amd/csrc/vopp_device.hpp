@@ -89,6 +89,19 @@ constexpr uint32_t kRunLenShift = 7;
 constexpr uint32_t kRunMask = 127u;
 constexpr uint32_t kRunLeaf = 1u << 14;     // the episode ended at an existing leaf
 
+// Error flags of a plan (counters[1], then the result record).
+enum : unsigned int {
+  kErrState = 1,             // a belief particle outside [0, nS)
+  kErrTable = 2,             // no free slot in the belief table
+  kErrWait = 4               // a wait inside a launch did not end
+};
+// Turns a wait inside a launch may take: about a second.  The longest that a
+// sound tree asks for is a few hundred microseconds (another episode's run, the
+// full beliefs of one depth).  Two plans that write one tree at a time can leave
+// an episode waiting for an id that nobody will publish: that has to end in an
+// error, not in a launch that never does.
+constexpr uint32_t kWaitTurns = 1u << 20;
+
 enum : uint32_t { kTagRoot = 1, kTagStep = 2, kTagEnv = 4, kTagPF = 5, kTagResample = 6 };
 enum : int { kTabular = 0, kNav = 1 };
 
@@ -336,6 +349,7 @@ struct PlanView {
   // the level steps before the plan's own, listed by depth in t.carry_rng.
   int carry;
   int short_out;           // the result record ends at A + 9
+  uint32_t wait_turns;     // bound of every wait inside a launch (kWaitTurns)
   FilterView f;            // served episodes only
 };
 

@@ -68,6 +68,7 @@ struct vopp_workspace {
   unsigned long long* gate_host = nullptr;
   unsigned long long* gate_dev = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  uint32_t wait_turns = vopp::kWaitTurns;
   int n_prev_beliefs = 0, n_prev_actions = 0;
   int last_A = 0, last_apad = 0, last_steps = 0, last_n_p = 0, last_K = 0,
       last_depth = 0, last_schedule = 0;
@@ -95,6 +96,8 @@ std::vector<Phase> plan_phases(const vopp_pomdp* p, const PlanView& P, int accum
 
 vopp_status fail(vopp_status st, const char* fmt, ...);
 vopp_status hip_fail(hipError_t e, const char* what);
+// The status that a plan's error flags stand for.
+vopp_status flags_status(int flags);
 void clear_error();
 int sum_depths(int K, int depth, int schedule);
 vopp_status check_params(const vopp_pomdp* p, const vopp_params* prm, int32_t budget,

@@ -428,6 +428,14 @@ __device__ __forceinline__ uint4 load_seen(const BeliefNode* p) {
       __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
 }
+// Whether a wait of this launch that has taken `turns` turns is given up: it
+// reached its bound, or another wait of the plan has.
+__device__ __forceinline__ bool wait_over(const PlanView& P, uint32_t turns) {
+  if (turns > P.wait_turns) return true;
+  return (turns & 1023u) == 0u &&
+         (__hip_atomic_load(&P.t.counters[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
+          kErrWait);
+}
 // Every store of this wavefront so far has reached the point all XCDs see.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -443,6 +451,8 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // (TreeView::run, zero until the owner has ended) says that the run is
 // complete.  Owners run already and wait for nothing, and a turn of the loop
 // moves every other lane of the wavefront on as well, so every wait ends.
+// (P.wait_turns bounds them all the same, for a tree that something else wrote
+// to: the episode then ends where it waits and the plan reports an error.)
 //
 // Bound by dependent accesses while the episode visits beliefs of the
 // tree (node and row, table line, compare-and-swap: 2 to 3 levels of them),
@@ -609,7 +619,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
       int old = -1;
       h = probe(T, line, bk, stamp, won, fresh, old);
       if (h == ~0u) {                         // table full: stop and report
-        atomicOr((unsigned int*)&T.counters[1], 2u);
+        atomicOr((unsigned int*)&T.counters[1], kErrTable);
         alive = false;
         tl = d + 1;
       } else if (won) {
@@ -694,7 +704,16 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
   // The loop ends for the whole wavefront at once, so that a lane that has ended
   // has published its run before any lane of the wavefront waits again.
   bool done = false;
+  uint32_t turns = 0;         // of the wavefront, with a lane that waits
   do {
+    if (__any(waits) && wait_over(P, ++turns)) {
+      if (waits) {            // levels 0 .. d - 1 are in the trace
+        atomicOr((unsigned int*)&T.counters[1], kErrWait);
+        waits = 0;
+        alive = false;
+        tl = d;
+      }
+    }
     if (to_publish == 2) {
       stores_done();
       __hip_atomic_store(&T.h_slot[slot].id, id_head, __ATOMIC_RELAXED,
@@ -797,7 +816,7 @@ __device__ __forceinline__ Episode at_root(const PlanView& P, int k, int ep, boo
   if (P.m.kind == kTabular) {
     e.s = ((const int*)P.e.belief)[idx];
     if ((unsigned)e.s >= (unsigned)P.m.nS) {   // caller's particle out of range
-      if (report) atomicOr((unsigned int*)&P.t.counters[1], 1u);
+      if (report) atomicOr((unsigned int*)&P.t.counters[1], kErrState);
       e.s = 0;
     }
   } else {
@@ -1467,8 +1486,17 @@ __device__ void dev_full(const PlanView& P, int k, int blk, Smem& sm) {
     const int dep = D - 1 - l;                    // D: the leaves
     if (dep == 0 && item > first) break;          // past the root: uniform
     auto wait = [&]() {
-      if (threadIdx.x == 0 && first > 0)
-        while (read_shared(&T.counters[3]) < (unsigned long long)first) __builtin_amdgcn_s_sleep(1);
+      if (threadIdx.x == 0 && first > 0) {
+        uint32_t turns = 0;
+        while (read_shared(&T.counters[3]) < (unsigned long long)first) {
+          if (wait_over(P, ++turns)) {            // ends every wait of this launch
+            atomicOr((unsigned int*)&T.counters[1], kErrWait);
+            atomicAdd(&T.counters[3], 1ull << 32);
+          } else {
+            __builtin_amdgcn_s_sleep(1);
+          }
+        }
+      }
       __syncthreads();
     };
     if (dep == 0) {
@@ -2652,7 +2680,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
       fresh = __shfl(fresh, 0, kHalf);
       old = __shfl(old, 0, kHalf);
       if (h == ~0u) {
-        if (lane == 0) atomicOr((unsigned int*)&T.counters[1], 2u);
+        if (lane == 0) atomicOr((unsigned int*)&T.counters[1], kErrTable);
         alive = false;
         tl = d + 1;
       } else if (won) {
@@ -2728,7 +2756,16 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
   // The loop ends for the whole wavefront at once, so that a lane that has ended
   // has published its run before any lane of the wavefront waits again.
   bool done = false;
+  uint32_t turns = 0;         // of the wavefront, with a half that waits
   do {
+    if (__any(waits) && wait_over(P, ++turns)) {
+      if (waits) {            // levels 0 .. d - 1 are in the trace
+        if (lane == 0) atomicOr((unsigned int*)&T.counters[1], kErrWait);
+        waits = 0;
+        alive = false;
+        tl = d;
+      }
+    }
     if (to_publish == 2) {
       stores_done();
       if (lane == 0)

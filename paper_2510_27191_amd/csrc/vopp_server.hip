@@ -233,8 +233,7 @@ vopp_status harvest_one(vopp_server* s, bool wait) {
     v.episode = id;
     v.step = e.step;
     v.action = (int32_t)o[0];
-    const int flags = (int)o[A + 5];
-    v.status = (flags & 2) ? VOPP_E_INTERNAL : (flags & 1) ? VOPP_E_INVALID : VOPP_OK;
+    v.status = flags_status((int)o[A + 5]);
     v.v_root = o[A + 1];
     v.particle_steps = (int64_t)o[A + 2];
     v.arrival_s = e.arrival;

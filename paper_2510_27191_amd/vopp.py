@@ -29,7 +29,8 @@ EXPORTS = (
     "vopp_last_error", "vopp_version", "vopp_pomdp_tabular", "vopp_pomdp_nav2d",
     "vopp_pomdp_num_actions", "vopp_pomdp_set_reference_policy", "vopp_pomdp_free",
     "vopp_plan_footprint",
-    "vopp_workspace_create", "vopp_workspace_free", "vopp_plan", "vopp_plan_anytime",
+    "vopp_workspace_create", "vopp_workspace_free", "vopp_workspace_wait_limit",
+    "vopp_plan", "vopp_plan_anytime",
     "vopp_reroot",
     "vopp_tree_dump", "vopp_level_counts", "vopp_profile_enable", "vopp_profile_reset",
     "vopp_profile_read", "vopp_batch_create", "vopp_batch_footprint",
@@ -155,6 +156,8 @@ def lib():
     L.vopp_workspace_create.restype = st
     L.vopp_workspace_free.argtypes = [vp]
     L.vopp_workspace_free.restype = None
+    L.vopp_workspace_wait_limit.argtypes = [vp, i32]
+    L.vopp_workspace_wait_limit.restype = st
     L.vopp_plan.argtypes = [vp, vp, i32, i32, i32, C.POINTER(vopp_params), vp, vp,
                             C.POINTER(i32), vp, vp, C.POINTER(vopp_stats)]
     L.vopp_plan.restype = st
@@ -301,6 +304,10 @@ class Workspace:
         _check(lib().vopp_workspace_create(pomdp.handle, C.byref(prm), int(budget),
                                            int(depth), C.byref(h)))
         self.handle = h
+
+    def wait_limit(self, turns):
+        """Test hook: bound the waits inside the launches of later plans."""
+        _check(lib().vopp_workspace_wait_limit(self.handle, int(turns)))
 
     def close(self):
         if self.handle:

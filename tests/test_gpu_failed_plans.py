@@ -164,3 +164,31 @@ def test_kept_subtree_of_another_model_is_refused(V, nA, other):
             w.close()
         pom.close()
         pom2.close()
+
+
+# Waits inside a launch are bounded: with a bound of no turns at all, a plan in which
+# episodes share new beliefs ends with an error, and so do its launches.
+@pytest.mark.parametrize("nA,n_p", [(2, 64), (2, 2500), (16, 1500), (64, 900), (70, 900)])
+@pytest.mark.parametrize("schedule", [0, 1])
+def test_waits_are_bounded(V, nA, n_p, schedule):
+    inst = I.tabular_dense(21, 7, nA, 1, with_heuristic=True)
+    bel = I.tabular_belief(inst)
+    pom = V.Pomdp.from_instance(inst)
+    b = V.belief_tensor(inst, bel)
+    prm = V.params(n_p, seed=2, schedule=schedule)
+    ws, ref = V.Workspace(pom, prm, 5, 5), V.Workspace(pom, prm, 5, 5)
+    try:
+        ws.wait_limit(0)
+        with pytest.raises(V.VoppError) as e:
+            V.plan(pom, b, b.numel(), 5, 5, prm, ws=ws)
+        assert e.value.status == V.VOPP_E_INTERNAL and "wait" in str(e.value)
+        with pytest.raises(V.VoppError):
+            V.level_counts(ws)
+        ws.wait_limit(-1)
+        r = V.plan(pom, b, b.numel(), 5, 5, prm, ws=ws)
+        f = V.plan(pom, b, b.numel(), 5, 5, prm, ws=ref)
+        same_plan(V, nA, r, ws, f, ref)
+    finally:
+        ws.close()
+        ref.close()
+        pom.close()
