@@ -565,6 +565,7 @@ PlanView make_view(const vopp_pomdp* p, vopp_workspace* w, const void* belief,
   P.schedule = prm->schedule;
   P.carry_steps = carry ? w->carry.n_steps : 0;
   P.carry = carry ? 1 : 0;
+  for (double b = p->branch; P.crowd < depth && b * kCrowd <= P.n_p; b *= p->branch) ++P.crowd;
   P.t.h_mask = carry ? w->carry.h_mask : table_mask(prm->n_particles, K);
   P.t.run = reinterpret_cast<unsigned short*>(P.t.list);
   P.t.full = P.t.list + ((size_t)K * prm->n_particles + 1) / 2;
