@@ -88,6 +88,8 @@ constexpr uint32_t kLinkInner = 1u << 31;   // full, and so is a child of it
 constexpr uint32_t kRunLenShift = 7;
 constexpr uint32_t kRunMask = 127u;
 constexpr uint32_t kRunLeaf = 1u << 14;     // the episode ended at an existing leaf
+constexpr uint32_t kRunOpen = 1u << 15;     // the episode goes on: its beliefs above
+                                            // this level are written
 
 // Error flags of a plan (counters[1], then the result record).
 enum : unsigned int {
@@ -204,8 +206,8 @@ struct TreeView {
                                  // episode passes through one of them)
   double* v_root;                // [1]
   int* list;                     // [steps * n_p] words holding run and full:
-  unsigned short* run;           // [K * n_p] runs by (iteration, episode), 0 until
-                                 // the episode has ended
+  unsigned short* run;           // [K * n_p] runs by (iteration, episode): 0 at
+                                 // first, then kRunOpen while its run grows
   int* full;                     // full beliefs by depth (full_first); a full
                                  // belief has two visits or more, so half the
                                  // level steps' episodes bound them
