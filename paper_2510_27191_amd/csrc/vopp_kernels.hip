@@ -438,16 +438,17 @@ __device__ __forceinline__ void make_full(const PlanView& P, const float* psi0s,
 
 // Whether the caller is the first to reach the single-visit belief id besides
 // its creator (link: its record's flags as read; a full or claimed one: no).
-__device__ __forceinline__ bool claim(const TreeView& T, int id, uint32_t link) {
+__device__ __forceinline__ bool claim(const TreeView& T, int id, uint32_t link,
+                                      uint32_t more = 0u) {
   if (id == 0 || (link & (kLinkFull | kLinkClaim))) return false;
-  return !(atomicOr(&T.node[id].link, kLinkClaim) & kLinkClaim);
+  return !(atomicOr(&T.node[id].link, kLinkClaim | more) & kLinkClaim);
 }
 // claim() by a lane per episode.
 __device__ __forceinline__ bool claim_lanes(const TreeView& T, int id, uint32_t link,
-                                            bool crowd) {
+                                            bool crowd, uint32_t more = 0u) {
   const bool want = id != 0 && !(link & (kLinkFull | kLinkClaim));
   const int lead = lead_lane(want && crowd, (unsigned long long)(uint32_t)id);
-  return want && lead == (int)(threadIdx.x & 63) && claim(T, id, link);
+  return want && lead == (int)(threadIdx.x & 63) && claim(T, id, link, more);
 }
 
 // Stores and loads that pass the caches of this XCD: what an episode's run
@@ -924,29 +925,146 @@ __device__ __forceinline__ unsigned long long trace_word(const PlanView& P, int 
   return has ? P.t.tr_key[(size_t)lvl * (size_t)P.n_p + ep] : kEmptyKey;
 }
 
-// Long rows: the first visit of each (b, a) in the trace of an iteration
-// sets bit a of b's bitmap and clears N[a], C[a] and W[a] (the root keeps its
-// sums elsewhere).  It runs before the accumulate pass adds the visits.
+// The parent and key of belief id (link: its record's) once its run is
+// complete: inside a run, the belief before it.
+__device__ __forceinline__ unsigned long long own_of(const TreeView& t, int id, uint32_t link,
+                                                     int n_p) {
+  if (link & (kLinkHead | kLinkClaim | kLinkFull)) return t.info[id].own;
+  const int par = id - n_p;
+  return ((unsigned long long)(uint32_t)par << kKeyLowBits) | (t.node[par].link & kLinkKey);
+}
+// The action of a single-visit belief's one node, or -1.
+__device__ __forceinline__ int one_action(uint32_t link, int ob) {
+  return (link & kLinkAct) ? (int)((link & kLinkKey) >> ob) : -1;
+}
+// A long-row belief that becomes full (make_full), by one lane: its action node
+// (the other columns are cleared by their first visit) and the rest but Psi and the
+// bitmap.
+__device__ __forceinline__ void make_full_node(const PlanView& P, int id, uint32_t link, float r,
+                                               unsigned long long own, bool fresh) {
+  const TreeView& T = P.t;
+  const int a = one_action(link, P.m.obs_bits);
+  const unsigned long long fx = to_fix(r, P.fix_scale);
+  if (a >= 0) {
+    rec_n(T, id)[a] = 1;
+    rec_c(T, id)[a] = fx;
+    rec_w(T, id)[a] = 0ull;
+  }
+  const bool leaf = fresh && a < 0;
+  if (!(link & kLinkHead)) T.info[id] = BeliefInfo{leaf ? 1 : 0, 1, own};
+  else if (leaf) atomicAdd(&T.info[id].leaf_cnt, 1);
+  if (a < 0) T.node[id].u.leaf_h = leaf ? fx : 0ull;
+}
+// Quad i of a long row, with psi as the row's entry a (a < 0: none).
+__device__ __forceinline__ float4 with_entry(float4 v, int i, int a, float psi) {
+  if (a >> 2 == i) {
+    if ((a & 3) == 0) v.x = psi;
+    if ((a & 3) == 1) v.y = psi;
+    if ((a & 3) == 2) v.z = psi;
+    if ((a & 3) == 3) v.w = psi;
+  }
+  return v;
+}
+// The bitmap of such a belief, by W lanes.
+template <int W>
+__device__ __forceinline__ void store_bits(const TreeView& T, int id, int a, int lane) {
+  uint32_t* bits = rec_bits(T, id);
+  for (int i = lane; i < T.bw; i += W) bits[i] = a >> 5 == i ? 1u << (a & 31) : 0u;
+}
+
+// Long rows.  The first visit of each (b, a) in the trace of an iteration sets bit
+// a of b's bitmap and clears N[a], C[a] and W[a] (the root keeps its sums
+// elsewhere).  A leaf's visits come as its table slot or its id: here the first
+// one besides its creator's makes it full, and the word becomes the id.  (In the
+// search an episode would wait for a new leaf's creator, read the leaf's
+// record and set its flag, one after the other, only to end there; and once the
+// policy leans to one action, most episodes set one flag.  Four iterations to
+// depth 2, 16,384 episodes: 364 us that way, 335 this way with 65 actions, 1,058
+// and 1,029 with 3,000.)  All of it before the accumulate pass adds the visits.
+// Blocks 0 .. claim_visit_blocks - 1 take the visits of (b, a), the others the
+// leaves, claim_leaves episodes a wavefront: the wavefront writes the rows of
+// the leaves it makes full, so there are few to each, unless they stay bare.
+__host__ __device__ inline int claim_visit_blocks(int n_p, int D) {
+  const long long b = ((long long)D * n_p + kBlock - 1) / kBlock;
+  return (int)(b < (1 << 16) ? b : 1 << 16);
+}
+__host__ __device__ inline int claim_leaves(const PlanView& P, int D) {
+  return D == P.depth ? 64 : 8;
+}
 __global__ __launch_bounds__(kBlock) void k_claim_wide(PlanView P, int k, int D) {
   if (budget_spent(P, k)) return;
   const TreeView& T = P.t;
-  const long long n = (long long)D * P.n_p;
-  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n;
-       i += (long long)gridDim.x * kBlock) {
-    const int lvl = (int)(i / P.n_p);
-    const unsigned long long tk = trace_word(P, k, D, lvl, (int)(i - (long long)lvl * P.n_p));
-    if (tk == kEmptyKey) continue;
-    const unsigned long long body = tk & ~kTraceClaim;
-    const int id = (int)(body >> kActBits);
-    if (id == 0) continue;
-    const int a = (int)(body & kActMask);
-    const uint32_t bit = 1u << (a & 31);
-    if (!(atomicOr(&rec_bits(T, id)[a >> 5], bit) & bit)) {
-      rec_n(T, id)[a] = 0;
-      rec_c(T, id)[a] = 0ull;
-      rec_w(T, id)[a] = 0ull;
+  const int first_new = 1 + first_step(P, k) * P.n_p;
+  const int lane = threadIdx.x & 63;
+  const int visit_blocks = claim_visit_blocks(P.n_p, D);
+  if ((int)blockIdx.x < visit_blocks) {
+    const long long n = (long long)D * P.n_p;
+    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n;
+         i += (long long)visit_blocks * kBlock) {
+      const int lvl = (int)(i / P.n_p);
+      const unsigned long long tk = trace_word(P, k, D, lvl, (int)(i - (long long)lvl * P.n_p));
+      if (tk == kEmptyKey) continue;
+      const unsigned long long body = tk & ~kTraceClaim;
+      const int id = (int)(body >> kActBits);
+      if (id == 0) continue;
+      const int a = (int)(body & kActMask);
+      const uint32_t bit = 1u << (a & 31);
+      if (!(atomicOr(&rec_bits(T, id)[a >> 5], bit) & bit)) {
+        rec_n(T, id)[a] = 0;
+        rec_c(T, id)[a] = 0ull;
+        rec_w(T, id)[a] = 0ull;
+      }
     }
+    return;
   }
+  const int per = claim_leaves(P, D);
+  const int ep =
+      (((int)blockIdx.x - visit_blocks) * (kBlock / 64) + (int)(threadIdx.x >> 6)) * per + lane;
+  unsigned long long tk = kEmptyKey;
+  if (lane < per && ep < P.n_p) tk = trace_word(P, k, D, D, ep);
+  int id = 0;
+  uint4 q = make_uint4(0u, 0u, 0u, 0u);
+  if (tk != kEmptyKey) {
+    id = (tk & kTraceSlot) ? max(T.h_slot[tk & ~kTraceSlot].id, 0) : (int)tk;
+    q = *reinterpret_cast<const uint4*>(&T.node[id]);
+  }
+  // (a leaf at the plan's full depth never draws an action: it needs no row)
+  const bool bare = D == P.depth && !(q.y & kLinkAct);
+  const bool first = claim_lanes(T, id, q.y, true, bare ? kLinkBare : 0u);
+  if (first || (tk != kEmptyKey && (tk & kTraceSlot)))
+    T.tr_key[(size_t)D * (size_t)P.n_p + ep] =
+        (unsigned long long)(uint32_t)id | (first ? kTraceClaim : 0ull);
+  if (first)
+    make_full_node(P, id, q.y, __uint_as_float(q.z), own_of(T, id, q.y, P.n_p), id >= first_new);
+  const unsigned long long all = __ballot(first && !bare);
+  if (!all) return;                             // uniform
+  const int a = one_action(q.y, P.m.obs_bits);
+  const auto each = [&](auto f) {
+    for (unsigned long long m = all; m; m &= m - 1) {
+      const int src = __ffsll((long long)m) - 1;
+      f((int)__builtin_amdgcn_readlane(id, src), (int)__builtin_amdgcn_readlane(a, src),
+        __uint_as_float(__builtin_amdgcn_readlane(q.w, src)));
+    }
+  };
+  // A lane reads N quads of the initial row, then stores them to one belief after
+  // the other, so no load waits behind a store.
+  constexpr int N = 8;
+  const int nq = T.ra / 4;
+  for (int i0 = lane; i0 < (nq + 63) / 64 * 64; i0 += 64 * N) {   // uniform
+    float4 v[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      v[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (i0 + 64 * u < nq) v[u] = reinterpret_cast<const float4*>(T.psi0)[i0 + 64 * u];
+    }
+    each([&](int b, int ba, float psi) {
+      float4* p = reinterpret_cast<float4*>(rec_psi(T, b));
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+        if (i0 + 64 * u < nq) p[i0 + 64 * u] = with_entry(v[u], i0 + 64 * u, ba, psi);
+    });
+  }
+  each([&](int b, int ba, float) { store_bits<64>(T, b, ba, lane); });
 }
 
 __device__ void dev_accum(const PlanView& P, int k, int D, int blk, int nblk, Smem& sm) {
@@ -967,7 +1085,9 @@ __device__ void dev_accum(const PlanView& P, int k, int D, int blk, int nblk, Sm
     const int wv = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) sm.wave[wv] = (unsigned long long)__popcll(cm);
     const unsigned long long body = tk & ~kTraceClaim;
-    const int id = (int)(leaf ? body : body >> kActBits);
+    int id = (int)(leaf ? body : body >> kActBits);
+    if (leaf && has && (body & kTraceSlot))        // (a plan of one level)
+      id = max(T.h_slot[body & ~kTraceSlot].id, 0);
     float v = 0.0f;
     if (has) v = T.tr_val[(size_t)lvl * (size_t)P.n_p + ep];
     agg_clear(G);
@@ -1077,6 +1197,24 @@ __device__ __forceinline__ int full_id(const FullSet& s, int i) {
   return i < s.n_kept ? s.kept0 + i : s.ids[i - s.n_kept];
 }
 
+// Value and visits of full leaf b, read as q and in: with visits in this
+// iteration, their mean heuristic and count.
+__device__ __forceinline__ void leaf_value(const PlanView& P, int b, const uint4& q,
+                                           const BeliefInfo& in, float& V, int& N) {
+  const TreeView& T = P.t;
+  V = __uint_as_float(q.x);
+  N = in.Nb;
+  if (in.leaf_cnt > 0) {
+    const unsigned long long hs = ((unsigned long long)q.w << 32) | q.z;
+    V = from_fix(hs, P.fix_inv) / (float)in.leaf_cnt;
+    N = in.leaf_cnt;
+    T.node[b].V = V;
+    T.info[b].Nb = N;
+    T.info[b].leaf_cnt = 0;
+    if (hs) T.node[b].u.leaf_h = 0ull;
+  }
+}
+
 // Full leaves of this iteration take count and mean heuristic; every full
 // belief of depth D pushes V*N_b to its parent action.  Beliefs base ..
 // base + kBlock - 1 of the set; every thread of the block calls.
@@ -1091,17 +1229,9 @@ __device__ __forceinline__ void full_leaves(const PlanView& P, const FullSet& S,
     const int b = full_id(S, i);
     const uint4 nq = *reinterpret_cast<const uint4*>(&T.node[b]);
     const BeliefInfo in = T.info[b];
-    float V = __uint_as_float(nq.x);
-    int N = in.Nb;
-    if (in.leaf_cnt > 0) {
-      const unsigned long long hs = ((unsigned long long)nq.w << 32) | nq.z;
-      V = from_fix(hs, P.fix_inv) / (float)in.leaf_cnt;
-      N = in.leaf_cnt;
-      T.node[b].V = V;
-      T.info[b].Nb = N;
-      T.info[b].leaf_cnt = 0;
-      if (hs) T.node[b].u.leaf_h = 0ull;
-    }
+    float V;
+    int N;
+    leaf_value(P, b, nq, in, V, N);
     target = parent_of(in.own, P.m.obs_bits);
     f = push_value(P, V, N);
   }
@@ -1122,22 +1252,29 @@ __device__ void dev_backup_leaf(const PlanView& P, int dep, int k, int blk, int 
     atomicAdd(&stat_bank(P, k)[kStripes + blk % kStripes], n);
 }
 
-// Plans of one level so far: every run is one leaf, which pushes into the
-// root. A thread each, in the leaf sweep's launch: a launch of the walk for
+// Iterations of one level over long rows: every run is one leaf, which pushes into
+// the root.  A thread each, in the leaf sweep's launch: a launch of the walk for
 // them was 9 to 12 us more an iteration of plans of depth 1 (111 to 3,000
 // actions).
 __device__ void dev_leaf_runs(const PlanView& P, int k, int blk, int nblk, Smem& sm) {
   const TreeView& T = P.t;
+  const bool all_full = one_level(P);
   unsigned long long n = 0;
   const long long all = (long long)k * P.n_p;
   for (long long i = (long long)blk * kBlock + threadIdx.x; i < all; i += (long long)nblk * kBlock) {
-    if (!((T.run[i] >> kRunLenShift) & kRunMask)) continue;
     const int kk = (int)(i / P.n_p) + 1, ep = (int)(i % P.n_p);
     const int id = 1 + first_step(P, kk) * P.n_p + ep;
-    const uint2 q = *reinterpret_cast<const uint2*>(&T.node[id]);
-    if (q.y & (kLinkFull | kLinkClaim)) continue;
-    const unsigned long long f = push_value(P, __uint_as_float(q.x), 1);
-    if (f) push_one(T, parent_of(T.info[id].own, P.m.obs_bits), f);
+    // All reads at once; of no belief, if the run word says that there is none.
+    const uint32_t run = T.run[i];
+    const uint4 q = *reinterpret_cast<const uint4*>(&T.node[id]);
+    const BeliefInfo in = T.info[id];
+    if (!((run >> kRunLenShift) & kRunMask)) continue;
+    float V = __uint_as_float(q.x);
+    int N = 1;
+    if (all_full) leaf_value(P, id, q, in, V, N);
+    else if (q.y & (kLinkFull | kLinkClaim)) continue;
+    const unsigned long long f = push_value(P, V, N);
+    if (f) push_one(T, parent_of(in.own, P.m.obs_bits), f);
     ++n;
   }
   n = block_sum(n, sm.wave);
@@ -2528,14 +2665,7 @@ __device__ int draw_long_row(const float* __restrict__ row, int a1, float p1, in
   // evaluated again.
   const float4* r4 = reinterpret_cast<const float4*>(row);
   auto read = [&](int q) {
-    float4 v = r4[q];
-    if (a1 >> 2 == q) {
-      if ((a1 & 3) == 0) v.x = p1;
-      if ((a1 & 3) == 1) v.y = p1;
-      if ((a1 & 3) == 2) v.z = p1;
-      if ((a1 & 3) == 3) v.w = p1;
-    }
-    return v;
+    return with_entry(r4[q], q, a1, p1);
   };
   const int nq = (A + 3) / 4;
   const int nc = (nq + kHalf - 1) / kHalf;
@@ -2606,43 +2736,8 @@ __device__ int draw_long_row(const float* __restrict__ row, int a1, float p1, in
   return A - 1;
 }
 
-// The rows of a long-row belief that becomes full, by the half (make_full):
-// Psi, the bitmap and the one action node it has; the other columns are
-// cleared by their first visit.
-__device__ __forceinline__ void make_full_wide(const PlanView& P, int id, uint32_t link, float r,
-                                               float psi, unsigned long long own, bool fresh,
-                                               int lane) {
-  const TreeView& T = P.t;
-  const int a = (link & kLinkAct) ? (int)((link & kLinkKey) >> P.m.obs_bits) : -1;
-  float4* q = reinterpret_cast<float4*>(rec_psi(T, id));
-  const float4* p0 = reinterpret_cast<const float4*>(T.psi0);
-  for (int i = lane; i < T.ra / 4; i += kHalf) {
-    float4 v = p0[i];
-    if (a >> 2 == i) {
-      if ((a & 3) == 0) v.x = psi;
-      if ((a & 3) == 1) v.y = psi;
-      if ((a & 3) == 2) v.z = psi;
-      if ((a & 3) == 3) v.w = psi;
-    }
-    q[i] = v;
-  }
-  uint32_t* bits = rec_bits(T, id);
-  for (int i = lane; i < T.bw; i += kHalf) bits[i] = a >> 5 == i ? 1u << (a & 31) : 0u;
-  if (lane == 0) {
-    const unsigned long long fx = to_fix(r, P.fix_scale);
-    if (a >= 0) {
-      rec_n(T, id)[a] = 1;
-      rec_c(T, id)[a] = fx;
-      rec_w(T, id)[a] = 0ull;
-    }
-    const bool leaf = fresh && a < 0;
-    if (!(link & kLinkHead)) T.info[id] = BeliefInfo{leaf ? 1 : 0, 1, own};
-    else if (leaf) atomicAdd(&T.info[id].leaf_cnt, 1);
-    if (a < 0) T.node[id].u.leaf_h = leaf ? fx : 0ull;
-  }
-}
-
 // search() on half a wavefront: the episode's state is the same in every lane.
+template <bool ONE>
 __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episode& e0,
                             uint32_t* qs, unsigned long long& g, unsigned long long& nt) {
   const TreeView& T = P.t;
@@ -2652,10 +2747,10 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
   const int A = P.m.nA, ob = P.m.obs_bits;
   const size_t n_p = (size_t)P.n_p;
   const unsigned long long stamp = (unsigned long long)(k - 1) << kStampShift;
-  int s = e0.s, id = 0, d = 0;
+  int s = e0.s, d = 0;
+  int id = 0;                 // < 0: of a leaf known by its table slot ~id
   uint32_t link = 0;
   float nr = 0.0f, npsi = 0.0f;
-  unsigned long long own = 0;
   auto arrive = [&]() {
     uint4 q;
     if (id >= first_new) q = load_seen(&T.node[id]);
@@ -2666,7 +2761,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
   };
   bool tail = false;
   uint32_t head = 0;
-  int tl = 0;
+  int tl = 0;                 // (1 also for the creator of a leaf of a plan of one level)
   uint32_t slot = 0;
   int id_head = 0, to_publish = 0, waits = 0;
   bool alive = true;
@@ -2719,16 +2814,15 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
     const int b = id;
     const uint32_t blink = link;
     const float b_r = nr, b_psi = npsi;
-    const unsigned long long b_own = own;
     const unsigned long long bk = belief_key(b, low);
     int first = 0;
     if (lane == 0) first = claim(T, b, blink);
     int won = 0, fresh = 0, old = -1;
     uint32_t h = 0;
+    const bool to_leaf = d + 1 == D;            // k_claim_wide sees to it
     if ((blink & kLinkChild) && (blink & kLinkKey) == low) {
       id = b + P.n_p;
-      own = bk;
-      if (b >= first_new) waits = 2;
+      if (b >= first_new && !to_leaf) waits = 2;
     } else {
       // AppendBeliefs by lane 0 of the half; the outcome goes to the half.
       if (lane == 0) {
@@ -2747,6 +2841,18 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
         if (lane == 0) atomicOr((unsigned int*)&T.counters[1], kErrTable);
         alive = false;
         tl = d + 1;
+      } else if (ONE && won) {
+        id = 1 + t0 * P.n_p + ep;
+        tl = 1;
+        if (lane == 0) {
+          T.h_slot[h].id = id;                  // (read by later launches only)
+          BeliefNode nb;
+          nb.V = 0.0f;
+          nb.link = kLinkFull | kLinkBare;
+          nb.u.leaf_h = 0ull;
+          T.node[id] = nb;
+          T.info[id] = BeliefInfo{0, 0, bk};
+        }
       } else if (won) {
         tail = true;
         head = kLinkHead;
@@ -2755,6 +2861,8 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
         id_head = id;
         slot = h;
         to_publish = 1;
+      } else if (fresh && to_leaf) {
+        id = ~(int)h;
       } else if (fresh) {
         slot = h;
         waits = 1;
@@ -2762,7 +2870,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
         id = old;
       }
     }
-    if (alive && !tail && !waits) arrive();
+    if (alive && !tail && !waits && !to_leaf) arrive();
     first = __shfl(first, 0, kHalf);
     if (lane == 0) {
       // Every visit goes to the trace: the first visit of (b, a) clears its
@@ -2770,9 +2878,21 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
       T.tr_key[(size_t)d * n_p + ep] = ((unsigned long long)(uint32_t)b << kActBits) |
                                        (uint32_t)a | (first ? kTraceClaim : 0ull);
       T.tr_val[(size_t)d * n_p + ep] = r;
-      if (won) store_seen(&T.info[id], bk);
+      if (won && tail) store_seen(&T.info[id], bk);
     }
-    if (first) make_full_wide(P, b, blink, b_r, b_psi, b_own, b >= first_new, lane);
+    if (first) {
+      if (lane == 0) {
+        unsigned long long own = 0;             // (a run's first belief has it already)
+        if (!(blink & kLinkHead))
+          own = belief_key(b - P.n_p, load_seen(&T.node[b - P.n_p]).y & kLinkKey);
+        make_full_node(P, b, blink, b_r, own, b >= first_new);
+      }
+      const int a1 = one_action(blink, ob);
+      float4* q = reinterpret_cast<float4*>(rec_psi(T, b));
+      const float4* p0 = reinterpret_cast<const float4*>(T.psi0);
+      for (int i = lane; i < T.ra / 4; i += kHalf) q[i] = with_entry(p0[i], i, a1, b_psi);
+      store_bits<kHalf>(T, b, a1, lane);
+    }
     if (alive) ++d;
   };
   // The end of the episode: its leaf, its run word.
@@ -2787,27 +2907,15 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
                      __float_as_uint(hv), 0u);
         run = (uint32_t)tl | (uint32_t)(D - tl + 1) << kRunLenShift;
       } else {
-        run = (uint32_t)D;
-        int first = 0;
-        if (lane == 0) first = claim(T, id, link);
-        first = __shfl(first, 0, kHalf);
-        if (D >= kDirectLevel && (link & kLinkFull)) {
-          if (lane == 0) {
-            atomicAdd(&T.info[id].leaf_cnt, 1);
-            if (fx) atomicAdd(&T.node[id].u.leaf_h, fx);
-          }
-        } else {
-          run |= kRunLeaf;
-          if (lane == 0) {
-            T.tr_key[(size_t)D * n_p + ep] =
-                (unsigned long long)(uint32_t)id | (first ? kTraceClaim : 0ull);
-            T.tr_val[(size_t)D * n_p + ep] = hv;
-          }
+        run = (uint32_t)D | kRunLeaf | (uint32_t)tl << kRunLenShift;
+        if (lane == 0) {
+          T.tr_key[(size_t)D * n_p + ep] =
+              id < 0 ? kTraceSlot | (uint32_t)~id : (unsigned long long)(uint32_t)id;
+          T.tr_val[(size_t)D * n_p + ep] = hv;
         }
-        if (first) make_full_wide(P, id, link, nr, npsi, own, id >= first_new, lane);
       }
     }
-    stores_done();
+    if (tail) stores_done();                    // (nobody waits for another's word)
     if (lane == 0) {
       if (to_publish)
         __hip_atomic_store(&T.h_slot[slot].id, id_head, __ATOMIC_RELAXED,
@@ -2867,6 +2975,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
 
 // Four wavefronts per SIMD (128 registers, a few spilled): each episode is a
 // chain of dependent reads, so residency is what hides them.
+template <bool ONE>
 __global__ __launch_bounds__(kBlock, 4) void k_forward_wide(PlanView P, int k, int D) {
   __shared__ unsigned long long red[kBlock / 64];
   __shared__ uint32_t qsum[kBlock / kHalf][kLongChunks * kHalf];
@@ -2876,7 +2985,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_forward_wide(PlanView P, int k, i
   unsigned long long g = 0, nt = 0;
   if (ep < P.n_p) {
     const Episode e = at_root(P, k, ep, lane == 0);
-    search_wide(P, k, D, ep, e, qsum[threadIdx.x / kHalf], g, nt);
+    search_wide<ONE>(P, k, D, ep, e, qsum[threadIdx.x / kHalf], g, nt);
   }
   tally(P.t, blockIdx.x, lane == 0 ? g : 0ull, lane == 0 ? nt : 0ull, red);
 }
@@ -3207,17 +3316,21 @@ static void launch_forward_rows(const PlanView& P, int k, int D, hipStream_t s) 
 hipError_t launch_forward(const PlanView& P, int k, hipStream_t s) {
   const int D = depth_at(P, k);
   const dim3 b(kBlock);
-  if (P.m.Apad > kMaxA) plan_launch(k_forward_wide, wide_grid(P), b, 0, s, P, k, D);
+  if (one_level(P)) plan_launch(k_forward_wide<true>, wide_grid(P), b, 0, s, P, k, D);
+  else if (P.m.Apad > kMaxA) plan_launch(k_forward_wide<false>, wide_grid(P), b, 0, s, P, k, D);
   else if (P.t.dbg_act) launch_forward_rows<true>(P, k, D, s);
   else launch_forward_rows<false>(P, k, D, s);
   return hipGetLastError();
 }
 hipError_t launch_accum(const PlanView& P, int k, int grid, hipStream_t s) {
   const int D = depth_at(P, k);
-  plan_launch(k_claim_wide, dim3(blocks_for(std::min((long long)D * P.n_p, 1ll << 24))),
-              dim3(kBlock), 0, s, P, k, D);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!one_level(P)) {
+    const int leaves = kBlock / 64 * claim_leaves(P, D);   // episodes a block
+    plan_launch(k_claim_wide, dim3(claim_visit_blocks(P.n_p, D) + (P.n_p + leaves - 1) / leaves),
+                dim3(kBlock), 0, s, P, k, D);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   plan_launch(k_accum, dim3(grid), dim3(kBlock), 0, s, P, k, D);
   return hipGetLastError();
 }
@@ -3265,15 +3378,11 @@ hipError_t launch_pf_resample(const PlanView& P, int t, hipStream_t s) {
   hipLaunchKernelGGL(k_pf_resample, dim3(blocks_for(P.f.M)), dim3(kBlock), 0, s, P, t);
   return hipGetLastError();
 }
-// The parent and key of belief id in a finished plan's tree (link: its
-// record's): inside a run, the belief before it.
-__device__ __forceinline__ unsigned long long own_of(const TreeView& t, int id, uint32_t link,
-                                                     int n_p) {
-  if (link & (kLinkHead | kLinkClaim | kLinkFull)) return t.info[id].own;
-  const int par = id - n_p;
-  return ((unsigned long long)(uint32_t)par << kKeyLowBits) | (t.node[par].link & kLinkKey);
+// Whether a belief of a finished plan has a row of its own.
+__device__ __forceinline__ bool has_row(const TreeView& t, uint32_t link) {
+  return (link & kLinkFull) && !(t.ra > kMaxA && (link & kLinkBare));
 }
-// Action and N, C of the action node of a single-visit belief.
+// Action and N, C of the action node of a belief without.
 struct OneNode {
   int a, n;                  // a = -1: none
   unsigned long long c;
@@ -3300,7 +3409,7 @@ __global__ __launch_bounds__(kBlock) void k_gather(TreeView t, int n_p, int ob, 
        i += (long long)gridDim.x * kBlock) {
     const int id = ids[i];
     const BeliefNode b = t.node[id];
-    const bool full = (b.link & kLinkFull) != 0;
+    const bool full = has_row(t, b.link);
     const OneNode one = one_node(b, ob, scale);
     unsigned char* o = out + (size_t)i * db;
     float* po = reinterpret_cast<float*>(o);
@@ -3314,7 +3423,7 @@ __global__ __launch_bounds__(kBlock) void k_gather(TreeView t, int n_p, int ob, 
     const unsigned long long own = id == 0 ? kEmptyKey : own_of(t, id, b.link, n_p);
     unsigned char* tl = o + dump_tail_off(ra);
     *reinterpret_cast<float*>(tl) = b.V;
-    *reinterpret_cast<int*>(tl + 4) = full ? t.info[id].Nb : 1;
+    *reinterpret_cast<int*>(tl + 4) = (b.link & kLinkFull) ? t.info[id].Nb : 1;
     *reinterpret_cast<int*>(tl + 8) = (int)(own & ((1ull << ob) - 1));
     *reinterpret_cast<int*>(tl + 12) = 0;
     *reinterpret_cast<unsigned long long*>(tl + 16) =
@@ -3408,8 +3517,9 @@ __global__ __launch_bounds__(kBlock) void k_reroot_mark(RerootView V) {
         const int* n = rec_n(V.src, r);
         const uint32_t* bits = rec_bits(V.src, r);
         const bool wide = V.src.ra > kMaxA;   // long rows: columns valid per bitmap
-        if (!(link & kLinkFull)) nn = nv = (link & kLinkAct) ? 1ull : 0ull;
-        for (int j = 0; (link & kLinkFull) && j < V.A; ++j) {
+        const bool full = has_row(V.src, link);
+        if (!full) nn = nv = (link & kLinkAct) ? 1ull : 0ull;
+        for (int j = 0; full && j < V.A; ++j) {
           const int c = (!wide || ((bits[j >> 5] >> (j & 31)) & 1u)) ? n[j] : 0;
           nn += c > 0 ? 1ull : 0ull;
           nv += (unsigned long long)(c > 0 ? c : 0);
@@ -3445,7 +3555,7 @@ __global__ __launch_bounds__(kBlock) void k_reroot_copy(RerootView V) {
   }
   V.new_id[r] = nr;
   const BeliefNode b = V.src.node[r];
-  const bool full = (b.link & kLinkFull) != 0;
+  const bool full = has_row(V.src, b.link);
   const OneNode one = one_node(b, V.obs_bits, V.src_scale);
   const int ra = V.src.ra;
   const bool wide = ra > kMaxA;             // long rows: columns valid per bitmap
@@ -3469,7 +3579,7 @@ __global__ __launch_bounds__(kBlock) void k_reroot_copy(RerootView V) {
   nb.link = kLinkFull;
   nb.u.leaf_h = 0ull;
   V.dst.node[nr] = nb;
-  const int Nb = full ? V.src.info[r].Nb : 1;
+  const int Nb = (b.link & kLinkFull) ? V.src.info[r].Nb : 1;
   if (d_new == 0) {
     V.dst.info[nr] = BeliefInfo{0, Nb, kEmptyKey};
     return;
