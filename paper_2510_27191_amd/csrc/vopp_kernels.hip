@@ -107,13 +107,14 @@ __device__ __forceinline__ int lead_lane(bool in, unsigned long long key) {
   }
   return lead;
 }
-// crowd: lanes of the wavefront may have the same key (lead_lane).  won:
+// crowd (uniform): levels below it are those at which lanes of the wavefront may
+// have the same key (lead_lane); level: the caller's.  won:
 // inserted by this call.  fresh: the stamp found is `stamp` (for a key
 // found, not inserted: another episode of this launch inserted it, and id is
 // not known yet); id: else the belief's id.  b: the key's first bucket, read.
 __device__ __forceinline__ uint32_t probe(const TreeView& t, Bucket& b, unsigned long long key,
-                                          unsigned long long stamp, bool crowd, bool& won,
-                                          bool& fresh, int& id) {
+                                          unsigned long long stamp, int crowd, int level,
+                                          bool& won, bool& fresh, int& id) {
   const uint32_t lines = (t.h_mask + 1) / kBucket;
   for (uint32_t n = 0; n <= 2 * lines; ++n) {
     // The first slot in the key's order that holds the key or is empty.
@@ -141,10 +142,11 @@ __device__ __forceinline__ uint32_t probe(const TreeView& t, Bucket& b, unsigned
     }
     const uint32_t slot = b.base + (uint32_t)at;
     if (empty) {
-      const int lead = lead_lane(crowd, key);
+      int lead = (int)(threadIdx.x & 63);
+      if (crowd) lead = lead_lane(level < crowd, key);
       const bool behind = lead != (int)(threadIdx.x & 63);
       if (!behind) seen = atomicCAS(&t.h_slot[slot].key, kEmptyKey, key | stamp);
-      if (__any(behind)) {                      // what the leader found there, or put
+      if (crowd && __any(behind)) {             // what the leader found there, or put
         const uint32_t lo = __shfl((uint32_t)seen, lead, 64);
         const uint32_t hi = __shfl((uint32_t)(seen >> 32), lead, 64);
         if (behind) {
@@ -661,7 +663,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
     const unsigned long long bk = belief_key(b, low);
     Bucket line;
     if (look) bucket_read(T, bk, line);
-    const bool first = claim_lanes(T, b, blink, d <= P.crowd);
+    const bool first = P.crowd ? claim_lanes(T, b, blink, d <= P.crowd) : claim(T, b, blink);
     next_block();
     const float b_r = nr, b_psi = npsi;
     const unsigned long long b_own = own;
@@ -678,7 +680,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
       // AppendBeliefs: find or insert (b, a, o).
       bool fresh = false;
       int old = -1;
-      h = probe(T, line, bk, stamp, d < P.crowd, won, fresh, old);
+      h = probe(T, line, bk, stamp, P.crowd, d, won, fresh, old);
       if (h == ~0u) {                         // table full: stop and report
         atomicOr((unsigned int*)&T.counters[1], kErrTable);
         alive = false;
@@ -742,7 +744,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
         run = (uint32_t)tl | (uint32_t)(D - tl + 1) << kRunLenShift;
       } else {
         run = (uint32_t)D;
-        const bool first = claim_lanes(T, id, link, d <= P.crowd);
+        const bool first = P.crowd ? claim_lanes(T, id, link, d <= P.crowd) : claim(T, id, link);
         if (D >= kDirectLevel && (link & kLinkFull)) {
           atomicAdd(&T.info[id].leaf_cnt, 1);
           if (fx) atomicAdd(&T.node[id].u.leaf_h, fx);
@@ -2829,7 +2831,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
         Bucket line;
         bucket_read(T, bk, line);
         bool bw = false, bf = false;
-        h = probe(T, line, bk, stamp, false, bw, bf, old);
+        h = probe(T, line, bk, stamp, 0, 0, bw, bf, old);
         won = bw;
         fresh = bf;
       }
@@ -3592,7 +3594,7 @@ __global__ __launch_bounds__(kBlock) void k_reroot_copy(RerootView V) {
   int id = -1;
   Bucket line;
   bucket_read(V.dst, key, line);
-  const uint32_t h = probe(V.dst, line, key, kCarryStamp, false, won, fresh, id);
+  const uint32_t h = probe(V.dst, line, key, kCarryStamp, 0, 0, won, fresh, id);
   if (h == ~0u || !won) {
     atomicOr((unsigned int*)&V.cnt[4 * kRerootCnt], 1u);
     return;
