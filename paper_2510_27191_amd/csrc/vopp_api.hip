@@ -355,7 +355,6 @@ WsSizes sizes_for(const vopp_pomdp* p, int n_p, int K, int depth, int schedule,
   z.K = K;
   z.depth = depth;
   z.Apad = p->view.Apad;
-  z.rs = rec_bytes(z.Apad);
   z.cap_b = 1 + (long long)n_p * z.steps;
   uint64_t h = 1024;
   while (h < 2 * (uint64_t)z.cap_b) h <<= 1;      // load <= 1/2
@@ -366,28 +365,6 @@ WsSizes sizes_for(const vopp_pomdp* p, int n_p, int K, int depth, int schedule,
 // Doubles of a workspace's result record: action, |A| root preferences, V,
 // counts and flags.
 size_t out_len(const WsSizes& z) { return (size_t)std::max(kOutStride, z.Apad + 12); }
-
-size_t bytes_for(const WsSizes& z) {
-  size_t b = 0;
-  auto add = [&](size_t n) { b += align_up(n, 256); };
-  const size_t cb = (size_t)z.cap_b;                 // the belief field arrays
-  add(cb * z.Apad * 4); add(cb * z.Apad * 4); add(cb * z.Apad * 8); add(cb * z.Apad * 8);
-  add(cb * sizeof(BeliefNode)); add(cb * sizeof(BeliefInfo));
-  add(cb * (size_t)rec_bitmap_words(z.Apad) * 4);
-  add(z.hcap * sizeof(HSlot));                       // table
-  const size_t ar = (size_t)std::max(kMaxA, z.Apad);
-  add(ar * 8); add(ar * 8); add(8);                  // root row and its CDF, V(root)
-  add(ar * 8);                                       // running sums of the initial row
-  add(ar * 4);                                       // initial preference row
-  add((size_t)3 * z.Apad * kStripes * 8);            // striped root action nodes
-  add((size_t)z.steps * z.n_p * 4);                  // runs and full beliefs
-  add(64); add(kStatRows * kStripes * 8); add(32); add((z.K + 1) * 4);
-  add(2 * (kMaxDepth + 1) * 4);                      // kept-subtree steps by depth
-  add((size_t)(z.depth + 1) * z.n_p * 8);            // trace words
-  add((size_t)(z.depth + 1) * z.n_p * 4);            // trace values
-  add(out_len(z) * 8);                               // result record
-  return b + 4096;                                   // and the full beliefs' counts
-}
 
 bool fits(const WsSizes& have, const WsSizes& need) {
   return have.n_p >= need.n_p && have.cap_b >= need.cap_b && have.steps >= need.steps &&
@@ -405,9 +382,10 @@ void set_rows(TreeView& t, int Apad, long long cap_b) {
   t.row_end = Apad <= kRowSpreadMaxA ? (uint32_t)(cap_b >> t.row_bits << t.row_bits) : 0u;
 }
 
-// Lays out the buffers of one plan's tree (sizes z) in device memory at base,
-// bytes_for(z) of it, in the order bytes_for counts them.
-void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, double** out) {
+// Lays out the buffers of one plan's tree (sizes z) in device memory at base
+// and returns their bytes (base null: only counts them).
+static size_t carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng,
+                         double** out) {
   Carver c(base);
   const size_t cb = (size_t)z.cap_b;
   set_rows(t, z.Apad, z.cap_b);
@@ -437,6 +415,16 @@ void carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_rng, doub
   t.tr_val = c.take<float>((size_t)(z.depth + 1) * z.n_p);
   *out = c.take<double>(out_len(z));
   t.full_cnt = c.take<unsigned int>(kMaxDepth + 1);
+  return align_up(c.off, 256);
+}
+
+// (The last term keeps what fits into a fixed amount of memory, such as the
+// allocation-free plan's, as it was.)
+size_t bytes_for(const WsSizes& z) {
+  TreeView t{};
+  int* rng = nullptr;
+  double* out = nullptr;
+  return carve_tree(nullptr, z, t, &rng, &out) + 4096 - 256;
 }
 
 vopp_status ws_alloc(const WsSizes& z, vopp_workspace** out) {
@@ -901,12 +889,9 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   ws->n_prev_beliefs = (int)nb;
   ws->n_prev_actions = (int)na;
   ws->last_A = A;
-  ws->last_apad = p->view.Apad;
   ws->last_steps = steps;
   ws->last_n_p = prm->n_particles;
   ws->last_K = k_run;
-  ws->last_depth = depth;
-  ws->last_schedule = prm->schedule;
   ws->last_fix_inv64 = P.fix_inv64;
   ws->last_tree = P.t;
   ws->last_obs_bits = p->view.obs_bits;

@@ -69,13 +69,13 @@ namespace vopp {
 std::vector<Phase> plan_phases(const vopp_pomdp* p, const PlanView& P, int accum_cap,
                                int backup_cap) {
   std::vector<Phase> ph;
-  ph.push_back({kPhaseSetup, 0, 0, setup_blocks(P)});
+  ph.push_back({kPhaseSetup, 0, setup_blocks(P)});
   for (int k = 1; k <= P.K; ++k) {
-    ph.push_back({kPhaseForward, k, 0, forward_blocks(P)});
-    ph.push_back({kPhaseFold, k, 0, fold_grid(P, k, std::min(accum_cap, backup_cap))});
-    ph.push_back({kPhaseFull, k, 0, std::min(backup_cap, full_grid(P, k, nullptr))});
+    ph.push_back({kPhaseForward, k, forward_blocks(P)});
+    ph.push_back({kPhaseFold, k, fold_grid(P, k, std::min(accum_cap, backup_cap))});
+    ph.push_back({kPhaseFull, k, std::min(backup_cap, full_grid(P, k, nullptr))});
   }
-  ph.push_back({kPhaseSelect, 0, 0, 1});
+  ph.push_back({kPhaseSelect, 0, 1});
   return ph;
 }
 
@@ -134,7 +134,6 @@ vopp_status build_schedule(vopp_batch* b) {
       it.inst = i;
       it.kind = f.kind;
       it.a0 = f.a0;
-      it.a1 = f.a1;
       it.blk0 = blocks;
       it.nblk = f.nblk;
       blocks += f.nblk;
@@ -164,7 +163,6 @@ vopp_status build_schedule(vopp_batch* b) {
       it.inst = i;
       it.kind = f.kind;
       it.a0 = f.a0;
-      it.a1 = f.a1;
       it.blk0 = 0;
       it.nblk = f.nblk;
       if (f.kind == kPhaseForward) {        // fewer, larger forward tiles

@@ -252,10 +252,6 @@ __host__ __device__ inline int rec_bitmap_quads(int ra) { return (ra + 127) / 12
 __host__ __device__ inline int rec_bitmap_words(int ra) {
   return ra > kMaxA ? 4 * rec_bitmap_quads(ra) : 0;
 }
-// Bytes one belief owns across the field arrays.
-__host__ __device__ inline int rec_bytes(int ra) {
-  return 24 * ra + (int)(sizeof(BeliefNode) + sizeof(BeliefInfo)) + 4 * rec_bitmap_words(ra);
-}
 __device__ __forceinline__ float* rec_psi(const TreeView& t, int id) {
   return t.psi + (size_t)id * (size_t)t.ra;
 }
@@ -438,7 +434,7 @@ enum : int {
 // One phase of one instance inside a batched launch: blocks
 // [blk0, blk0 + nblk) of the launch run phase `kind` of instance `inst`.
 struct BatchItem {
-  int inst, kind, a0, a1, blk0, nblk;
+  int inst, kind, a0, blk0, nblk;
 };
 
 // The persistent batched launch: a work queue over every instance's phase

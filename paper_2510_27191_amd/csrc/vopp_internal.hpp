@@ -27,7 +27,7 @@ struct vopp_pomdp {
 
 namespace vopp {
 struct WsSizes {
-  int n_p = 0, steps = 0, K = 0, depth = 0, Apad = 0, rs = 0;
+  int n_p = 0, steps = 0, K = 0, depth = 0, Apad = 0;
   long long cap_b = 0;
   uint64_t hcap = 0;
 };
@@ -70,8 +70,7 @@ struct vopp_workspace {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   uint32_t wait_turns = vopp::kWaitTurns;
   int n_prev_beliefs = 0, n_prev_actions = 0;
-  int last_A = 0, last_apad = 0, last_steps = 0, last_n_p = 0, last_K = 0,
-      last_depth = 0, last_schedule = 0;
+  int last_A = 0, last_steps = 0, last_n_p = 0, last_K = 0;
   double last_fix_inv64 = 0.0;
   // Per-kernel event timing (vopp_profile_enable).
   bool prof_on = false;
@@ -87,7 +86,7 @@ struct vopp_workspace {
 namespace vopp {
 // One phase of one plan or served request, in execution order.
 struct Phase {
-  int kind, a0, a1, nblk;
+  int kind, a0, nblk;           // a0: iteration, or real step of a served episode
 };
 // The planning phases of a plan (set-up ... select) for the given block caps
 // of the accumulate and backup sweeps.

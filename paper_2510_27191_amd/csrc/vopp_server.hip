@@ -173,9 +173,9 @@ void start_request(vopp_server* s, Episode& e, double arrival) {
   if (e.step > 0) {
     const int t = e.step - 1;
     const int pb = (e.d.n_particles + kBlock - 1) / kBlock;
-    e.phases.push_back({kPhaseEnv, t, 0, 1});
-    e.phases.push_back({kPhasePFWeight, t, 0, pf_segments(e.d.n_particles)});
-    e.phases.push_back({kPhasePFResample, t, 0, pb});
+    e.phases.push_back({kPhaseEnv, t, 1});
+    e.phases.push_back({kPhasePFWeight, t, pf_segments(e.d.n_particles)});
+    e.phases.push_back({kPhasePFResample, t, pb});
   }
   std::vector<Phase> plan = plan_phases(e.d.pomdp, P, kAccumCap, kBackupCap);
   e.phases.insert(e.phases.end(), plan.begin(), plan.end());
@@ -470,7 +470,7 @@ extern "C" vopp_status vopp_server_tick(vopp_server* s, int32_t* pending) {
         e.new_view = false;
       }
       const Phase& f = e.phases[e.next++];
-      it[n] = BatchItem{slot, f.kind, f.a0, f.a1, blocks, f.nblk};
+      it[n] = BatchItem{slot, f.kind, f.a0, blocks, f.nblk};
       blocks += f.nblk;
       ++n;
       amax = std::max(amax, e.d.pomdp->view.Apad);

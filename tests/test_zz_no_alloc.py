@@ -85,3 +85,36 @@ def test_noalloc_rejects_plans_beyond_the_scratch(V):
         assert "allocation-free" in str(e.value)
     finally:
         pom.close()
+
+
+# The largest plans that the scratch takes, of one level and many iterations and of
+# many levels: the memory a plan needs is what its buffers end at.
+@pytest.mark.parametrize("K,depth,schedule", [(256, 1, 0), (255, 1, 0), (63, 1, 0), (1, 64, 1),
+                                              (64, 64, 0), (4, 3, 0)])
+def test_noalloc_at_the_limit(V, K, depth, schedule):
+    inst = I.tabular_dense(21, 7, 3, 4, with_heuristic=True)
+    bel = I.tabular_belief(inst)
+    pom = V.Pomdp.from_instance(inst)
+    try:
+        def need(n_p):
+            return V.footprint(pom, V.params(n_p, seed=3, schedule=schedule), K, depth)
+        lo, hi = 1, 1 << 20                          # the largest n_p that fits
+        while lo < hi:
+            mid = (lo + hi + 1) // 2
+            if 0 < need(mid) <= V.NOALLOC_SCRATCH_BYTES:     # 0: too many beliefs at all
+                lo = mid
+            else:
+                hi = mid - 1
+        prm = V.params(lo, seed=3, schedule=schedule)
+        belt = V.belief_tensor(inst, bel)
+        for _ in range(2):
+            o = noalloc(V, pom, belt, bel.size, K, depth, prm)
+            same(plain(V, pom, belt, bel.size, K, depth, prm), o, pom.nA)
+        import torch
+        out = torch.zeros(pom.nA + 10, dtype=torch.float64, device="cuda")
+        with pytest.raises(V.VoppError) as e:
+            V.plan_noalloc(pom, belt, bel.size, K, depth,
+                           V.params(lo + 1, seed=3, schedule=schedule), out)
+        assert e.value.status == V.VOPP_E_INVALID
+    finally:
+        pom.close()
