@@ -173,10 +173,13 @@ typedef struct {
 
 /* A workspace holds one plan's tree and per-episode trace in HBM, sized for
  * the worst case (beliefs <= 1 + n_p * sum_k D_k <= 2^28), so no plan can
- * overflow it.  Each belief owns a record of 24*ra + 32 bytes rounded up to a
- * multiple of 128 (ra = |A| rounded up to a multiple of 4), stored by level
- * step, and a 16-byte slot of an open-addressing table of
- * 2^ceil(log2(2*(1 + n_p*sum_k D_k))) slots (load <= 1/2). */
+ * overflow it.  The tree is one array per field: for each belief that may be
+ * created 24*ra + 32 bytes over all arrays (ra = |A| rounded up to a multiple
+ * of 4; rows of more than 64 actions 16*ceil(ra/128) more), of which a belief
+ * that only one episode reaches touches 16 to 32, and a 16-byte slot of an
+ * open-addressing table of 2^ceil(log2(2*(1 + n_p*sum_k D_k))) slots.  A plan
+ * uses and clears as many slots of the table as it can fill, at most one per
+ * episode and iteration at load 1/2. */
 typedef struct vopp_workspace vopp_workspace;
 
 /* Bytes of device memory a workspace for (pomdp, params, budget, depth) needs. */
@@ -405,14 +408,14 @@ typedef struct {
   double values[VOPP_MAX_ACTIONS];
 } vopp_result;
 
-/* Launch-shape knobs of a batch.  accum_cap: most tiles (blocks) of one
- * instance's accumulate sweep (a tile loops over its share of the trace);
- * backup_cap: most tiles of one backup sweep of one instance (both in the
- * per-phase launches).  The persistent launch sizes
- * its tiles by work instead: sweep_group chunks of 256 record positions (or
- * trace items, or table slots of the set-up) per sweep tile, forward_group
- * blocks of 256 episodes per forward tile (both >= 1), and runs blocks_per_cu
- * blocks per compute unit (0: as many as fit). */
+/* Launch-shape knobs of a batch.  accum_cap, backup_cap: in the per-phase
+ * launches the smaller of the two bounds the tiles (blocks) of one instance's
+ * trace sweep, and as many again those of its walk along the runs of
+ * single-visit beliefs; backup_cap also bounds those of its full beliefs.  The
+ * persistent launch sizes its tiles by work instead: a tile of the first two
+ * takes the work of sweep_group blocks, a forward tile forward_group blocks of
+ * 256 episodes (both >= 1), and it runs blocks_per_cu blocks per compute unit
+ * (0: as many as fit). */
 typedef struct {
   int32_t accum_cap;
   int32_t backup_cap;

@@ -376,7 +376,6 @@ bool fits(const WsSizes& have, const WsSizes& need) {
 void set_rows(TreeView& t, int Apad, long long cap_b) {
   t.ra = Apad;
   t.bw = rec_bitmap_words(Apad);
-  // Rows of more than kRowSpreadMaxA actions keep their order.
   t.row_bits = 16;
   while (t.row_bits > kRowSpread && (cap_b >> t.row_bits) == 0) --t.row_bits;
   t.row_end = Apad <= kRowSpreadMaxA ? (uint32_t)(cap_b >> t.row_bits << t.row_bits) : 0u;

@@ -11,6 +11,8 @@
 //               episode creates a belief it is alone: the rest of its path is
 //               a run of single-visit records, written without any look-up
 //               (see vopp_device.hpp).
+//   claim       long rows (|A| > kMaxA) only: first visits of action nodes, and
+//               the leaves that became full.
 //   accumulate  folds the trace of visits into the full beliefs (LDS-aggregated
 //               atomics) and lists the beliefs that became full.
 //   backup      Alg. 3 over every belief: the runs first, each walked bottom-up
@@ -28,9 +30,11 @@
 //
 // Every phase is a __device__ function of (plan view, block index within the
 // phase, block count of the phase).  The single-plan path launches one kernel
-// per phase; the batched path launches k_batch, whose blocks each run one
-// phase of one instance of a batch (BatchItem), so one launch advances every
-// instance of the batch by one phase.
+// per phase (for rows of up to kMaxA actions three per iteration: the search,
+// the trace together with the runs, the full beliefs together with the root);
+// the batched path launches k_batch, whose blocks each run one phase of one
+// instance of a batch (BatchItem), so one launch advances every instance of
+// the batch by one phase.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -3134,8 +3138,15 @@ __global__ __launch_bounds__(kBlock) void k_batch(const PlanView* __restrict__ v
 // block's writes (agent scope) before it counts; the last finisher publishes
 // the next phase with a release; a taker acquires after the add.  A block
 // that finds no tile sleeps briefly and looks again; it returns once every
-// instance is past its last phase.  Tiles never wait on anything, so every
-// taken tile finishes and the queue drains whatever the residency.
+// instance is past its last phase.
+//
+// The queue drains whatever the residency.  A tile may wait for another tile of
+// its phase, but only for work that a running block has already taken and that
+// waits for nothing itself: an episode of a forward tile waits for the creator of
+// a belief, which inserted it and so runs, and creators never wait (search()); a
+// tile of the full beliefs waits for items of lower numbers, which are taken in
+// that order (dev_full()).  Tiles that ran in another order than they are taken,
+// creators that wait, or items given out ahead of time would break that.
 __global__ void k_persist_reset(PersistView V) {
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (i < V.n) {
