@@ -10,8 +10,9 @@ K = 10 iterations, 8 obstacle disks, observations keyed on a 0.5 grid.  Inputs
 Prints one JSON line:
   value        particle-steps/s (generative-model calls per second, whole job)
   latency_ms   p50 / p99 of the per-plan wall time (host call to result)
-  roofline     achieved algorithmic GB/s of the dominant kernel (its launches'
-               own start and end timestamps) against the 8 TB/s HBM peak
+  roofline     the method's bytes over the time of the dominant launches (their own
+               start and end timestamps) against the 8 TB/s HBM peak, a rate
+               normalised to the method, and the traffic measured for them
   cpu_baseline the serial CPU oracle timed on a bounded sample of the workload
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -85,21 +86,23 @@ def leaf_sweep_visits(n_p, K, depth, counts):
     return total
 
 
-# Measured HBM traffic of the dominant kernels per launch (bytes), from the
-# rocprofv3 FETCH_SIZE / WRITE_SIZE passes summarised in
-# profiles/planning_step_hbm_traffic.md.  "copy": each counter scaled by what it
-# reads for a plain device copy of known size (FETCH_SIZE x 2.0, WRITE_SIZE x
-# 1.0).  "gather": FETCH_SIZE unscaled, which is what the counter reads for
-# random 16-byte reads (128 B per access, one cache line), the access pattern of
-# these kernels.  Valid only for the kernel sources they were taken on (hash
-# below); otherwise `traffic` is reported as null.
+# Measured HBM traffic of the groups of launches above, bytes per launch (the
+# mean over a plan's launches of the group), from the rocprofv3 FETCH_SIZE /
+# WRITE_SIZE passes summarised in profiles/planning_step_hbm_traffic.md.  "copy":
+# each counter scaled by what it reads for a plain device copy of known size
+# (FETCH_SIZE x 2.0, WRITE_SIZE x 1.0).  "gather": FETCH_SIZE unscaled, which is
+# what the counter reads for random 16-byte reads (128 B per access, one cache
+# line).  Valid only for the kernel sources they were taken on (hash below);
+# otherwise `traffic` is reported as null.
 MEASURED_TRAFFIC = {
-    "sources_sha256_16": "ea77e652ac2a13d4",
-    "backup_level": {"nav2d": 3.91e+07, "sparse4096": 1.294e+08},
-    "forward": {"nav2d": 1.31e+08, "sparse4096": 6.829e+08},
-    "gather_scale": {
-        "backup_level": {"nav2d": 2.69e+07, "sparse4096": 8.177e+07},
-        "forward": {"nav2d": 1.073e+08, "sparse4096": 4.898e+08},
+    "sources_sha256_16": "0d3af634f193a7e2",
+    "copy": {
+        "forward": {"nav2d": 4.537e+07, "sparse4096": 4.126e+08},
+        "backup": {"nav2d": 4.625e+07, "sparse4096": 9.091e+07},
+    },
+    "gather": {
+        "forward": {"nav2d": 3.440e+07, "sparse4096": 2.473e+08},
+        "backup": {"nav2d": 3.034e+07, "sparse4096": 6.081e+07},
     },
 }
 
@@ -572,9 +575,11 @@ def bench_plain(V, I, name, steps, warmup, event_profile, cpu):
                         avg_launch_us=ms * 1e3 / launches,
                         bytes_per_launch=total[dom] / launches,
                         bytes_per_plan=total[dom] / steps,
-                        byte_model="the method's bytes per unit of work (per particle "
-                                   "step, new node, belief and action-node visit) "
-                                   "times the units each timed plan counted",
+                        byte_model="a method-normalised rate, not bandwidth used: the "
+                                   "method's bytes per unit of work (per particle step, "
+                                   "new node, belief and action-node visit) times the "
+                                   "units each timed plan counted; beliefs of a single "
+                                   "visit are kept in less (`traffic` is what was moved)",
                         timing="start and end timestamps of each launch's own dispatch "
                                "(HIP events taken by hipExtLaunchKernel on the plan stream), "
                                "over the timed plans run again")
@@ -583,16 +588,15 @@ def bench_plain(V, I, name, steps, warmup, event_profile, cpu):
                 roof["units_per_launch"] = {"belief_visits": sw[0],
                                             "internal_belief_visits": sw[1],
                                             "action_node_visits": sw[2]}
-            tr = MEASURED_TRAFFIC.get(dom, {}).get(name)
+            tr = MEASURED_TRAFFIC["copy"].get(dom, {}).get(name)
             if tr is not None and kernel_sources_hash() == MEASURED_TRAFFIC["sources_sha256_16"]:
                 roof["traffic"] = tr
                 roof["traffic_calibration"] = "plain device copy (FETCH_SIZE x 2, WRITE_SIZE x 1)"
                 roof["traffic_GBs"] = tr / (ms * 1e-3 / launches) / 1e9
                 roof["traffic_over_method_bytes"] = tr / (total[dom] / launches)
-                tg = MEASURED_TRAFFIC["gather_scale"].get(dom, {}).get(name)
-                if tg is not None:
-                    roof["traffic_gather_calibration"] = tg
-                    roof["traffic_gather_over_method_bytes"] = tg / (total[dom] / launches)
+                tg = MEASURED_TRAFFIC["gather"][dom][name]
+                roof["traffic_gather_calibration"] = tg
+                roof["traffic_gather_over_method_bytes"] = tg / (total[dom] / launches)
         else:
             roof.update(achieved=None, frac=None,
                         note=f"dominant kernel {dom} has no byte model")
