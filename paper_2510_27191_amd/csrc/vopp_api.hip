@@ -585,6 +585,7 @@ int full_grid(const PlanView& P, int k, const std::function<long long(int)>& kep
   // Lanes per belief (kRowLanes of the row's width).
   const int A = P.m.Apad, lanes = A <= 4 ? 1 : A <= 8 ? 2 : A <= 16 ? 4 : A <= 32 ? 8 : 16;
   long long items = 1;
+  if (one_level(P)) items += ((long long)P.n_p * k + kBlock - 1) / kBlock;
   for (int dep = 1; dep <= depth_at(P, k); ++dep)
     items += (long long)lanes * backup_grid(P, dep, k, kFullCap, kept ? kept(dep) : 0);
   return (int)std::min(items, (long long)kFullCap);
@@ -805,6 +806,7 @@ static vopp_status plan_common(const vopp_pomdp* p, const void* belief, int32_t 
   if (ws->z.Apad < p->view.Apad) return fail(VOPP_E_INVALID, "workspace built for fewer actions");
   hipStream_t s = (hipStream_t)stream;
   PlanView P = make_view(p, ws, belief, n_belief, budget, depth, prm);
+  P.t.one = depth == 1;
   if (draw_act) {
     P.t.dbg_act = draw_act;
     P.t.dbg_obs = draw_obs;
@@ -995,6 +997,7 @@ extern "C" vopp_status vopp_plan_noalloc(const vopp_pomdp* p, const void* belief
   carve_tree(base, z, w.tree, &w.carry_rng_dev, &unused_out);
   w.out_dev = result;
   PlanView P = make_view(p, &w, belief, n_belief, budget, depth, prm);
+  P.t.one = depth == 1;
   P.short_out = 1;
   int steps = 0;
   return enqueue_plan(p, &w, P, (hipStream_t)stream, &steps);

@@ -68,8 +68,8 @@ struct HSlot {
 // episodes share, and beliefs that became full in this iteration):
 //   level d < D: (id << kActBits) | action;  leaf (d = D): id;
 //   kTraceClaim: this visit made the belief full;  kEmptyKey: counted already.
-//   kTraceSlot: a leaf of long rows by its table slot (until k_claim_wide, or
-//   in a plan of one level).
+//   kTraceSlot: a leaf by its table slot (long rows until k_claim_wide, plans of
+//   one level).
 constexpr unsigned long long kTraceClaim = 1ull << 62;
 constexpr unsigned long long kTraceSlot = 1ull << 61;
 constexpr int kDirectLevel = 2;             // levels >= this count in place
@@ -84,7 +84,8 @@ constexpr uint32_t kLinkClaim = 1u << 29;   // another episode reached it
 constexpr uint32_t kLinkFull = 1u << 30;    // its rows hold it (set after the
                                             // iteration that claimed it)
 constexpr uint32_t kLinkInner = 1u << 31;   // full, and so is a child of it
-constexpr uint32_t kLinkBare = 1u << 31;    // long rows: a full leaf without a row
+constexpr uint32_t kLinkBare = 1u << 31;    // long rows, plans of one level: a full
+                                            // leaf without a row
 
 // An episode's run of one iteration (TreeView::run): levels 0 .. tl-1 were
 // visits of existing beliefs (trace rows), then len beliefs were created, at
@@ -195,6 +196,7 @@ struct TreeView {
   uint32_t* bits;                // [cap * bw] long rows only (see below)
   int ra;
   int bw;                        // bitmap words per belief (0 up to kMaxA actions)
+  int one;                       // of a plan of one level (one_level)
   HSlot* h_slot;                 // [h_mask + 1] open-addressing table
   uint32_t h_mask;               // of the present plan (the array may be longer)
   double* psi_root;              // [nA]
@@ -301,6 +303,7 @@ struct EpisodeView {
 };
 
 constexpr int kBackupCap = 2048;            // default block cap of a backup sweep
+constexpr int kFullCap = 512;               // block cap of a sweep of full beliefs
 constexpr int kStripes = 64;                // stripes of each tree statistic
 constexpr int kStatRows = 9;                // rows of kStripes in TreeView::stats
 constexpr int kStatNear = 5;                // row of the near-tie draw count
@@ -373,15 +376,15 @@ __host__ __device__ inline int first_step(const PlanView& P, int k) {
   const int ramp = P.schedule == 1 ? 0 : (j < P.depth ? j : P.depth);
   return P.carry_steps + ramp * (ramp + 1) / 2 + (j - ramp) * P.depth;
 }
-// A plan of one level over long rows: its beliefs besides the root are leaves
-// in every iteration, none of them draws an action.  They are full (without a
-// row) from the start, so an episode's leaf is a table slot or an id in the
-// trace and nothing else, and the leaf sweep goes by the run words: 154 us for
-// 65 actions, 304 for 3,000 (16,384 episodes, four iterations), 183 and 408 with
-// the leaves claimed by their second visitor as in other plans.
-__host__ __device__ inline bool one_level(const PlanView& P) {
-  return P.depth == 1 && P.m.Apad > kMaxA;
-}
+// A plan of one level: its beliefs besides the root are leaves in every
+// iteration, none of them draws an action.  They are full (without a row) from the
+// start, so an episode's leaf is a table slot or an id in the trace and nothing
+// else: nobody waits for a creator or claims a leaf, and the leaf sweep goes by the
+// run words.  Batches and served episodes take the general way (one kernel runs
+// all their phases).  Four iterations of 16,384 episodes: 154 us for 65 actions,
+// 304 for 3,000, with claims 183 and 408; five of 752 episodes of the navigation
+// model: 143 and 178.
+__host__ __device__ inline bool one_level(const PlanView& P) { return P.t.one != 0; }
 // First entry of TreeView::full for depth d: half of n_p times the level
 // steps that create beliefs of lower depths.
 __host__ __device__ inline long long full_first(const PlanView& P, int d) {

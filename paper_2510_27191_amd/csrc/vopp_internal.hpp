@@ -114,7 +114,6 @@ int backup_grid(const PlanView& P, int dep, int k, int cap, long long kept = 0);
 int fold_grid(const PlanView& P, int k, int cap);
 int chain_grid(const PlanView& P, int k, int cap);
 int full_grid(const PlanView& P, int k, const std::function<long long(int)>& kept);
-constexpr int kFullCap = 512;               // block cap of a sweep of full beliefs
 uint32_t table_mask(int n_p, long long runs);
 // Sizes of a plan; extra_steps: level steps of a kept subtree in front.
 WsSizes sizes_for(const vopp_pomdp* p, int n_p, int K, int depth, int schedule,

@@ -497,7 +497,24 @@ __device__ __forceinline__ bool wait_over(const PlanView& P, uint32_t turns) {
 // Every store of this wavefront so far has reached the point all XCDs see.
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Runs episode ep from e to its end.
+// The leaf of a plan of one level that the calling episode created, found in
+// slot h; the slot's id is read by later launches only.
+__device__ __forceinline__ void make_leaf(const TreeView& T, uint32_t h, int id,
+                                          unsigned long long own) {
+  T.h_slot[h].id = id;
+  BeliefNode nb;
+  nb.V = 0.0f;
+  nb.link = kLinkFull | kLinkBare;
+  nb.u.leaf_h = 0ull;
+  T.node[id] = nb;
+  T.info[id] = BeliefInfo{0, 0, own};
+}
+// The trace word of a leaf that needs no look: its id, or ~(table slot).
+__device__ __forceinline__ unsigned long long leaf_word(int id) {
+  return id < 0 ? kTraceSlot | (uint32_t)~id : (unsigned long long)(uint32_t)id;
+}
+
+// Runs episode ep from e to its end.  ONE: a plan of one level (one_level).
 //
 // Two episodes of one launch may reach the same new belief.  The one that
 // inserted its key owns it and never waits: it goes on along its run, and
@@ -524,7 +541,7 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 // counted its visit with two atomics: 57 us a launch instead of 36 for 65,536
 // episodes of nav2d to depth 10, 202 instead of 142 for sparse4096.
 constexpr int kPolls = 4;
-template <int AM, bool NAV, bool TRACE>
+template <int AM, bool NAV, bool TRACE, bool ONE>
 __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e0,
                        const SearchSmem& L, const DiskCache& dc, unsigned long long& g,
                        unsigned long long& nt) {
@@ -689,6 +706,10 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
         atomicOr((unsigned int*)&T.counters[1], kErrTable);
         alive = false;
         tl = d + 1;
+      } else if (ONE && won) {
+        id = 1 + t0 * P.n_p + ep;
+        tl = 1;
+        make_leaf(T, h, id, bk);
       } else if (won) {
         tail = true;
         head = kLinkHead;
@@ -697,6 +718,8 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
         id_head = id;
         slot = h;
         to_publish = 1;
+      } else if (ONE && fresh) {
+        id = ~(int)h;
       } else if (fresh) {
         slot = h;
         waits = 1;
@@ -704,7 +727,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
         id = old;
       }
     }
-    if (alive && !tail && !waits) arrive(d + 1 < D);
+    if (!ONE && alive && !tail && !waits) arrive(d + 1 < D);
     // Writes of level d: the visit and reward of (b, a) (AppendActions) go
     // to the row if it may be written in this launch, else to the trace.
     unsigned long long tk = kEmptyKey;
@@ -719,7 +742,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
     T.tr_key[(size_t)d * n_p + ep] = tk;
     T.tr_val[(size_t)d * n_p + ep] = r;
     if (first) make_full(P, psi0s, b, blink, b_r, b_psi, b_own, b >= first_new);
-    if (won) store_seen(&T.info[id], bk);
+    if (!ONE && won) store_seen(&T.info[id], bk);
     if (alive) ++d;
   };
   // The end of the episode: its leaf, its run word.
@@ -748,8 +771,12 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
         run = (uint32_t)tl | (uint32_t)(D - tl + 1) << kRunLenShift;
       } else {
         run = (uint32_t)D;
-        const bool first = P.crowd ? claim_lanes(T, id, link, d <= P.crowd) : claim(T, id, link);
-        if (D >= kDirectLevel && (link & kLinkFull)) {
+        const bool first = ONE ? false : P.crowd ? claim_lanes(T, id, link, d <= P.crowd) : claim(T, id, link);
+        if (ONE) {
+          run |= kRunLeaf | (uint32_t)tl << kRunLenShift;
+          T.tr_key[(size_t)D * n_p + ep] = leaf_word(id);
+          T.tr_val[(size_t)D * n_p + ep] = hv;
+        } else if (D >= kDirectLevel && (link & kLinkFull)) {
           atomicAdd(&T.info[id].leaf_cnt, 1);
           if (fx) atomicAdd(&T.node[id].u.leaf_h, fx);
         } else {
@@ -761,7 +788,7 @@ __device__ void search(const PlanView& P, int k, int D, int ep, const Episode& e
         if (first) make_full(P, psi0s, id, link, nr, npsi, own, id >= first_new);
       }
     }
-    stores_done();
+    if (!ONE) stores_done();
     if (to_publish)
       __hip_atomic_store(&T.h_slot[slot].id, id_head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     to_publish = 0;
@@ -895,7 +922,7 @@ __device__ __forceinline__ Episode at_root(const PlanView& P, int k, int ep, boo
 }
 
 // All episodes from the root, one thread each.
-template <int AM, bool NAV, bool TRACE>
+template <int AM, bool NAV, bool TRACE, bool ONE>
 __device__ void dev_forward(const PlanView& P, int k, int D, int blk, SearchSmem& L) {
   stage_search<NAV>(P, L);
   // dev_full of this iteration starts from nothing.
@@ -905,7 +932,7 @@ __device__ void dev_forward(const PlanView& P, int k, int D, int blk, SearchSmem
   const DiskCache dc = NAV ? load_disks(P.m) : DiskCache{};
   if (ep < P.n_p) {
     const Episode e = at_root(P, k, ep, true);
-    search<AM, NAV, TRACE>(P, k, D, ep, e, L, dc, g, nt);
+    search<AM, NAV, TRACE, ONE>(P, k, D, ep, e, L, dc, g, nt);
   }
   tally(P.t, blk, g, nt, L.wave);
 }
@@ -1256,6 +1283,48 @@ __device__ void dev_backup_leaf(const PlanView& P, int dep, int k, int blk, int 
   }
   if (n && counts_tree(P, k) && threadIdx.x == 0)
     atomicAdd(&stat_bank(P, k)[kStripes + blk % kStripes], n);
+}
+
+// The leaves of one item of a plan of one level: run_chunks blocks of runs, one
+// unless there are more than kFullCap of them; returns how many.  Every thread
+// of the block calls.
+__device__ __forceinline__ int run_chunks(const PlanView& P, int k) {
+  constexpr int all = kBlock * kFullCap;
+  return (k * P.n_p + all - 1) / all;
+}
+__device__ __forceinline__ int run_items(const PlanView& P, int k) {
+  const int per = kBlock * run_chunks(P, k);
+  return (k * P.n_p + per - 1) / per;
+}
+__device__ __forceinline__ int run_leaves(const PlanView& P, int k, int item, Smem& sm) {
+  const TreeView& T = P.t;
+  const int chunks = run_chunks(P, k);
+  int n = 0;
+  for (int c = item * chunks; c < (item + 1) * chunks; ++c) {
+    const int i = c * kBlock + (int)threadIdx.x;
+    bool has = false;
+    unsigned long long target = 0, f = 0;
+    if (i < k * P.n_p) {
+      // All reads at once; of no belief, if the run word says that there is none.
+      const int kk = i / P.n_p;
+      const int id = 1 + first_step(P, kk + 1) * P.n_p + (i - kk * P.n_p);
+      const uint32_t run = T.run[i];
+      const uint4 q = *reinterpret_cast<const uint4*>(&T.node[id]);
+      const BeliefInfo in = T.info[id];
+      has = ((run >> kRunLenShift) & kRunMask) != 0u;
+      if (has) {
+        float V;
+        int N;
+        leaf_value(P, id, q, in, V, N);
+        target = parent_of(in.own, P.m.obs_bits);
+        f = push_value(P, V, N);
+      }
+    }
+    const int m = __syncthreads_count(has);
+    if (m) push_shared(T, sm.agg, target, f);   // uniform
+    n += m;
+  }
+  return n;
 }
 
 // Iterations of one level over long rows: every run is one leaf, which pushes into
@@ -1664,13 +1733,15 @@ __device__ void dev_backup_root(const PlanView& P, int k, Smem& sm, Wait wait);
 // invalidation, only its own adds to have arrived.  Most depths hold no full
 // belief: they cost nothing here and about 4.4 us each as a launch of their
 // own (nav2d, depth 10: nine of them and the root's, in every iteration).
-template <int AM>
+template <int AM, bool ONE>
 __device__ void dev_full(const PlanView& P, int k, int blk, Smem& sm) {
   const TreeView& T = P.t;
   const int D = depth_at(P, k);
   const int lane = threadIdx.x & 63;
   const FullSet leaves = full_set(P, D);
-  const int n_leaf = (leaves.n + kBlock - 1) / kBlock;
+  const int n_set = (leaves.n + kBlock - 1) / kBlock;
+  // (a plan of one level: its own leaves by the run words, after the kept ones)
+  const int n_leaf = n_set + (ONE ? run_items(P, k) : 0);
   // Lane l: the first item of depth D - 1 - l; lane D - 1: the root's.
   const int my_dep = D - 1 - lane;
   int n = 0;
@@ -1712,10 +1783,14 @@ __device__ void dev_full(const PlanView& P, int k, int blk, Smem& sm) {
       if (threadIdx.x == 0) atomicAdd(&T.counters[3], 1ull);
     };
     if (dep == D) {
-      full_leaves(P, leaves, D, item * kBlock, sm);
-      leaf_cnt += min(kBlock, leaves.n - item * kBlock);
+      if (!ONE || item < n_set) {
+        full_leaves(P, leaves, D, item * kBlock, sm);
+        leaf_cnt += min(kBlock, leaves.n - item * kBlock);
+      } else {
+        leaf_cnt += run_leaves(P, k, item - n_set, sm);
+      }
       pushed();
-    } else {
+    } else if constexpr (!ONE) {
       full_level<AM>(P, full_set(P, dep), dep, k, (item - first) * per, sm, cnt, wait, pushed);
     }
   }
@@ -2850,15 +2925,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
       } else if (ONE && won) {
         id = 1 + t0 * P.n_p + ep;
         tl = 1;
-        if (lane == 0) {
-          T.h_slot[h].id = id;                  // (read by later launches only)
-          BeliefNode nb;
-          nb.V = 0.0f;
-          nb.link = kLinkFull | kLinkBare;
-          nb.u.leaf_h = 0ull;
-          T.node[id] = nb;
-          T.info[id] = BeliefInfo{0, 0, bk};
-        }
+        if (lane == 0) make_leaf(T, h, id, bk);
       } else if (won) {
         tail = true;
         head = kLinkHead;
@@ -2915,8 +2982,7 @@ __device__ void search_wide(const PlanView& P, int k, int D, int ep, const Episo
       } else {
         run = (uint32_t)D | kRunLeaf | (uint32_t)tl << kRunLenShift;
         if (lane == 0) {
-          T.tr_key[(size_t)D * n_p + ep] =
-              id < 0 ? kTraceSlot | (uint32_t)~id : (unsigned long long)(uint32_t)id;
+          T.tr_key[(size_t)D * n_p + ep] = leaf_word(id);
           T.tr_val[(size_t)D * n_p + ep] = hv;
         }
       }
@@ -3011,11 +3077,11 @@ __global__ __launch_bounds__(kBlock) void k_setup(PlanView P) {
 }
 // The phases of one iteration return at once when a time budget ran out
 // at the end of an earlier iteration.
-template <int AM, bool NAV, bool TRACE>
+template <int AM, bool NAV, bool TRACE, bool ONE>
 __global__ __launch_bounds__(kBlock) void k_forward(PlanView P, int k, int D) {
   __shared__ SearchSmem L;
   if (budget_spent(P, k)) return;
-  dev_forward<AM, NAV, TRACE>(P, k, D, blockIdx.x, L);
+  dev_forward<AM, NAV, TRACE, ONE>(P, k, D, blockIdx.x, L);
 }
 __global__ __launch_bounds__(kBlock) void k_accum(PlanView P, int k, int D) {
   __shared__ Smem sm;
@@ -3043,7 +3109,13 @@ template <int AM>
 __global__ __launch_bounds__(kBlock) void k_full(PlanView P, int k) {
   __shared__ Smem sm;
   if (budget_spent(P, k)) return;
-  dev_full<AM>(P, k, blockIdx.x, sm);
+  dev_full<AM, false>(P, k, blockIdx.x, sm);
+}
+template <int AM>
+__global__ __launch_bounds__(kBlock) void k_full_one(PlanView P, int k) {
+  __shared__ Smem sm;
+  if (budget_spent(P, k)) return;
+  dev_full<AM, true>(P, k, blockIdx.x, sm);
 }
 template <int QPL>
 __global__ __launch_bounds__(kBlock) void k_backup_level_wide(PlanView P, int dep, int k) {
@@ -3077,11 +3149,11 @@ __device__ __forceinline__ void run_rows(const PlanView& P, const BatchItem& it,
   const int k = it.a0;
   switch (it.kind) {
     case kPhaseForward:
-      if (AM == 4 && P.m.kind == kNav) dev_forward<AM, true, false>(P, k, depth_at(P, k), blk, L);
-      else dev_forward<AM, false, false>(P, k, depth_at(P, k), blk, L);
+      if (AM == 4 && P.m.kind == kNav) dev_forward<AM, true, false, false>(P, k, depth_at(P, k), blk, L);
+      else dev_forward<AM, false, false, false>(P, k, depth_at(P, k), blk, L);
       break;
     case kPhaseFold: dev_fold<AM>(P, k, blk, it.nblk, sm); break;
-    case kPhaseFull: dev_full<AM>(P, k, blk, sm); break;
+    case kPhaseFull: dev_full<AM, false>(P, k, blk, sm); break;
     default: break;
   }
 }
@@ -3315,24 +3387,27 @@ hipError_t launch_setup(const PlanView& P, hipStream_t s) {
 static dim3 wide_grid(const PlanView& P) {
   return dim3((P.n_p + kBlock / kHalf - 1) / (kBlock / kHalf));
 }
-template <bool TRACE>
+template <bool TRACE, bool ONE>
 static void launch_forward_rows(const PlanView& P, int k, int D, hipStream_t s) {
   const dim3 g(forward_blocks(P)), b(kBlock);
   const int Ap = P.m.Apad;
-  if (P.m.kind == kNav) plan_launch(k_forward<4, true, TRACE>, g, b, 0, s, P, k, D);
-  else if (Ap <= 4) plan_launch(k_forward<4, false, TRACE>, g, b, 0, s, P, k, D);
-  else if (Ap <= 8) plan_launch(k_forward<8, false, TRACE>, g, b, 0, s, P, k, D);
-  else if (Ap <= 16) plan_launch(k_forward<16, false, TRACE>, g, b, 0, s, P, k, D);
-  else if (Ap <= 32) plan_launch(k_forward<32, false, TRACE>, g, b, 0, s, P, k, D);
-  else plan_launch(k_forward<kMaxA, false, TRACE>, g, b, 0, s, P, k, D);
+  if (P.m.kind == kNav) plan_launch(k_forward<4, true, TRACE, ONE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 4) plan_launch(k_forward<4, false, TRACE, ONE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 8) plan_launch(k_forward<8, false, TRACE, ONE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 16) plan_launch(k_forward<16, false, TRACE, ONE>, g, b, 0, s, P, k, D);
+  else if (Ap <= 32) plan_launch(k_forward<32, false, TRACE, ONE>, g, b, 0, s, P, k, D);
+  else plan_launch(k_forward<kMaxA, false, TRACE, ONE>, g, b, 0, s, P, k, D);
+}
+template <bool ONE>
+static void launch_forward_of(const PlanView& P, int k, hipStream_t s) {
+  const int D = depth_at(P, k);
+  if (P.m.Apad > kMaxA) plan_launch(k_forward_wide<ONE>, wide_grid(P), dim3(kBlock), 0, s, P, k, D);
+  else if (P.t.dbg_act) launch_forward_rows<true, ONE>(P, k, D, s);
+  else launch_forward_rows<false, ONE>(P, k, D, s);
 }
 hipError_t launch_forward(const PlanView& P, int k, hipStream_t s) {
-  const int D = depth_at(P, k);
-  const dim3 b(kBlock);
-  if (one_level(P)) plan_launch(k_forward_wide<true>, wide_grid(P), b, 0, s, P, k, D);
-  else if (P.m.Apad > kMaxA) plan_launch(k_forward_wide<false>, wide_grid(P), b, 0, s, P, k, D);
-  else if (P.t.dbg_act) launch_forward_rows<true>(P, k, D, s);
-  else launch_forward_rows<false>(P, k, D, s);
+  if (one_level(P)) launch_forward_of<true>(P, k, s);
+  else launch_forward_of<false>(P, k, s);
   return hipGetLastError();
 }
 hipError_t launch_accum(const PlanView& P, int k, int grid, hipStream_t s) {
@@ -3349,7 +3424,8 @@ hipError_t launch_accum(const PlanView& P, int k, int grid, hipStream_t s) {
 }
 hipError_t launch_fold(const PlanView& P, int k, int grid, hipStream_t s) {
   const dim3 g(grid), b(kBlock);
-  VOPP_BY_ROW(k_fold, g, b, s, P, k);
+  if (one_level(P)) plan_launch(k_accum, g, b, 0, s, P, k, depth_at(P, k));   // no runs to walk
+  else VOPP_BY_ROW(k_fold, g, b, s, P, k);
   return hipGetLastError();
 }
 hipError_t launch_chain(const PlanView& P, int k, int grid, hipStream_t s) {
@@ -3363,7 +3439,8 @@ hipError_t launch_backup_leaf(const PlanView& P, int dep, int k, int grid, hipSt
 }
 hipError_t launch_full(const PlanView& P, int k, int grid, hipStream_t s) {
   const dim3 g(grid), b(kBlock);
-  VOPP_BY_ROW(k_full, g, b, s, P, k);
+  if (one_level(P)) VOPP_BY_ROW(k_full_one, g, b, s, P, k);
+  else VOPP_BY_ROW(k_full, g, b, s, P, k);
   return hipGetLastError();
 }
 hipError_t launch_backup_level(const PlanView& P, int dep, int k, int grid, hipStream_t s) {
@@ -3393,7 +3470,7 @@ hipError_t launch_pf_resample(const PlanView& P, int t, hipStream_t s) {
 }
 // Whether a belief of a finished plan has a row of its own.
 __device__ __forceinline__ bool has_row(const TreeView& t, uint32_t link) {
-  return (link & kLinkFull) && !(t.ra > kMaxA && (link & kLinkBare));
+  return (link & kLinkFull) && !((t.ra > kMaxA || t.one) && (link & kLinkBare));
 }
 // Action and N, C of the action node of a belief without.
 struct OneNode {
