@@ -89,9 +89,9 @@ __device__ __forceinline__ void bucket_read(const TreeView& t, unsigned long lon
 // leads or has `in` unset).  Where thousands of episodes share a few new beliefs,
 // each lane's atomic on a belief's table slot or record takes its turn at one
 // address; the leader's serves the lanes behind it (at most kAlone keys that one
-// lane only has are looked at).  A plan of 16,384 episodes, four iterations and
-// two beliefs took 270 us without, 110 with; 65,536 episodes over 30 beliefs of
-// four levels 1,480 and 655.
+// lane only has are looked at).  A plan of 60,000 episodes over 6 beliefs of two
+// levels took 1,499 us without, 748 with; 65,536 over 30 beliefs of four levels
+// 1,480 and 655.
 constexpr int kAlone = 8;
 __device__ __forceinline__ int lead_lane(bool in, unsigned long long key) {
   const int lane = threadIdx.x & 63;
@@ -524,12 +524,12 @@ __device__ __forceinline__ unsigned long long leaf_word(int id) {
 // from the belief like any visitor.  If it draws the owner's own action and
 // observation it follows the owner's run, each belief of it once the owner's run
 // word (TreeView::run) says that it is written; the owner says so one level
-// later, when the record's store has arrived (to the end of the owner's run, as
+// later, when the record's store has arrived.  (To the end of the owner's run, as
 // it was before, the followers of few beliefs waited once per level: 3 x 8
 // levels of 16,384 episodes over 511 beliefs took 484 us, now 408, and 65,536
-// of nav2d over one cell 760, now 690).  Owners run already and wait for
-// nothing, and a turn of the loop
-// moves every other lane of the wavefront on as well, so every wait ends.
+// of nav2d over one cell 760, now 690.)  Owners run already and wait for
+// nothing, and a turn of the loop moves every other lane of the wavefront on as
+// well, so every wait ends.
 // (P.wait_turns bounds them all the same, for a tree that something else wrote
 // to: the episode then ends where it waits and the plan reports an error.)
 //
