@@ -95,14 +95,14 @@ def leaf_sweep_visits(n_p, K, depth, counts):
 # line).  Valid only for the kernel sources they were taken on (hash below);
 # otherwise `traffic` is reported as null.
 MEASURED_TRAFFIC = {
-    "sources_sha256_16": "0d3af634f193a7e2",
+    "sources_sha256_16": "6d17c29d8abd120f",
     "copy": {
-        "forward": {"nav2d": 4.537e+07, "sparse4096": 4.126e+08},
-        "backup": {"nav2d": 4.625e+07, "sparse4096": 9.091e+07},
+        "forward": {"nav2d": 4.549e+07, "sparse4096": 4.145e+08},
+        "backup": {"nav2d": 4.633e+07, "sparse4096": 9.092e+07},
     },
     "gather": {
-        "forward": {"nav2d": 3.440e+07, "sparse4096": 2.473e+08},
-        "backup": {"nav2d": 3.034e+07, "sparse4096": 6.081e+07},
+        "forward": {"nav2d": 3.439e+07, "sparse4096": 2.483e+08},
+        "backup": {"nav2d": 3.038e+07, "sparse4096": 6.082e+07},
     },
 }
 
