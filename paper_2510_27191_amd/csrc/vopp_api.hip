@@ -417,13 +417,13 @@ static size_t carve_tree(void* base, const WsSizes& z, TreeView& t, int** carry_
   return align_up(c.off, 256);
 }
 
-// (The last term keeps what fits into a fixed amount of memory, such as the
-// allocation-free plan's, as it was.)
+// (The last terms are slack: they keep what fits into a fixed amount of memory,
+// such as the allocation-free plan's, as it was.)
 size_t bytes_for(const WsSizes& z) {
   TreeView t{};
   int* rng = nullptr;
   double* out = nullptr;
-  return carve_tree(nullptr, z, t, &rng, &out) + 4096 - 256;
+  return carve_tree(nullptr, z, t, &rng, &out) + 4096 - 512 + align_up((z.K + 1) * 4, 256);
 }
 
 vopp_status ws_alloc(const WsSizes& z, vopp_workspace** out) {
